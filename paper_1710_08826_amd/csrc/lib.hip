@@ -289,7 +289,9 @@ static void compile_tddp3(const json::Value& d, fn_model* m, bool device = true)
   if (!(tau > 0.0) || !(sig > 0.0)) throw Error(FN_E_INVALID, "tddp3: need tau > 0 and sigma_t > 0");
   m->tdt.gamma = 1.0 / tau;
   m->tdt.sigma = sig;
+  m->tdt.tk = time_const(m->tdt.gamma, sig);
   td4_weideman_coefficients(m->tdt.wa, &m->tdt.wL);
+  td4_erfc_coefficients(m->tdt.we);
   m->P = 4 * dc.K + 2;
   m->n_obs = 3;
   // the autotuner's choice on MI355X at 1M events (1024: 90.5 us, 2048: 83.9, 4096: 80.2, 8192: 130)
@@ -358,6 +360,7 @@ static void compile_td4(const json::Value& d, fn_model* m, bool device = true) {
   if (!(tau > 0.0)) throw Error(FN_E_INVALID, "td4: tau must be > 0");
   tc.gamma = 1.0 / tau;
   td4_weideman_coefficients(tc.wa, &tc.wL);
+  td4_erfc_coefficients(tc.we);
   tc.ps_wmax = td4_ps_wmax(tc);
   std::vector<double> fixed;
   auto pair = [&](const char* key, int* n, int* L, int* nr) {

@@ -133,6 +133,7 @@ __global__ __launch_bounds__(kTd4PrologueThreads) void td4_prologue(Td4Const tc,
     t.x = th[tc.n_params - 2];
     t.y = th[tc.n_params - 1];
     t.sigma = fc.sigma;
+    t.tk = time_const(tc.gamma, fc.sigma);
     ok = fc.sigma > 0.0 && fabs(t.y) < 1.0 && isfinite(t.x);
   }
   const bool bad = __syncthreads_or(!ok);
@@ -319,23 +320,22 @@ __global__ void td4_eval(Td4Const tc, const Td4Table* __restrict__ tab, const do
     A = {A.re + x.re, A.im + x.im};
     Ab = {Ab.re + y.re, Ab.im + y.im};
   }
-  const double t = ev[5 * ld + i], s = tb.sigma, s2 = s * s;
-  const double g = exp(-t * t * 0.5 / s2), G = tc.gamma;
-  double hp, dhp, hm, dhm;
-  cplx hc, dhc;
-  h_real(tc.wa, tc.wL, G * (1.0 - tb.y), t, s, s2, g, hp, dhp);
-  h_real(tc.wa, tc.wL, G * (1.0 + tb.y), t, s, s2, g, hm, dhm);
-  h_cplx(tc.wa, tc.wL, {G, -G * tb.x}, t, s, s2, g, hc, dhc);
+  TimeFns T;
+  time_fns<false>(tb.tk, tc.wa, tc.wL, tb.x, tb.y, ev[5 * ld + i], T);
   const double a2 = A.re * A.re + A.im * A.im, b2 = Ab.re * Ab.re + Ab.im * Ab.im;
   const double zr = A.re * Ab.re + A.im * Ab.im, zi = A.re * Ab.im - A.im * Ab.re;
-  const double R = 0.5 * ((a2 + b2) * 0.5 * (hp + hm) + (a2 - b2) * hc.re - 2.0 * zr * 0.5 * (hp - hm) -
-                          2.0 * zi * hc.im);
+  const double R = 0.5 * ((a2 + b2) * T.Hc + (a2 - b2) * T.hr - 2.0 * zr * T.Hs - 2.0 * zi * T.hi);
   p[i] = R / *norm;
 }
 
 // ---------------------------------------------------------------- launchers
 int td4_kmax(int K) { return K; }  // partial rows hold exactly the model's amplitudes
 int td4_nv(const Td4Const& tc, bool grad) { return grad ? 1 + tc.n_params : 1; }
+
+void td4_erfc_coefficients(double* we) {
+  const double c[kErfcN] = {FN_ERFC_COEFFS};
+  std::memcpy(we, c, sizeof(c));
+}
 
 // Fourier coefficients a_n (n = 1..N) of f(theta) = exp(-t^2)(L^2 + t^2),
 // t = L tan(theta/2), by the trapezoidal rule on 2M - 1 interior points of

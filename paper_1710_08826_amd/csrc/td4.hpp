@@ -21,6 +21,7 @@ std::shared_ptr<Td4Jit> td4_jit(const Td4Const& tc);
 int td4_kmax(int K);
 int td4_nv(const Td4Const& tc, bool grad);  // doubles per events-pass partial row: NLL, then the gradient in theta order
 void td4_weideman_coefficients(double* a, double* L);
+void td4_erfc_coefficients(double* we);
 // Bound of the phase-space weight used by the generators (host).
 double td4_ps_wmax(const Td4Const& tc);
 // n unweighted phase-space points (5 rows of leading dimension ld) from key

@@ -69,22 +69,26 @@ __device__ inline cplx faddeeva(const double* __restrict__ wa, double L, cplx z)
   return cmul({t.re + kInvSqrtPi, t.im}, id);
 }
 
-// w(i y), y >= 0 (real on the imaginary axis): Z = (L - y)/(L + y).
-__device__ inline double faddeeva_imag(const double* __restrict__ wa, double L, double y) {
-  const double id = rcp_fast(L + y);
-  const double Z = (L - y) * id;
-  double p = wa[kWeidN - 1];
+// w(i y) = exp(y^2) erfc(y), y >= 0: (K + y) w(i y) as a polynomial in Z =
+// (K - y)/(K + y), which maps [0, inf) to (-1, 1] (the Chebyshev expansion of
+// Schonfelder, Math. Comp. 32 (1978) 1232, in powers of Z; we: its kErfcN
+// coefficients, td4_types.hpp).  Relative error at most 7.2e-16 over y in
+// [1e-6, 1e3] (host emulation; the 40-term form of w(z) on this axis: 1.0e-15).
+__device__ inline double erfcx_pos(const double* __restrict__ we, double y) {
+  const double id = rcp_acc(kErfcK + y);  // its error enters twice, through Z and the last product
+  const double Z = (kErfcK - y) * id;
+  double p = we[kErfcN - 1];
 #pragma unroll
-  for (int n = kWeidN - 2; n >= 0; --n) p = __builtin_fma(p, Z, wa[n]);
-  return __builtin_fma(2.0 * p, id, kInvSqrtPi) * id;
+  for (int n = kErfcN - 2; n >= 0; --n) p = __builtin_fma(p, Z, we[n]);
+  return p * id;
 }
 
 // h(a; t) and dh/da for real a.  g = exp(-t^2/(2 s^2)).
-__device__ inline void h_real(const double* __restrict__ wa, double L, double a, double t, double s, double s2,
-                              double g, double& h, double& dh) {
+__device__ inline void h_real(const double* __restrict__ we, double a, double t, double s, double s2, double g,
+                              double& h, double& dh) {
   const double u = a * s2 - t;
   const double z = u * (kInvSqrt2 / s);
-  const double w = faddeeva_imag(wa, L, fabs(z));
+  const double w = erfcx_pos(we, fabs(z));
   h = z >= 0.0 ? 0.5 * g * w : exp(0.5 * a * a * s2 - a * t) - 0.5 * g * w;
   dh = u * h - s * kInvSqrt2Pi * g;
 }
@@ -111,41 +115,175 @@ __device__ inline void h_cplx(const double* __restrict__ wa, double L, cplx a, d
   dh = {uh.re - s * kInvSqrt2Pi * g, uh.im};
 }
 
+// The time functions of one event and their derivatives: Hc, Hs and dHc/dy,
+// dHs/dy; hr + i hi = Hcos + i Hsin and dhr/dx, dhi/dx.
+struct TimeFns {
+  double Hc, Hs, hr, hi, dHc, dHs, dr, di;
+};
+
+// The resolution constants of one fit (G = 1/tau, s = sigma_t).
+__host__ __device__ inline TimeConst time_const(double G, double s) {
+  TimeConst k;
+  const double s2 = s * s;
+  k.g = G;
+  k.s = s;
+  k.s2 = s2;
+  k.gs2 = G * s2;
+  k.hg2s2 = 0.5 * G * G * s2;
+  k.iz = kInvSqrt2 / s;
+  k.ni2s2 = -0.5 / s2;
+  k.kg = G * s * kInvSqrt2Pi;
+  k.g2s2 = G * G * s2;
+  k.s3 = 3.0 * s;
+  return k;
+}
+
+// Terms 2 k0 + 1 .. 2 k1 of the series of time_fns: c_n = G^n h_n / n! and
+// e_n = n c_n = v c_{n-1} + w c_{n-2} (v = G u, w = G^2 s^2) added to the
+// four sums and, for gradients, their derivatives' sums; qy, qx: y^2k, (-x^2)^k.
+struct TimeSeries {
+  double ce, co;           // c_{2k}, c_{2k-1}
+  double qy, qx;
+  double ey, oy, ex, ox;   // even terms past c_0 and odd terms / y, / x
+  double dey, doy, dex, dox;
+};
+template <bool GRAD>
+__device__ __forceinline__ void time_terms(TimeSeries& a, double v, double w, double y2, double nx2, int k0, int k1) {
+#pragma unroll
+  for (int k = k0; k < k1; ++k) {
+    const double eo = __builtin_fma(v, a.ce, w * a.co);
+    a.co = eo * (1.0 / (2 * k + 1));
+    const double ee = __builtin_fma(v, a.co, w * a.ce);
+    a.ce = ee * (1.0 / (2 * k + 2));
+    a.oy = __builtin_fma(a.co, a.qy, a.oy);
+    a.ox = __builtin_fma(a.co, a.qx, a.ox);
+    if (GRAD) {
+      a.doy = __builtin_fma(eo, a.qy, a.doy);
+      a.dox = __builtin_fma(eo, a.qx, a.dox);
+      a.dey = __builtin_fma(ee, a.qy, a.dey);
+      a.dex = __builtin_fma(ee, a.qx, a.dex);
+    }
+    a.qy *= y2;
+    a.qx *= nx2;
+    a.ey = __builtin_fma(a.ce, a.qy, a.ey);
+    a.ex = __builtin_fma(a.ce, a.qx, a.ex);
+  }
+}
+
+// The time functions at decay time t.  All four are h(a; t) at points a = G +
+// d, d = +-G y and -i G x, near a = G, and h's derivatives follow from h itself:
+// h_0 = h(G; t), h_1 = u h_0 - s g / sqrt(2 pi), h_{n+1} = u h_n + n s^2 h_{n-1}
+// (u = G s^2 - t, g = exp(-t^2 / 2 s^2); for u < 0 the terms of each step have
+// one sign).  So one real h and a Taylor series give what otherwise takes two
+// real and one complex h.  |h_n d^n / n!| <= h_0 r^n / n! with r = max(|x|,
+// |y|) G (|t| + 3 s) for n <= 20, which puts the rest after ten terms below
+// 3e-18 h_0 (3e-16 in the derivatives' sums) for r <= 1/8 and after twenty
+// below 2e-18 (4e-17) for r <= 5/4.  A wave takes ten terms, twenty when one of
+// its events needs them, and the three functions evaluated one by one beyond
+// that (the line lies where twenty terms, 160 multiply-adds, stop sufficing;
+// the three evaluations take about 460 instructions).  The events are few
+// there: mixing parameters of the size fits meet (below 0.01) keep r <= 1/8 up
+// to twelve lifetimes.
+// One NLL and gradient: four-body, 10M events, twenty amplitudes 456 -> 349 us;
+// three-body, 1M events, sixteen resonances 105.8 -> 94.5 us.
+template <bool GRAD>
+__device__ __forceinline__ void time_fns(const TimeConst& k, const double* __restrict__ wt, double wL, double x,
+                                         double y, double t, TimeFns& o) {
+  const double g = exp(t * t * k.ni2s2);
+  const double r = fmax(fabs(x), fabs(y)) * k.g * (fabs(t) + k.s3);
+  if (__any(!(r <= kTimeSeriesMax))) {
+    double hp, dhp, hm, dhm;
+    cplx hc, dhc;
+    const double* we = wt + kWeidN;
+    h_real(we, k.g * (1.0 - y), t, k.s, k.s2, g, hp, dhp);
+    h_real(we, k.g * (1.0 + y), t, k.s, k.s2, g, hm, dhm);
+    h_cplx(wt, wL, {k.g, -k.g * x}, t, k.s, k.s2, g, hc, dhc);
+    o.Hc = 0.5 * (hp + hm);
+    o.Hs = 0.5 * (hp - hm);
+    o.hr = hc.re;
+    o.hi = hc.im;
+    // d hp/dy = -G dh(G(1-y)), d hm/dy = +G dh(G(1+y)), d hc/dx = -i G dh(G(1-ix))
+    o.dHc = 0.5 * k.g * (dhm - dhp);
+    o.dHs = -0.5 * k.g * (dhp + dhm);
+    o.dr = k.g * dhc.im;
+    o.di = -k.g * dhc.re;
+    return;
+  }
+  const double u = k.gs2 - t;
+  const double z = u * k.iz;
+  const double e = 0.5 * g * erfcx_pos(wt + kWeidN, fabs(z));
+  const double c0 = z >= 0.0 ? e : exp(__builtin_fma(-k.g, t, k.hg2s2)) - e;
+  const double v = k.g * u, w = k.g2s2;
+  const double y2 = y * y, nx2 = -x * x;
+  // n = 1, 2
+  const double c1 = __builtin_fma(v, c0, -k.kg * g);
+  const double e2 = __builtin_fma(v, c1, w * c0);
+  TimeSeries a;
+  a.ce = 0.5 * e2;
+  a.co = c1;
+  a.qy = y2;
+  a.qx = nx2;
+  a.oy = a.ox = a.doy = a.dox = c1;
+  a.dey = a.dex = e2;
+  a.ey = a.ce * y2;
+  a.ex = a.ce * nx2;
+  time_terms<GRAD>(a, v, w, y2, nx2, 1, 5);
+  if (__any(r > kTimeSeriesTen)) time_terms<GRAD>(a, v, w, y2, nx2, 5, 10);
+  o.Hc = c0 + a.ey;
+  o.Hs = -y * a.oy;
+  o.hr = c0 + a.ex;
+  o.hi = -x * a.ox;
+  o.dHc = y * a.dey;
+  o.dHs = -a.doy;
+  o.dr = -x * a.dex;
+  o.di = -a.dox;
+}
+
 // ------------------------------------------------------- shape-specialized
 // A shape S gives, as compile-time constants: K, N12, N34, L12[], NR12[],
 // L34[], NR34[] (NR = 1 marks a flat entry), A1[], A2[] (pair entries of
 // every basis amplitude) and T[] (angular factor).
 
-template <int N>
-__device__ __host__ constexpr bool any_l1(const int (&L)[N], const int (&NR)[N]) {
-  bool u = false;
-  for (int r = 0; r < N; ++r) u = u || (L[r] == 1 && !NR[r]);
-  return u;
-}
+// Entry r of pair 12 or 34 of shape S, read as a constant expression: a
+// template parameter bound to the array itself left the compiler with a load
+// and a branch per entry and event.
+template <class S, bool P34>
+struct Td4Pair {
+  static constexpr int N = P34 ? S::N34 : S::N12;
+  static __device__ __forceinline__ constexpr int L(int r) { return P34 ? S::L34[r] : S::L12[r]; }
+  static __device__ __forceinline__ constexpr bool flat(int r) { return (P34 ? S::NR34[r] : S::NR12[r]) != 0; }
+  static constexpr bool any_l1() {
+    bool u = false;
+    for (int r = 0; r < N; ++r) u = u || ((P34 ? S::L34[r] : S::L12[r]) == 1 && !(P34 ? S::NR34[r] : S::NR12[r]));
+    return u;
+  }
+};
 
 // Lineshapes of one pair from its invariant mass m (rt: the fit's m0^2, Kw, Ka).
-template <int N, const int (&L)[N], const int (&NR)[N]>
+template <class S, bool P34>
 __device__ __forceinline__ void pair_amps_s(double m, double sum2, double dif2, double r2,
-                                            const double (*__restrict__ rt)[3], cplx (&amp)[N]) {
+                                            const double (*__restrict__ rt)[3], cplx (&amp)[Td4Pair<S, P34>::N]) {
+  using T = Td4Pair<S, P34>;
   const double s = m * m;
   const double im = rcp_fast(m);
   const double lq = fmax((s - sum2) * (s - dif2), 0.0);
   const double q2 = 0.25 * lq * im * im;
   const double G0 = sqrt_fast(q2) * im;
   double F1 = 1.0, G1 = 0.0;
-  if (any_l1<N>(L, NR)) {
+  constexpr bool l1 = T::any_l1();
+  if (l1) {
     F1 = rsqrt_fast(1.0 + q2 * r2);
     G1 = G0 * q2 * F1 * F1;
   }
 #pragma unroll
-  for (int r = 0; r < N; ++r) {
+  for (int r = 0; r < T::N; ++r) {
     amp[r] = {1.0, 0.0};
-    if (!NR[r]) {
-      const double G = L[r] == 1 ? G1 : G0;
+    if (!T::flat(r)) {
+      const double G = T::L(r) == 1 ? G1 : G0;
       const double a = rt[r][0] - s;
       const double b = rt[r][1] * G;
       const double d = rcp_fast(__builtin_fma(a, a, b * b));
-      const double k = (L[r] == 1 ? rt[r][2] * F1 : rt[r][2]) * d;
+      const double k = (T::L(r) == 1 ? rt[r][2] * F1 : rt[r][2]) * d;
       amp[r] = {k * a, k * b};
     }
   }
@@ -163,8 +301,8 @@ struct Td4Point {
 template <class S>
 __device__ __forceinline__ void td4_point_s(const Td4Const& tc, const Td4Table& tb, double m12, double m34, double c12,
                                             double c34, double phi, Td4Point<S>& p) {
-  pair_amps_s<S::N12, S::L12, S::NR12>(m12, tc.sum12, tc.dif12, tc.r2, tb.r12, p.a12);
-  pair_amps_s<S::N34, S::L34, S::NR34>(m34, tc.sum34, tc.dif34, tc.r2, tb.r34, p.a34);
+  pair_amps_s<S, false>(m12, tc.sum12, tc.dif12, tc.r2, tb.r12, p.a12);
+  pair_amps_s<S, true>(m34, tc.sum34, tc.dif34, tc.r2, tb.r34, p.a34);
   constexpr bool has_sc = [] {
     bool u = false;
     for (int k = 0; k < S::K; ++k) u = u || S::T[k] >= 4;
@@ -267,10 +405,6 @@ __device__ inline void td4_events_body(const Td4Const& tc, const Td4Table* __res
   double acc[NV];
 #pragma unroll
   for (int i = 0; i < NV; ++i) acc[i] = 0.0;
-  const double s = tabs[f].sigma, s2 = s * s, inv2s2 = 0.5 / s2;
-  const double G = tc.gamma;
-  const double ap = G * (1.0 - tabs[f].y), am = G * (1.0 + tabs[f].y);
-  const cplx ac = {G, -G * tabs[f].x};
   const int64_t base = ch * chunk;
   const int64_t end = base + chunk < n ? base + chunk : n;
   LogProd lp;  // -sum ln R enters acc[0] once per thread, at the end
@@ -281,16 +415,10 @@ __device__ inline void td4_events_body(const Td4Const& tc, const Td4Table* __res
     int zero = 0;
     asm volatile("" : "+s"(zero));
     const Td4Table& tb = tabs[f + zero];
-    // time functions first: the lineshapes are not live across the three
-    // rational-approximation evaluations
+    // time functions first: the lineshapes are not live across them
     const double t = ev[5 * ld + i];
-    const double g = exp(-t * t * inv2s2);
-    double hp, dhp, hm, dhm;
-    cplx hc, dhc;
-    const double* wa = tc.wa + zero;  // re-read per event, like the table
-    h_real(wa, tc.wL, ap, t, s, s2, g, hp, dhp);
-    h_real(wa, tc.wL, am, t, s, s2, g, hm, dhm);
-    h_cplx(wa, tc.wL, ac, t, s, s2, g, hc, dhc);
+    TimeFns T;
+    time_fns<GRAD>(tb.tk, tc.wa + zero, tc.wL, tb.x, tb.y, t, T);
     Td4Point<S> pt;
     td4_point_s<S>(tc, tb, ev[i], ev[ld + i], ev[2 * ld + i], ev[3 * ld + i], ev[4 * ld + i], pt);
     cplx A = {0.0, 0.0}, Ab = {0.0, 0.0};
@@ -300,7 +428,8 @@ __device__ inline void td4_events_body(const Td4Const& tc, const Td4Table* __res
       if (S::PA[k] >= 0) A = cfma({tb.c[k][0], tb.c[k][1]}, b, A);
       if (S::PB[k] >= 0) Ab = cfma({tb.cb[k][0], tb.cb[k][1]}, b, Ab);
     }
-    const double Hc = 0.5 * (hp + hm), Hs = 0.5 * (hp - hm);
+    const double Hc = T.Hc, Hs = T.Hs;
+    const cplx hc = {T.hr, T.hi};
     const double a2 = A.re * A.re + A.im * A.im, b2 = Ab.re * Ab.re + Ab.im * Ab.im;
     const double zr = A.re * Ab.re + A.im * Ab.im, zi = A.re * Ab.im - A.im * Ab.re;  // conj(A) Abar
     const double R = 0.5 * ((a2 + b2) * Hc + (a2 - b2) * hc.re - 2.0 * zr * Hs - 2.0 * zi * hc.im);
@@ -321,11 +450,8 @@ __device__ inline void td4_events_body(const Td4Const& tc, const Td4Table* __res
         if (S::PA[k] >= 0) grad_acc(lc, b, acc[1 + S::PA[k]], acc[2 + S::PA[k]]);
         if (S::PB[k] >= 0) grad_acc(lb, b, acc[1 + S::PB[k]], acc[2 + S::PB[k]]);
       }
-      // x: d hc/dx = -i G dh(ac);  y: d hp/dy = -G dh(ap), d hm/dy = +G dh(am)
-      const double dcos = G * dhc.im, dsin = -G * dhc.re;
-      acc[P - 1] += w * 0.5 * ((a2 - b2) * dcos - 2.0 * zi * dsin);
-      const double dHc = 0.5 * G * (dhm - dhp), dHs = -0.5 * G * (dhp + dhm);
-      acc[P] += w * 0.5 * ((a2 + b2) * dHc - 2.0 * zr * dHs);
+      acc[P - 1] += w * 0.5 * ((a2 - b2) * T.dr - 2.0 * zi * T.di);
+      acc[P] += w * 0.5 * ((a2 + b2) * T.dHc - 2.0 * zr * T.dHs);
     }
   }
   acc[0] = -lp.log();

@@ -13,6 +13,33 @@ constexpr int kWeidN = 40;       // terms of the Faddeeva rational approximation
 // sample (2 x rows x K doubles per thread).
 __host__ __device__ constexpr int td4_row_block(int K) { return K > 12 ? 2 : 4; }
 
+// w(i y) = exp(y^2) erfc(y) on y >= 0: kErfcK and the coefficients in Z =
+// (K - y)/(K + y) of (K + y) w(i y), rising powers (Chebyshev expansion of
+// degree 23 computed with 50 digits, rounded once).
+constexpr int kErfcN = 24;
+constexpr double kErfcK = 3.75;
+#define FN_ERFC_COEFFS                                                                             \
+  0x1.178842825349dp+0, 0x1.eae02d0a1456bp-1, 0x1.78fecb4e81b0dp-1, 0x1.f63dd81196191p-2, \
+  0x1.1dc271189e1d8p-2, 0x1.0e3ea224bc968p-3, 0x1.92618b78faeb3p-5, 0x1.9ac6956772b07p-7, \
+  0x1.029006d608353p-10, -0x1.a0b75a1ed9a23p-11, -0x1.6d95256e626cep-12, -0x1.63793f07b8761p-17, \
+  0x1.3a550343ac142p-15, 0x1.2ac332d500810p-17, -0x1.b9620425f3497p-19, -0x1.bc81305359091p-20, \
+  0x1.2b30aeec1a69fp-22, 0x1.1b2f3e2d5daa8p-22, -0x1.bd29fda663e3ap-26, -0x1.5b8e3892d117dp-25, \
+  0x1.7cbe65b7d4a0bp-29, 0x1.77e18f2629084p-28, -0x1.f7c249888c033p-33, -0x1.f79317cac1c2fp-32
+
+// Largest r (td4_device.hpp: time_fns) the time functions' series take with
+// ten terms and with twenty.
+constexpr double kTimeSeriesTen = 0.125;
+constexpr double kTimeSeriesMax = 1.25;
+
+// Constants of the time functions for one decay constant G = 1/tau and one
+// resolution width s: products that do not depend on the event.
+struct TimeConst {
+  double g, s, s2;
+  double gs2, hg2s2, g2s2;  // G s^2, G^2 s^2 / 2, G^2 s^2
+  double iz, ni2s2;         // 1/(s sqrt 2), -1/(2 s^2)
+  double kg, s3;            // G s / sqrt(2 pi), 3 s
+};
+
 struct Td4Const {
   double M;                            // parent mass
   double m1s, m2s, m3s, m4s;           // squared daughter masses
@@ -23,6 +50,7 @@ struct Td4Const {
   double gamma;                        // 1 / tau
   double wL;                           // Faddeeva approximation scale L
   double wa[kWeidN];                   // its polynomial coefficients a_1..a_N
+  double we[kErfcN];                   // real form's coefficients (time_fns takes both at wa)
   int K, n12, n34, n_params;
   int L12[kTd4MaxRes], L34[kTd4MaxRes];
   int nr12[kTd4MaxRes], nr34[kTd4MaxRes];  // 1 = non-resonant (flat) entry
@@ -31,6 +59,9 @@ struct Td4Const {
   // basis function is not a member of that sum
   int pa[kTd4MaxAmp], pb[kTd4MaxAmp];
 };
+
+static_assert(__builtin_offsetof(Td4Const, we) == __builtin_offsetof(Td4Const, wa) + kWeidN * sizeof(double),
+              "we follows wa");
 
 // Fixed constants of one fit (systematic variations change them per fit).
 struct Td4FitConst {
@@ -86,6 +117,7 @@ struct Td4Table {
   double r34[kTd4MaxRes][3];
   double c[kTd4MaxAmp][2], cb[kTd4MaxAmp][2];
   double x, y, sigma;
+  TimeConst tk;                 // time functions' constants (sigma's)
   double valid;
 };
 

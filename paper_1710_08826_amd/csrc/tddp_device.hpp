@@ -20,14 +20,18 @@
 
 namespace fn {
 
-// Decay-time constants of a model: 1/tau, the resolution width and the
-// Faddeeva approximation of the resolution functions.
+// Decay-time constants of a model: 1/tau, the resolution width, the time
+// functions' constants and the coefficients of the resolution functions (wa of
+// the complex form, then we of the real one: time_fns takes both at wa).
 struct TddpTime {
   double gamma;
   double sigma;
+  TimeConst tk;
   double wL;
   double wa[kWeidN];
+  double we[kErfcN];
 };
+static_assert(__builtin_offsetof(TddpTime, we) == __builtin_offsetof(TddpTime, wa) + kWeidN * sizeof(double), "we follows wa");
 
 // Both amplitude sets at one point: A_k(s12, s13) and B_k = A_k(s13, s12).
 // With m2 = m3 (the model requires it) the pair terms at the mirrored point
@@ -79,11 +83,6 @@ __device__ inline void tddp_events_body(const DalitzConst& dc, const DalitzTable
   double acc[NV];
 #pragma unroll
   for (int i = 0; i < NV; ++i) acc[i] = 0.0;
-  const double s = tt.sigma, s2 = s * s, inv2s2 = 0.5 / s2;
-  const double G = tt.gamma;
-  const double x = coef0[4 * K], y = coef0[4 * K + 1];
-  const double ap = G * (1.0 - y), am = G * (1.0 + y);
-  const cplx ac = {G, -G * x};
   const int64_t base = (int64_t)blockIdx.x * chunk;
   const int64_t end = base + chunk < n ? base + chunk : n;
   const double* const r0 = &tab->r[0][0];
@@ -95,14 +94,9 @@ __device__ inline void tddp_events_body(const DalitzConst& dc, const DalitzTable
     asm volatile("" : "+s"(zero));
     const double* r = r0 + zero;
     const double* coef = coef0 + zero;
-    const double* wa = tt.wa + zero;
     const double t = ev[2 * ld + i];
-    const double g = exp(-t * t * inv2s2);
-    double hp, dhp, hm, dhm;
-    cplx hc, dhc;
-    h_real(wa, tt.wL, ap, t, s, s2, g, hp, dhp);
-    h_real(wa, tt.wL, am, t, s, s2, g, hm, dhm);
-    h_cplx(wa, tt.wL, ac, t, s, s2, g, hc, dhc);
+    TimeFns T;
+    time_fns<GRAD>((&tt.tk)[zero], tt.wa + zero, tt.wL, coef[4 * K], coef[4 * K + 1], t, T);
     const double s12 = ev[i], s13 = ev[ld + i];
     double Are[K], Aim[K], Bre[K], Bim[K];
     tddp_basis2<S>(dc, r, s12, s13, Are, Aim, Bre, Bim);
@@ -114,7 +108,8 @@ __device__ inline void tddp_events_body(const DalitzConst& dc, const DalitzTable
       A = cfma({cr, ci}, {Are[k], Aim[k]}, A);
       Ab = cfma({br, bi}, {Bre[k], Bim[k]}, Ab);
     }
-    const double Hc = 0.5 * (hp + hm), Hs = 0.5 * (hp - hm);
+    const double Hc = T.Hc, Hs = T.Hs;
+    const cplx hc = {T.hr, T.hi};
     const double a2 = A.re * A.re + A.im * A.im, b2 = Ab.re * Ab.re + Ab.im * Ab.im;
     const double zr = A.re * Ab.re + A.im * Ab.im, zi = A.re * Ab.im - A.im * Ab.re;  // conj(A) Abar
     const double R = 0.5 * ((a2 + b2) * Hc + (a2 - b2) * hc.re - 2.0 * zr * Hs - 2.0 * zi * hc.im);
@@ -132,11 +127,8 @@ __device__ inline void tddp_events_body(const DalitzConst& dc, const DalitzTable
         grad_acc(lc, {Are[k], Aim[k]}, acc[1 + 2 * k], acc[2 + 2 * k]);
         grad_acc(lb, {Bre[k], Bim[k]}, acc[1 + 2 * K + 2 * k], acc[2 + 2 * K + 2 * k]);
       }
-      // x: d hc/dx = -i G dh(ac);  y: d hp/dy = -G dh(ap), d hm/dy = +G dh(am)
-      const double dcos = G * dhc.im, dsin = -G * dhc.re;
-      acc[1 + 4 * K] += w * 0.5 * ((a2 - b2) * dcos - 2.0 * zi * dsin);
-      const double dHc = 0.5 * G * (dhm - dhp), dHs = -0.5 * G * (dhp + dhm);
-      acc[2 + 4 * K] += w * 0.5 * ((a2 + b2) * dHc - 2.0 * zr * dHs);
+      acc[1 + 4 * K] += w * 0.5 * ((a2 - b2) * T.dr - 2.0 * zi * T.di);
+      acc[2 + 4 * K] += w * 0.5 * ((a2 + b2) * T.dHc - 2.0 * zr * T.dHs);
     }
   }
   acc[0] = -lp.log();
