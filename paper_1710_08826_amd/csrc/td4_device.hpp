@@ -64,7 +64,7 @@ __device__ inline cplx faddeeva(const double* __restrict__ wa, double L, cplx z)
   cplx p = {wa[kWeidN - 1], 0.0};
 #pragma unroll
   for (int n = kWeidN - 2; n >= 0; --n)
-    p = {__builtin_fma(p.re, Z.re, __builtin_fma(-p.im, Z.im, wa[n])), __builtin_fma(p.re, Z.im, p.im * Z.re)};
+    p = {__builtin_fma(p.re, Z.re, fma_sc(-p.im, Z.im, wa[n])), __builtin_fma(p.re, Z.im, p.im * Z.re)};
   const cplx t = cmul({2.0 * p.re, 2.0 * p.im}, id);
   return cmul({t.re + kInvSqrtPi, t.im}, id);
 }
@@ -79,7 +79,7 @@ __device__ inline double erfcx_pos(const double* __restrict__ we, double y) {
   const double Z = (kErfcK - y) * id;
   double p = we[kErfcN - 1];
 #pragma unroll
-  for (int n = kErfcN - 2; n >= 0; --n) p = __builtin_fma(p, Z, we[n]);
+  for (int n = kErfcN - 2; n >= 0; --n) p = fma_sc(p, Z, we[n]);
   return p * id;
 }
 
@@ -189,7 +189,7 @@ __device__ __forceinline__ void time_terms(TimeSeries& a, double v, double w, do
 template <bool GRAD>
 __device__ __forceinline__ void time_fns(const TimeConst& k, const double* __restrict__ wt, double wL, double x,
                                          double y, double t, TimeFns& o) {
-  const double g = exp(t * t * k.ni2s2);
+  const double g = exp_fast(t * t * k.ni2s2);
   const double r = fmax(fabs(x), fabs(y)) * k.g * (fabs(t) + k.s3);
   if (__any(!(r <= kTimeSeriesMax))) {
     double hp, dhp, hm, dhm;
@@ -212,7 +212,7 @@ __device__ __forceinline__ void time_fns(const TimeConst& k, const double* __res
   const double u = k.gs2 - t;
   const double z = u * k.iz;
   const double e = 0.5 * g * erfcx_pos(wt + kWeidN, fabs(z));
-  const double c0 = z >= 0.0 ? e : exp(__builtin_fma(-k.g, t, k.hg2s2)) - e;
+  const double c0 = z >= 0.0 ? e : exp_fast(__builtin_fma(-k.g, t, k.hg2s2)) - e;
   const double v = k.g * u, w = k.g2s2;
   const double y2 = y * y, nx2 = -x * x;
   // n = 1, 2
@@ -283,7 +283,7 @@ __device__ __forceinline__ void pair_amps_s(double m, double sum2, double dif2, 
       const double a = rt[r][0] - s;
       const double b = rt[r][1] * G;
       const double d = rcp_fast(__builtin_fma(a, a, b * b));
-      const double k = (T::L(r) == 1 ? rt[r][2] * F1 : rt[r][2]) * d;
+      const double k = T::L(r) == 1 ? rt[r][2] * F1 * d : d;  // Ka = 1 for L = 0
       amp[r] = {k * a, k * b};
     }
   }
@@ -338,6 +338,101 @@ __device__ __forceinline__ cplx td4_bk(const Td4Point<S>& p, int k) {
     case 3: { const double cc = p.c12 * p.c34; return {xy.re * cc, xy.im * cc}; }
     case 4: return cmul(xy, {p.ssc, p.sss});
     default: return cmul(xy, {p.ssc, -p.sss});
+  }
+}
+
+// Whether any basis function of shape S in sum SIDE (0: A, 1: Abar) has pair
+// entries r1 and r2 (r2 < 0: any).
+template <class S>
+__host__ __device__ constexpr bool td4_has(int side, int r1, int r2) {
+  bool u = false;
+  for (int k = 0; k < S::K; ++k)
+    u = u || (S::A1[k] == r1 && (r2 < 0 || S::A2[k] == r2) && (side ? S::PB[k] : S::PA[k]) >= 0);
+  return u;
+}
+
+// w += c Omega_T, the angular factor of type T (first: w = c Omega_T).
+template <class S>
+__device__ __forceinline__ void td4_add_omega(const Td4Point<S>& p, int T, double cr, double ci, bool first, cplx& w) {
+  if (first && T == 0) {
+    w = {cr, ci};
+    return;
+  }
+  if (first) w = {0.0, 0.0};
+  if (T == 0) {
+    w = {w.re + cr, w.im + ci};
+  } else if (T <= 3) {
+    const double om = T == 1 ? p.c34 : (T == 2 ? p.c12 : p.c12 * p.c34);
+    w = {__builtin_fma(cr, om, w.re), __builtin_fma(ci, om, w.im)};
+  } else {
+    const double sn = T == 4 ? p.sss : -p.sss;
+    w = {__builtin_fma(cr, p.ssc, __builtin_fma(-ci, sn, w.re)), __builtin_fma(cr, sn, __builtin_fma(ci, p.ssc, w.im))};
+  }
+}
+
+// The coherent sum SIDE of a point, sum_k c_k B_k with B_k = a12 a34 Omega_k,
+// factored by pair entries: sum_r1 a12[r1] sum_r2 a34[r2] sum_k c_k Omega_k.
+// The products of lineshapes are taken once per pair of entries and sum, not
+// once per basis function, and no basis function is formed.
+template <class S, int SIDE>
+__device__ __forceinline__ cplx td4_sum(const Td4Point<S>& p, const double (*__restrict__ c)[2]) {
+  cplx A = {0.0, 0.0};
+#pragma unroll
+  for (int r1 = 0; r1 < S::N12; ++r1) {
+    if (!td4_has<S>(SIDE, r1, -1)) continue;
+    cplx in = {0.0, 0.0};
+    bool none = true;
+#pragma unroll
+    for (int r2 = 0; r2 < S::N34; ++r2) {
+      if (!td4_has<S>(SIDE, r1, r2)) continue;
+      cplx w = {0.0, 0.0};
+      bool first = true;
+#pragma unroll
+      for (int k = 0; k < S::K; ++k)
+        if (S::A1[k] == r1 && S::A2[k] == r2 && (SIDE ? S::PB[k] : S::PA[k]) >= 0) {
+          td4_add_omega<S>(p, S::T[k], c[k][0], c[k][1], first, w);
+          first = false;
+        }
+      if (S::NR34[r2]) in = none ? w : cplx{in.re + w.re, in.im + w.im};
+      else in = cfma(p.a34[r2], w, in);
+      none = false;
+    }
+    if (S::NR12[r1]) A = {A.re + in.re, A.im + in.im};
+    else A = cfma(p.a12[r1], in, A);
+  }
+  return A;
+}
+
+// Adds the event's gradient terms of sum SIDE, Re(l B_k) and -Im(l B_k), to
+// the accumulators of its coefficients (acc: their slots in theta order), with
+// the products l a12 and l a12 a34 shared in the same way.
+template <class S, int SIDE>
+__device__ __forceinline__ void td4_sum_grad(const Td4Point<S>& p, cplx l, double* acc) {
+#pragma unroll
+  for (int r1 = 0; r1 < S::N12; ++r1) {
+    if (!td4_has<S>(SIDE, r1, -1)) continue;
+    const cplx u = S::NR12[r1] ? l : cmul(l, p.a12[r1]);
+#pragma unroll
+    for (int r2 = 0; r2 < S::N34; ++r2) {
+      if (!td4_has<S>(SIDE, r1, r2)) continue;
+      const cplx v = S::NR34[r2] ? u : cmul(u, p.a34[r2]);
+#pragma unroll
+      for (int k = 0; k < S::K; ++k) {
+        const int i = SIDE ? S::PB[k] : S::PA[k];
+        if (S::A1[k] != r1 || S::A2[k] != r2 || i < 0) continue;
+        const int T = S::T[k];
+        if (T == 0) {
+          acc[i] += v.re;
+          acc[i + 1] -= v.im;
+        } else if (T <= 3) {
+          const double om = T == 1 ? p.c34 : (T == 2 ? p.c12 : p.c12 * p.c34);
+          acc[i] = __builtin_fma(v.re, om, acc[i]);
+          acc[i + 1] = __builtin_fma(-v.im, om, acc[i + 1]);
+        } else {
+          grad_acc(v, {p.ssc, T == 4 ? p.sss : -p.sss}, acc[i], acc[i + 1]);
+        }
+      }
+    }
   }
 }
 
@@ -421,13 +516,7 @@ __device__ inline void td4_events_body(const Td4Const& tc, const Td4Table* __res
     time_fns<GRAD>(tb.tk, tc.wa + zero, tc.wL, tb.x, tb.y, t, T);
     Td4Point<S> pt;
     td4_point_s<S>(tc, tb, ev[i], ev[ld + i], ev[2 * ld + i], ev[3 * ld + i], ev[4 * ld + i], pt);
-    cplx A = {0.0, 0.0}, Ab = {0.0, 0.0};
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
-      const cplx b = td4_bk<S>(pt, k);
-      if (S::PA[k] >= 0) A = cfma({tb.c[k][0], tb.c[k][1]}, b, A);
-      if (S::PB[k] >= 0) Ab = cfma({tb.cb[k][0], tb.cb[k][1]}, b, Ab);
-    }
+    const cplx A = td4_sum<S, 0>(pt, tb.c), Ab = td4_sum<S, 1>(pt, tb.cb);
     const double Hc = T.Hc, Hs = T.Hs;
     const cplx hc = {T.hr, T.hi};
     const double a2 = A.re * A.re + A.im * A.im, b2 = Ab.re * Ab.re + Ab.im * Ab.im;
@@ -442,14 +531,8 @@ __device__ inline void td4_events_body(const Td4Const& tc, const Td4Table* __res
       // (the event's factor w = -1/R included)
       const cplx lc = {w * (hpc * A.re - Hs * Ab.re - hc.im * Ab.im), w * (-hpc * A.im + Hs * Ab.im - hc.im * Ab.re)};
       const cplx lb = {w * (hmc * Ab.re - Hs * A.re + hc.im * A.im), w * (-hmc * Ab.im + Hs * A.im + hc.im * A.re)};
-      // the basis functions again, formed from the lineshapes
-      td4_opaque<S>(pt);
-#pragma unroll
-      for (int k = 0; k < K; ++k) {
-        const cplx b = td4_bk<S>(pt, k);
-        if (S::PA[k] >= 0) grad_acc(lc, b, acc[1 + S::PA[k]], acc[2 + S::PA[k]]);
-        if (S::PB[k] >= 0) grad_acc(lb, b, acc[1 + S::PB[k]], acc[2 + S::PB[k]]);
-      }
+      td4_sum_grad<S, 0>(pt, lc, acc + 1);
+      td4_sum_grad<S, 1>(pt, lb, acc + 1);
       acc[P - 1] += w * 0.5 * ((a2 - b2) * T.dr - 2.0 * zi * T.di);
       acc[P] += w * 0.5 * ((a2 + b2) * T.dHc - 2.0 * zr * T.dHs);
     }
