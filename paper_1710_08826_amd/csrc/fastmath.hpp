@@ -121,6 +121,41 @@ __device__ __forceinline__ double exp_fast(double x) {
   return x < -750.0 ? 0.0 : e;
 }
 
+// sin x and cos x: x = k pi/2 + r with |r| <= pi/4 (Cody & Waite, pi/2 in two
+// parts), the two functions of r by polynomials in r^2 at the Chebyshev nodes
+// of [0, pi^2/16] (errors 2.0e-17 relative and 9e-19), exchanged and signed by
+// k's quadrant.  Absolute error below 2e-16 for |x| < 1e5; a wave with a
+// larger (or not finite) argument takes the library's function.
+__device__ __forceinline__ void sincos_fast(double x, double& sn, double& cs) {
+  if (__any(!(fabs(x) < 1e5))) {
+    sincos(x, &sn, &cs);
+    return;
+  }
+  const double k = __builtin_rint(x * 0.63661977236758134308);
+  const double r = __builtin_fma(-k, 0x1.1a62633145c07p-54, __builtin_fma(-k, 0x1.921fb54442d18p+0, x));
+  const double z = r * r;
+  double s = 0x1.5e0b13ccdcb64p-33;
+  s = fma_sc(s, z, -0x1.ae600af19478ap-26);
+  s = fma_sc(s, z, 0x1.71de3796799f6p-19);
+  s = fma_sc(s, z, -0x1.a01a019e839e3p-13);
+  s = fma_sc(s, z, 0x1.1111111110bb2p-7);
+  s = fma_sc(s, z, -0x1.5555555555555p-3);
+  s = __builtin_fma(r * z, s, r);
+  double c = -0x1.907d9d3a50522p-37;
+  c = fma_sc(c, z, 0x1.1eeb68e0a87edp-29);
+  c = fma_sc(c, z, -0x1.27e4fa17d1cf9p-22);
+  c = fma_sc(c, z, 0x1.a01a019f4ea9bp-16);
+  c = fma_sc(c, z, -0x1.6c16c16c16967p-10);
+  c = fma_sc(c, z, 0x1.5555555555555p-5);
+  c = __builtin_fma(z * z, c, __builtin_fma(z, -0.5, 1.0));
+  const int q = (int)k;
+  const bool odd = q & 1;
+  const double a = odd ? c : s, b = odd ? s : c;
+  // sin takes the sign of bit 1 of k, cos that of bit 1 of k + 1
+  sn = __longlong_as_double(__double_as_longlong(a) ^ ((long long)(q & 2) << 62));
+  cs = __longlong_as_double(__double_as_longlong(b) ^ ((long long)((q + 1) & 2) << 62));
+}
+
 // sqrt for x >= 0; arguments below 1e-300 are treated as 1e-300.
 __device__ __forceinline__ double sqrt_fast(double x) {
   const double xc = __builtin_fmax(x, 1e-300);

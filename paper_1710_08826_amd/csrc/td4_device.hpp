@@ -61,10 +61,11 @@ __device__ inline cplx faddeeva(const double* __restrict__ wa, double L, cplx z)
   const cplx d = {L + z.im, -z.re};           // L - i z
   const cplx id = crcp(d);
   const cplx Z = cmul({L - z.im, z.re}, id);  // (L + i z)/(L - i z)
+  const double nZi = -Z.im;
   cplx p = {wa[kWeidN - 1], 0.0};
 #pragma unroll
   for (int n = kWeidN - 2; n >= 0; --n)
-    p = {__builtin_fma(p.re, Z.re, fma_sc(-p.im, Z.im, wa[n])), __builtin_fma(p.re, Z.im, p.im * Z.re)};
+    p = {__builtin_fma(p.re, Z.re, fma_sc(p.im, nZi, wa[n])), __builtin_fma(p.re, Z.im, p.im * Z.re)};
   const cplx t = cmul({2.0 * p.re, 2.0 * p.im}, id);
   return cmul({t.re + kInvSqrtPi, t.im}, id);
 }
@@ -315,7 +316,7 @@ __device__ __forceinline__ void td4_point_s(const Td4Const& tc, const Td4Table& 
   if (has_sc) {
     const double ss = 0.5 * sqrt_fast(fmax(1.0 - c12 * c12, 0.0)) * sqrt_fast(fmax(1.0 - c34 * c34, 0.0));
     double sp, cp;
-    sincos(phi, &sp, &cp);
+    sincos_fast(phi, sp, cp);
     p.ssc = ss * cp;
     p.sss = ss * sp;
   }
