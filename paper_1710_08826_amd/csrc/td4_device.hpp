@@ -504,7 +504,19 @@ __device__ inline void td4_events_body(const Td4Const& tc, const Td4Table* __res
   const int64_t base = ch * chunk;
   const int64_t end = base + chunk < n ? base + chunk : n;
   LogProd lp;  // -sum ln R enters acc[0] once per thread, at the end
-  for (int64_t i = base + threadIdx.x; i < end; i += kBlock) {
+  // an event's six values are loaded one iteration ahead (at a clamped index):
+  // with two waves per SIMD nothing else hides the latency
+  const int64_t i0 = base + threadIdx.x;
+  double nx[6];
+#pragma unroll
+  for (int j = 0; j < 6; ++j) nx[j] = ev[j * ld + (i0 < end ? i0 : base)];
+  for (int64_t i = i0; i < end; i += kBlock) {
+    double e[6];
+    const int64_t in = i + kBlock < end ? i + kBlock : i;
+#pragma unroll
+    for (int j = 0; j < 6; ++j) e[j] = nx[j];
+#pragma unroll
+    for (int j = 0; j < 6; ++j) nx[j] = ev[j * ld + in];
     // the fit's constants are re-read through the scalar cache on every event
     // (an opaque zero offset keeps them from being hoisted into SGPRs that
     // would overflow into VGPR lanes)
@@ -512,11 +524,10 @@ __device__ inline void td4_events_body(const Td4Const& tc, const Td4Table* __res
     asm volatile("" : "+s"(zero));
     const Td4Table& tb = tabs[f + zero];
     // time functions first: the lineshapes are not live across them
-    const double t = ev[5 * ld + i];
     TimeFns T;
-    time_fns<GRAD>(tb.tk, tc.wa + zero, tc.wL, tb.x, tb.y, t, T);
+    time_fns<GRAD>(tb.tk, tc.wa + zero, tc.wL, tb.x, tb.y, e[5], T);
     Td4Point<S> pt;
-    td4_point_s<S>(tc, tb, ev[i], ev[ld + i], ev[2 * ld + i], ev[3 * ld + i], ev[4 * ld + i], pt);
+    td4_point_s<S>(tc, tb, e[0], e[1], e[2], e[3], e[4], pt);
     const cplx A = td4_sum<S, 0>(pt, tb.c), Ab = td4_sum<S, 1>(pt, tb.cb);
     const double Hc = T.Hc, Hs = T.Hs;
     const cplx hc = {T.hr, T.hi};

@@ -87,17 +87,25 @@ __device__ inline void tddp_events_body(const DalitzConst& dc, const DalitzTable
   const int64_t end = base + chunk < n ? base + chunk : n;
   const double* const r0 = &tab->r[0][0];
   LogProd lp;  // -sum ln R enters acc[0] once per thread, at the end
-  for (int64_t i = base + threadIdx.x; i < end; i += kBlock) {
+  // an event's three values are loaded one iteration ahead (at a clamped
+  // index): with one or two waves per SIMD nothing else hides the latency
+  const int64_t i0 = base + threadIdx.x;
+  const int64_t f0 = i0 < end ? i0 : base;
+  double n12 = ev[f0], n13 = ev[ld + f0], nt = ev[2 * ld + f0];
+  for (int64_t i = i0; i < end; i += kBlock) {
+    const double s12 = n12, s13 = n13, t = nt;
+    const int64_t in = i + kBlock < end ? i + kBlock : i;
+    n12 = ev[in];
+    n13 = ev[ld + in];
+    nt = ev[2 * ld + in];
     // constants re-read through the scalar cache per event (an opaque zero
     // offset keeps them out of SGPRs that would overflow into VGPR lanes)
     int zero = 0;
     asm volatile("" : "+s"(zero));
     const double* r = r0 + zero;
     const double* coef = coef0 + zero;
-    const double t = ev[2 * ld + i];
     TimeFns T;
     time_fns<GRAD>((&tt.tk)[zero], tt.wa + zero, tt.wL, coef[4 * K], coef[4 * K + 1], t, T);
-    const double s12 = ev[i], s13 = ev[ld + i];
     double Are[K], Aim[K], Bre[K], Bim[K];
     tddp_basis2<S>(dc, r, s12, s13, Are, Aim, Bre, Bim);
     cplx A = {0.0, 0.0}, Ab = {0.0, 0.0};
