@@ -297,7 +297,7 @@ static void compile_tddp3(const json::Value& d, fn_model* m, bool device = true)
   // the autotuner's choice on MI355X at 1M events (1024: 90.5 us, 2048: 83.9, 4096: 80.2, 8192: 130)
   m->chunk = 4096;
   if (!device) return;
-  m->tddp_jit = tddp_jit(dc);
+  m->tddp_jit = tddp_jit(dc, m->fixed_ls.data());
   m->d_table.reserve(sizeof(DalitzTable));
   m->d_fixed.reserve(sizeof(double) * 2 * dc.K);
   hip_check(hipMemcpy(m->d_fixed.ptr, m->fixed_ls.data(), sizeof(double) * 2 * dc.K, hipMemcpyHostToDevice),
@@ -852,7 +852,7 @@ fn_status fn_model_check_compile(const char* desc_json, const char* arch) {
         (void)jit_compile(td4_jit_source(tmp.td4), target);
       } else if (kind == "tddp3") {
         compile_tddp3(d, &tmp, false);
-        (void)jit_compile(tddp_jit_source(tmp.dal), target);
+        (void)jit_compile(tddp_jit_source(tmp.dal, tmp.fixed_ls.data()), target);
       } else if (kind != "mix1d") {
         throw Error(FN_E_INVALID, "unknown model kind \"" + kind + "\"");
       }

@@ -16,7 +16,7 @@ namespace fn {
 
 int tddp_nv(int K, bool grad) { return grad ? 3 + 4 * K : 1; }
 
-std::string tddp_jit_source(const DalitzConst& dc) {
+std::string tddp_jit_source(const DalitzConst& dc, const double* fixed_ls) {
   std::ostringstream o;
   o << "#include \"tddp_device.hpp\"\n";
   o << "struct fn_shape {\n  static constexpr int K = " << dc.K << ";\n  static constexpr int chan[" << dc.K
@@ -24,6 +24,15 @@ std::string tddp_jit_source(const DalitzConst& dc) {
   for (int k = 0; k < dc.K; ++k) o << (k ? ", " : "") << dc.chan[k];
   o << "};\n  static constexpr int L[" << dc.K << "] = {";
   for (int k = 0; k < dc.K; ++k) o << (k ? ", " : "") << dc.L[k];
+  // the first resonance with the same lineshape, among pairs 12 and 13 or in pair 23
+  o << "};\n  static constexpr int REP[" << dc.K << "] = {";
+  for (int k = 0; k < dc.K; ++k) {
+    int rep = 0;
+    while (rep < k && ((dc.chan[rep] == 2) != (dc.chan[k] == 2) || dc.L[rep] != dc.L[k] ||
+                       fixed_ls[2 * rep] != fixed_ls[2 * k] || fixed_ls[2 * rep + 1] != fixed_ls[2 * k + 1]))
+      ++rep;
+    o << (k ? ", " : "") << rep;
+  }
   o << "};\n};\n";
   o << "FN_TDDP_EVENTS(fn_tddp_ev0, fn_shape, false)\n"
        "FN_TDDP_EVENTS(fn_tddp_ev1, fn_shape, true)\n"
@@ -34,9 +43,9 @@ std::string tddp_jit_source(const DalitzConst& dc) {
   return o.str();
 }
 
-std::shared_ptr<TddpJit> tddp_jit(const DalitzConst& dc) {
+std::shared_ptr<TddpJit> tddp_jit(const DalitzConst& dc, const double* fixed_ls) {
   auto j = std::make_shared<TddpJit>();
-  j->prog = jit_load(tddp_jit_source(dc), {"fn_tddp_ev0", "fn_tddp_ev1", "fn_tddp_maa", "fn_tddp_mbb", "fn_tddp_mab",
+  j->prog = jit_load(tddp_jit_source(dc, fixed_ls), {"fn_tddp_ev0", "fn_tddp_ev1", "fn_tddp_maa", "fn_tddp_mbb", "fn_tddp_mab",
                                            "fn_tddp_gmax", "fn_tddp_gen"});
   const auto& f = j->prog->fns;
   j->ev[0] = f[0];

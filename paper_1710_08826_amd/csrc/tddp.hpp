@@ -15,8 +15,8 @@ struct TddpJit {
   hipFunction_t mrows[3] = {nullptr, nullptr, nullptr};  // MAA, MBB, MAB row blocks
   hipFunction_t gmax = nullptr, gen = nullptr;            // toy generation
 };
-std::string tddp_jit_source(const DalitzConst& dc);
-std::shared_ptr<TddpJit> tddp_jit(const DalitzConst& dc);
+std::string tddp_jit_source(const DalitzConst& dc, const double* fixed_ls);
+std::shared_ptr<TddpJit> tddp_jit(const DalitzConst& dc, const double* fixed_ls);
 int tddp_nv(int K, bool grad);
 // The three normalization matrices (each K x K complex, dA included) into
 // Mc, Mc + 2K^2 and Mc + 4K^2; part holds one chunk of rows.
