@@ -121,14 +121,21 @@ __device__ __forceinline__ double exp_fast(double x) {
   return x < -750.0 ? 0.0 : e;
 }
 
+// The library's sine and cosine as a call: inlined, its coefficients would sit
+// in some forty vector registers of the caller's event loop.
+__device__ __attribute__((noinline)) inline void sincos_any(double x, double* sn, double* cs) { sincos(x, sn, cs); }
+
 // sin x and cos x: x = k pi/2 + r with |r| <= pi/4 (Cody & Waite, pi/2 in two
 // parts), the two functions of r by polynomials in r^2 at the Chebyshev nodes
 // of [0, pi^2/16] (errors 2.0e-17 relative and 9e-19), exchanged and signed by
 // k's quadrant.  Absolute error below 2e-16 for |x| < 1e5; a wave with a
 // larger (or not finite) argument takes the library's function.
 __device__ __forceinline__ void sincos_fast(double x, double& sn, double& cs) {
-  if (__any(!(fabs(x) < 1e5))) {
-    sincos(x, &sn, &cs);
+  if (__builtin_expect(__any(!(fabs(x) < 1e5)), 0)) {
+    double a, b;
+    sincos_any(x, &a, &b);
+    sn = a;
+    cs = b;
     return;
   }
   const double k = __builtin_rint(x * 0.63661977236758134308);

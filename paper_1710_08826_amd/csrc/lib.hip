@@ -294,8 +294,9 @@ static void compile_tddp3(const json::Value& d, fn_model* m, bool device = true)
   td4_erfc_coefficients(m->tdt.we);
   m->P = 4 * dc.K + 2;
   m->n_obs = 3;
-  // the autotuner's choice on MI355X at 1M events (1024: 90.5 us, 2048: 83.9, 4096: 80.2, 8192: 130)
-  m->chunk = 4096;
+  // two workgroups per compute unit in one round at 1M events on MI355X (NLL
+  // and gradient, sixteen resonances: 1024 86.7 us, 2048 77.4, 4096 80.4)
+  m->chunk = 2048;
   if (!device) return;
   m->tddp_jit = tddp_jit(dc, m->fixed_ls.data());
   m->d_table.reserve(sizeof(DalitzTable));

@@ -90,7 +90,7 @@ __device__ inline void h_real(const double* __restrict__ we, double a, double t,
   const double u = a * s2 - t;
   const double z = u * (kInvSqrt2 / s);
   const double w = erfcx_pos(we, fabs(z));
-  h = z >= 0.0 ? 0.5 * g * w : exp(0.5 * a * a * s2 - a * t) - 0.5 * g * w;
+  h = z >= 0.0 ? 0.5 * g * w : exp_fast(0.5 * a * a * s2 - a * t) - 0.5 * g * w;
   dh = u * h - s * kInvSqrt2Pi * g;
 }
 
@@ -108,8 +108,8 @@ __device__ inline void h_cplx(const double* __restrict__ wa, double L, cplx a, d
     const double er = 0.5 * (a.re * a.re - a.im * a.im) * s2 - a.re * t;
     const double ei = a.re * a.im * s2 - a.im * t;
     double sn, cs;
-    sincos(ei, &sn, &cs);
-    const double e = exp(er);
+    sincos_fast(ei, sn, cs);
+    const double e = exp_fast(er);
     h = {e * cs - 0.5 * g * w.re, e * sn - 0.5 * g * w.im};
   }
   const cplx uh = cmul(u, h);
@@ -186,13 +186,18 @@ __device__ __forceinline__ void time_terms(TimeSeries& a, double v, double w, do
 // there: mixing parameters of the size fits meet (below 0.01) keep r <= 1/8 up
 // to twelve lifetimes.
 // One NLL and gradient: four-body, 10M events, twenty amplitudes 456 -> 349 us;
-// three-body, 1M events, sixteen resonances 105.8 -> 94.5 us.
+// three-body, 1M events, sixteen resonances 105.8 -> 94.5 us.  The rare forms are
+// kept out of the registers of the common one: their branches are marked
+// unlikely, and they use the written-out exponential, sine and cosine (with the
+// library's inlined, its coefficients filled some sixty vector registers over
+// the whole event loop: four-body pass 227 -> 185 registers, 290 -> 281 us;
+// three-body 296 -> 256 and two waves per SIMD instead of one, 83.4 -> 77.4 us).
 template <bool GRAD>
 __device__ __forceinline__ void time_fns(const TimeConst& k, const double* __restrict__ wt, double wL, double x,
                                          double y, double t, TimeFns& o) {
   const double g = exp_fast(t * t * k.ni2s2);
   const double r = fmax(fabs(x), fabs(y)) * k.g * (fabs(t) + k.s3);
-  if (__any(!(r <= kTimeSeriesMax))) {
+  if (__builtin_expect(__any(!(r <= kTimeSeriesMax)), 0)) {
     double hp, dhp, hm, dhm;
     cplx hc, dhc;
     const double* we = wt + kWeidN;
@@ -212,8 +217,10 @@ __device__ __forceinline__ void time_fns(const TimeConst& k, const double* __res
   }
   const double u = k.gs2 - t;
   const double z = u * k.iz;
+  double eg = exp_fast(__builtin_fma(-k.g, t, k.hg2s2));
+  asm volatile("" : "+v"(eg));  // formed in line with the rest, not behind a branch on z
   const double e = 0.5 * g * erfcx_pos(wt + kWeidN, fabs(z));
-  const double c0 = z >= 0.0 ? e : exp_fast(__builtin_fma(-k.g, t, k.hg2s2)) - e;
+  const double c0 = z >= 0.0 ? e : eg - e;
   const double v = k.g * u, w = k.g2s2;
   const double y2 = y * y, nx2 = -x * x;
   // n = 1, 2
@@ -229,7 +236,7 @@ __device__ __forceinline__ void time_fns(const TimeConst& k, const double* __res
   a.ey = a.ce * y2;
   a.ex = a.ce * nx2;
   time_terms<GRAD>(a, v, w, y2, nx2, 1, 5);
-  if (__any(r > kTimeSeriesTen)) time_terms<GRAD>(a, v, w, y2, nx2, 5, 10);
+  if (__builtin_expect(__any(r > kTimeSeriesTen), 0)) time_terms<GRAD>(a, v, w, y2, nx2, 5, 10);
   o.Hc = c0 + a.ey;
   o.Hs = -y * a.oy;
   o.hr = c0 + a.ex;

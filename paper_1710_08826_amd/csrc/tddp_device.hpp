@@ -390,7 +390,7 @@ __device__ inline void tddp_gen_body(const DalitzConst& dc, const DalitzTable* _
 
 // Kernels for shape S (used by the generated source).
 #define FN_TDDP_EVENTS(NAME, S, GRAD)                                                                          \
-  extern "C" __global__ __launch_bounds__(fn::kBlock) void NAME(                                               \
+  extern "C" __global__ __launch_bounds__(fn::kBlock) __attribute__((amdgpu_waves_per_eu(2))) void NAME(       \
       fn::DalitzConst dc, const fn::DalitzTable* __restrict__ tab, fn::TddpTime tt,                            \
       const double* __restrict__ coef, const double* __restrict__ ev, int64_t ld, int64_t n, int chunk,       \
       double* __restrict__ part) {                                                                             \
