@@ -124,8 +124,9 @@ typedef struct fn_model fn_model;
  *     vector (fn_model_fixed): (m0, w0) of every r12 entry, of every r34
  *     entry, then sigma_t.
  *  Optional keys for every kind: "chunk" (events per workgroup, a multiple of
- *  256 in [256, 2^22], default chosen per kind) -- fixed per model, it
- *  defines the summation tree.  dalitz3 only: "events_per_thread" (1, the
+ *  256 in [256, 2^22]) -- it defines the summation tree; when given (or chosen
+ *  by fn_model_autotune) it is the same for every sample, otherwise it
+ *  follows from the number of events alone, by a rule of the kind.  dalitz3 only: "events_per_thread" (1, the
  *  default, or 2: events each thread of the events passes evaluates per loop
  *  iteration; a thread adds its events in index order either way, so the
  *  results are bitwise the same).
@@ -138,7 +139,8 @@ fn_status fn_model_create(fn_ctx* ctx, const char* desc_json, fn_model** out);
  * Returns FN_E_INVALID with the compiler log for a description that does not
  * compile.  Needs no GPU. */
 fn_status fn_model_check_compile(const char* desc_json, const char* arch);
-/* Number of parameters, observables, and the summation chunk of a model. */
+/* Number of parameters, observables, and the summation chunk of a model (the
+ * kind's default where the chunk follows from the sample's size). */
 fn_status fn_model_info(const fn_model* m, int32_t* n_params, int32_t* n_obs, int32_t* chunk);
 /* Frees the model's device memory.  Streams using it must be synchronised. */
 fn_status fn_model_destroy(fn_model* m);
@@ -212,9 +214,9 @@ fn_status fn_nll_async(fn_model* m, const double* theta_dev, const double* ev, i
  * calls that overlap on one device (different streams, models or host
  * threads) race and give wrong results; serialise them.  The event pass is
  * never timed by fn_model_timing.  FN_E_INVALID as fn_nll_async, and when
- * the rows do not fit (about 2^21 / (1 + P) chunks of the model's chunk
- * size: 123k chunks, 250M events at 2048 per chunk, for a 16-parameter
- * dalitz3 gradient); nothing is enqueued then except, possibly, the
+ * the rows do not fit (about 2^21 / (1 + P) chunks: 123k chunks for a
+ * 16-parameter dalitz3 gradient, 250M events when the description fixes the
+ * chunk at 2048); nothing is enqueued then except, possibly, the
  * parameter prologue. */
 fn_status fn_nll_async_noalloc(fn_model* m, const double* theta_dev, const double* ev, int64_t n,
                                int64_t ld, double* out_dev, int32_t with_grad, void* stream);

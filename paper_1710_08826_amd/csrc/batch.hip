@@ -151,13 +151,18 @@ __global__ void batch_prologue(Mix1dConst mc, const BfgsState* __restrict__ st, 
   mix1d_table(mc, st[f].xt, tabs[f]);
 }
 
+__device__ __forceinline__ int64_t chunks_of(const ChunkRule& rule, int64_t n) {
+  const int c = rule(n);
+  return (n + c - 1) / c;
+}
+
 // Single workgroup: item_base[f] = sum of chunk counts of running fits < f;
 // item_base[n_fits] = total; *n_running = number of running fits.  Thread t
 // takes a contiguous run of fits; the exclusive scan of the per-thread sums
 // (thread order) is a shuffle scan within each wave plus the totals of the
 // preceding waves: exact integer sums, the same as a serial loop.
 __global__ __launch_bounds__(kBlock) void batch_scan(const int* __restrict__ stat, const int64_t* __restrict__ nev,
-                                                     int n_fits, int chunk, int64_t* __restrict__ item_base,
+                                                     int n_fits, ChunkRule rule, int64_t* __restrict__ item_base,
                                                      int* __restrict__ n_running) {
   constexpr int kWaves = kBlock / 64;
   __shared__ int64_t wsum[kWaves];
@@ -170,7 +175,7 @@ __global__ __launch_bounds__(kBlock) void batch_scan(const int* __restrict__ sta
 #pragma unroll 4
   for (int f = f0; f < f1; ++f) {
     if (stat[f] == kFitRunning) {
-      s += (nev[f] + chunk - 1) / chunk;
+      s += chunks_of(rule, nev[f]);
       ++c;
     }
   }
@@ -202,7 +207,7 @@ __global__ __launch_bounds__(kBlock) void batch_scan(const int* __restrict__ sta
 #pragma unroll 4
   for (int f = f0; f < f1; ++f) {
     item_base[f] = b;
-    if (stat[f] == kFitRunning) b += (nev[f] + chunk - 1) / chunk;
+    if (stat[f] == kFitRunning) b += chunks_of(rule, nev[f]);
   }
 }
 
@@ -211,7 +216,7 @@ __global__ __launch_bounds__(kBlock) void batch_eval(Mix1dConst mc, const Mix1dT
                                                      const double* const* __restrict__ ev,
                                                      const int64_t* __restrict__ nev,
                                                      const int64_t* __restrict__ item_base,
-                                                     const int64_t* __restrict__ part_base, int n_fits, int chunk,
+                                                     const int64_t* __restrict__ part_base, int n_fits, ChunkRule rule,
                                                      double* __restrict__ part) {
   constexpr int NV = GRAD ? mix_nv(KMAX) : 1;
   __shared__ double lds[block_sum_lds(NV)];
@@ -227,7 +232,7 @@ __global__ __launch_bounds__(kBlock) void batch_eval(Mix1dConst mc, const Mix1dT
     }
     const int f = lo;
     const int64_t ch = it - item_base[f];
-    mix1d_chunk<GRAD, KMAX, SIG>(mc, tabs + f, ev[f], nev[f], ch, chunk, part + (part_base[f] + ch) * NV, lds);
+    mix1d_chunk<GRAD, KMAX, SIG>(mc, tabs + f, ev[f], nev[f], ch, rule(nev[f]), part + (part_base[f] + ch) * NV, lds);
     __syncthreads();
   }
 }
@@ -236,13 +241,13 @@ __global__ __launch_bounds__(kBlock) void batch_finalize(Mix1dConst mc, const Mi
                                                          const int* __restrict__ stat,
                                                          const int64_t* __restrict__ nev,
                                                          const int64_t* __restrict__ part_base, const double* part,
-                                                         int chunk, int nv, int kmax, double* __restrict__ out,
+                                                         ChunkRule rule, int nv, int kmax, double* __restrict__ out,
                                                          int out_stride) {
   __shared__ double scratch[kBlock];
   __shared__ double res[kBlock];
   const int f = blockIdx.x;
   if (stat[f] != kFitRunning) return;
-  const int64_t rows = (nev[f] + chunk - 1) / chunk;
+  const int64_t rows = chunks_of(rule, nev[f]);
   mix1d_finalize_one(mc, tabs[f], part + part_base[f] * nv, rows, nv, kmax, 1, (double)nev[f],
                      out + (int64_t)f * out_stride,
                      nullptr, scratch, res);
@@ -271,17 +276,17 @@ void batch_launch_gather_rows(const BatchDev& b, const int* slots, int n, int P,
                      rows_out);
 }
 
-void batch_launch_step(const BatchDev& b, const Mix1dConst& mc, int n_fits, int P, int chunk, int eval_grid,
+void batch_launch_step(const BatchDev& b, const Mix1dConst& mc, int n_fits, int P, ChunkRule rule, int eval_grid,
                        double tol, int max_iter, hipStream_t s) {
   const int kmax = mix1d_kmax(mc.K);
   const int nv = mix1d_nv(kmax, true);
   const dim3 fg((n_fits + 63) / 64), fb(64);
   hipLaunchKernelGGL(batch_prologue, fg, fb, 0, s, mc, b.st, b.stat, n_fits, b.tabs);
-  hipLaunchKernelGGL(batch_scan, dim3(1), dim3(kBlock), 0, s, b.stat, b.nev, n_fits, chunk, b.item_base,
+  hipLaunchKernelGGL(batch_scan, dim3(1), dim3(kBlock), 0, s, b.stat, b.nev, n_fits, rule, b.item_base,
                      b.n_running);
 #define FN_EVAL(K, SIG)                                                                               \
   hipLaunchKernelGGL((batch_eval<true, K, SIG>), dim3(eval_grid), dim3(kBlock), 0, s, mc, b.tabs, b.ev, b.nev, \
-                     b.item_base, b.part_base, n_fits, chunk, b.part)
+                     b.item_base, b.part_base, n_fits, rule, b.part)
 #define FN_EVAL_SIG(SIG) \
   case SIG:              \
     FN_EVAL(2, SIG);     \
@@ -295,7 +300,7 @@ void batch_launch_step(const BatchDev& b, const Mix1dConst& mc, int n_fits, int 
 #undef FN_EVAL_SIG
 #undef FN_EVAL
   hipLaunchKernelGGL(batch_finalize, dim3(n_fits), dim3(kBlock), 0, s, mc, b.tabs, b.stat, b.nev, b.part_base, b.part,
-                     chunk, nv, kmax, b.out, 2 + 2 * P);
+                     rule, nv, kmax, b.out, 2 + 2 * P);
   bfgs_launch<kBatchMaxP>(b.st, b.out, 2 + 2 * P, n_fits, P, tol, max_iter, b.stat, b.rres, s);
 }
 

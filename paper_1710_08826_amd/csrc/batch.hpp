@@ -53,7 +53,7 @@ void batch_launch_set(const BatchDev& b, const double* theta0, int n_fits, int m
 // rows_out[i] = rres row of slot slots[i] (3 + 2P doubles), for n slots.
 void batch_launch_gather_rows(const BatchDev& b, const int* slots, int n, int P, double* rows_out, hipStream_t s);
 
-void batch_launch_step(const BatchDev& b, const Mix1dConst& mc, int n_fits, int P, int chunk, int eval_grid,
+void batch_launch_step(const BatchDev& b, const Mix1dConst& mc, int n_fits, int P, ChunkRule rule, int eval_grid,
                        double tol, int max_iter, hipStream_t s);
 int batch_eval_blocks_per_cu(const Mix1dConst& mc);
 void batch_launch_gen_mix1d(uint32_t k0, uint32_t k1, uint32_t word, int64_t n, const double* theta_gen, double lo,

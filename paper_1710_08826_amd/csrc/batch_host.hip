@@ -15,7 +15,7 @@ struct fn_batch {
   int max_fits = 0;
   int64_t max_ev = 0;
   int P = 0;
-  int chunk = 0;
+  ChunkRule rule{1024, 0};  // the model's when the batch was created
   int64_t rows_per_slot = 0;
   int eval_grid = 0;
   double tol = 1e-7;
@@ -76,7 +76,7 @@ static hipGraphExec_t step_graph(fn_batch* b) {
   if (!b->exec) {
     hipGraph_t g = nullptr;
     hip_check(hipStreamBeginCapture(b->stream, hipStreamCaptureModeThreadLocal), "hipStreamBeginCapture");
-    batch_launch_step(b->dev(), b->m->mix, b->max_fits, b->P, b->chunk, b->eval_grid, b->tol, b->max_iter,
+    batch_launch_step(b->dev(), b->m->mix, b->max_fits, b->P, b->rule, b->eval_grid, b->tol, b->max_iter,
                       b->stream);
     hip_check(hipStreamEndCapture(b->stream, &g), "hipStreamEndCapture");
     const hipError_t e = hipGraphInstantiate(&b->exec, g, nullptr, nullptr, 0);
@@ -90,7 +90,7 @@ static void step(fn_batch* b) {
   if (b->use_graph) {
     hip_check(hipGraphLaunch(step_graph(b), b->stream), "hipGraphLaunch");
   } else {
-    batch_launch_step(b->dev(), b->m->mix, b->max_fits, b->P, b->chunk, b->eval_grid, b->tol, b->max_iter,
+    batch_launch_step(b->dev(), b->m->mix, b->max_fits, b->P, b->rule, b->eval_grid, b->tol, b->max_iter,
                       b->stream);
     hip_check(hipGetLastError(), "kernel launch");
   }
@@ -121,8 +121,10 @@ fn_status fn_batch_create(fn_model* m, int32_t max_fits, int64_t max_events_per_
     b->max_fits = max_fits;
     b->max_ev = max_events_per_fit;
     b->P = m->P;
-    b->chunk = m->chunk;
-    b->rows_per_slot = (max_events_per_fit + m->chunk - 1) / m->chunk;
+    b->rule = m->rule();
+    // most rows of any fit up to that size (a rule with slots never gives more)
+    b->rows_per_slot = (max_events_per_fit + b->rule.lo - 1) / b->rule.lo;
+    if (b->rule.slots > 0) b->rows_per_slot = std::min<int64_t>(b->rows_per_slot, b->rule.slots);
     const int kmax = mix1d_kmax(m->mix.K);
     const int nv = mix1d_nv(kmax, true);
     hip_check(hipStreamCreateWithFlags(&b->stream, hipStreamNonBlocking), "hipStreamCreate");
@@ -332,14 +334,14 @@ fn_status fn_batch_step(fn_batch* b, void* stream) {
     hip_check(hipStreamIsCapturing(s, &cs), "hipStreamIsCapturing");
     if (cs == hipStreamCaptureStatusActive) {
       // recorded into the caller's graph: the step's kernels themselves
-      batch_launch_step(b->dev(), b->m->mix, b->max_fits, b->P, b->chunk, b->eval_grid, b->tol, b->max_iter, s);
+      batch_launch_step(b->dev(), b->m->mix, b->max_fits, b->P, b->rule, b->eval_grid, b->tol, b->max_iter, s);
       hip_check(hipGetLastError(), "kernel launch");
       return;
     }
     if (b->use_graph) {
       hip_check(hipGraphLaunch(step_graph(b), s), "hipGraphLaunch");
     } else {
-      batch_launch_step(b->dev(), b->m->mix, b->max_fits, b->P, b->chunk, b->eval_grid, b->tol, b->max_iter, s);
+      batch_launch_step(b->dev(), b->m->mix, b->max_fits, b->P, b->rule, b->eval_grid, b->tol, b->max_iter, s);
       hip_check(hipGetLastError(), "kernel launch");
     }
     if (!b->step_done) hip_check(hipEventCreateWithFlags(&b->step_done, hipEventDisableTiming), "hipEventCreate");

@@ -52,7 +52,10 @@ struct fn_model {
   int kind = 0;
   int P = 0;
   int n_obs = 0;
-  int chunk = 1024;       // events per workgroup (defines the summation tree)
+  int chunk = 1024;       // events per workgroup (defines the summation tree): the model's default
+  bool chunk_fixed = false;  // set by the description or the autotuner: the same for every sample
+  int chunk_lo = 1024, chunk_slots = 0;  // otherwise by the sample's size (ChunkRule)
+  fn::ChunkRule rule() const { return chunk_fixed ? fn::ChunkRule{chunk, 0} : fn::ChunkRule{chunk_lo, chunk_slots}; }
   int grid_chunk = 1024;  // grid cells per workgroup
   fn::Mix1dConst mix;
   fn::DalitzConst dal;

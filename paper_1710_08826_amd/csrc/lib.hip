@@ -37,7 +37,6 @@ constexpr uint32_t kPhaseSpaceStream0 = 100;
 // on 256 compute units) -- where they differ from the first ones.
 constexpr int kTunePow2 = 7;
 constexpr int kTuneMultiples = 8;
-constexpr int kMaxChunk = 1 << 22;
 static_assert(kTunePow2 + kTuneMultiples <= FN_TUNE_MAX, "candidate table");
 constexpr double kTuneTie = 0.02;  // relative time difference treated as a tie
 
@@ -453,7 +452,12 @@ double* Workspace::take_back(size_t count) {
 
 void run_nll(fn_model* m, const ParamBlock* pb, const double* theta_dev, const double* ev, int64_t n, int64_t ld,
              bool grad, double* out_user, hipStream_t s, Workspace* ws) {
-  const int64_t nch = nchunks_for(n, m->chunk);
+  const ChunkRule rule = m->rule();
+  const int chunk = rule(n);
+  const int64_t nch = nchunks_for(n, chunk);
+  // rows the buffers hold: with a rule, the most of any sample (a call on
+  // another sample size does not move buffers that a captured graph refers to)
+  const int64_t room = std::max<int64_t>(std::max<int64_t>(nch, 1), ws ? 1 : rule.slots);
   // level-1 partial rows of the events pass, and the normalization's partial
   // rows: model-owned buffers, or the front and the back of a workspace
   double* part = nullptr;
@@ -480,18 +484,18 @@ void run_nll(fn_model* m, const ParamBlock* pb, const double* theta_dev, const d
     const Mix1dConst& mc = m->mix;
     const int kmax = mix1d_kmax(mc.K);
     const int nv = mix1d_nv(kmax, grad);
-    events_rows((size_t)(nch > 0 ? nch : 1) * nv);
+    events_rows((size_t)room * nv);
     ParamBlock zero;
     mix1d_launch_prologue(mc, pb ? *pb : zero, pb ? nullptr : theta_dev, 1, 0, m->table_mix(), s);
     m->timed(launches, [&](hipEvent_t t0, hipEvent_t t1) {
-      mix1d_launch_events(mc, m->table_mix(), ev, n, m->chunk, nch, grad, part, s, t0, t1);
+      mix1d_launch_events(mc, m->table_mix(), ev, n, chunk, nch, grad, part, s, t0, t1);
     });
     mix1d_launch_finalize(mc, m->table_mix(), part, nch, grad, (double)n, m->out(), out_user, s);
   } else if (m->kind == kKindTddp3) {
     const DalitzConst& dc = m->dal;
     const int nv = tddp_nv(dc.K, grad);
     const int64_t pre = presum_blocks(nch, nv, 0, 0);
-    events_rows((size_t)((nch > 0 ? nch : 1) + pre) * nv);
+    events_rows((size_t)(room + (ws ? pre : presum_blocks(room, nv, 0, 0))) * nv);
     if (pb || !m->table_ready) {
       ParamBlock zero;
       dalitz_launch_prologue(dc, pb ? *pb : zero, pb ? nullptr : theta_dev, m->fixed(), 1, 0, m->table_dal(), s);
@@ -510,7 +514,7 @@ void run_nll(fn_model* m, const ParamBlock* pb, const double* theta_dev, const d
       m->M_valid = true;
     }
     m->timed(launches, [&](hipEvent_t t0, hipEvent_t t1) {
-      tddp_launch_events(*m->tddp_jit, dc, m->table_dal(), m->tdt, coef, ev, ld, n, m->chunk, nch, grad,
+      tddp_launch_events(*m->tddp_jit, dc, m->table_dal(), m->tdt, coef, ev, ld, n, chunk, nch, grad,
                          part, s, t0, t1);
     });
     // long row sets: pre-summed into the room after the rows
@@ -523,7 +527,7 @@ void run_nll(fn_model* m, const ParamBlock* pb, const double* theta_dev, const d
     const int kmax = td4_kmax(tc.K);
     const int nv = td4_nv(tc, grad);
     const int64_t pre = presum_blocks(nch, nv, 0, 0);
-    events_rows((size_t)((nch > 0 ? nch : 1) + pre) * nv);
+    events_rows((size_t)(room + (ws ? pre : presum_blocks(room, nv, 0, 0))) * nv);
     const Td4FitConst* fc = (const Td4FitConst*)m->d_fixed.ptr;
     td4_launch_prologue(tc, pb, theta_dev, m->P, fc, nullptr, 1, m->table_td4(), s);
     if (!m->M_valid) {
@@ -536,7 +540,7 @@ void run_nll(fn_model* m, const ParamBlock* pb, const double* theta_dev, const d
       m->M_valid = true;
     }
     m->timed(launches, [&](hipEvent_t t0, hipEvent_t t1) {
-      td4_launch_events(*m->td4_jit, tc, m->table_td4(), nullptr, 1, ev, ld, n, m->chunk, grad, part, s, t0,
+      td4_launch_events(*m->td4_jit, tc, m->table_td4(), nullptr, 1, ev, ld, n, chunk, grad, part, s, t0,
                         t1);
     });
     // long row sets: pre-summed into the room after the rows
@@ -555,7 +559,9 @@ void run_nll(fn_model* m, const ParamBlock* pb, const double* theta_dev, const d
     const int grid_nv = dc.free_ls ? dalitz_nv_events(kmax, g) : 0;
     const int64_t pre_e = presum_blocks(nch, nv, grid_rows_n, grid_nv);
     const int64_t pre_g = pre_e > 0 && dc.free_ls ? presum_blocks(grid_rows_n, grid_nv, nch, nv) : 0;
-    events_rows((size_t)((nch > 0 ? nch : 1) + pre_e) * nv);
+    const int64_t room_e = ws ? pre_e : presum_blocks(room, nv, grid_rows_n, grid_nv);
+    const int64_t room_g = ws ? pre_g : (dc.free_ls ? presum_blocks(grid_rows_n, grid_nv, room, nv) : 0);
+    events_rows((size_t)(room + room_e) * nv);
     // The table holds the lineshape constants (functions of theta only when the
     // lineshapes are free) and a copy of the coefficients; with fixed lineshapes
     // and theta on the device, the passes read the coefficients from theta and
@@ -573,7 +579,7 @@ void run_nll(fn_model* m, const ParamBlock* pb, const double* theta_dev, const d
       // lineshapes move: integrate P~ (and dP~) over the grid every call
       nrows = grid_rows_n;
       nnv = grid_nv;
-      norm_rows((size_t)(nrows + pre_g) * nnv);
+      norm_rows((size_t)(nrows + room_g) * nnv);
       dalitz_launch_grid(*m->dal_jit, dc, m->table_dal(), coef, (const GridCell*)m->d_cells.ptr, m->n_inside,
                          m->grid_chunk, nrows, g, npart, s);
       grid_rows = npart;
@@ -605,7 +611,7 @@ void run_nll(fn_model* m, const ParamBlock* pb, const double* theta_dev, const d
       span = (unsigned long long*)m->d_span.ptr;
     }
     m->timed(launches, [&](hipEvent_t t0, hipEvent_t t1) {
-      dalitz_launch_events(m->ept == 2 ? *m->dal_jit2 : *m->dal_jit, dc, m->table_dal(), coef, ev, ld, n, m->chunk,
+      dalitz_launch_events(m->ept == 2 ? *m->dal_jit2 : *m->dal_jit, dc, m->table_dal(), coef, ev, ld, n, chunk,
                            nch, g, part, s,
                            norm_in_pass ? m->Mc() : nullptr, norm_in_pass ? m->out() : nullptr, t0, t1, span);
     });
@@ -803,6 +809,7 @@ fn_status fn_model_create(fn_ctx* ctx, const char* desc_json, fn_model** out) {
         if (c % 256 != 0 || c < 256 || c > kMaxChunk)
           throw Error(FN_E_INVALID, "chunk must be a multiple of 256 in [256, " + std::to_string(kMaxChunk) + "]");
         m->chunk = (int)c;
+        m->chunk_fixed = true;
       }
       if (d.has("events_per_thread")) set_dalitz_ept(m, d.at("events_per_thread").integer());
     } catch (const Error&) {
@@ -810,6 +817,25 @@ fn_status fn_model_create(fn_ctx* ctx, const char* desc_json, fn_model** out) {
     } catch (const std::exception& e) {
       throw Error(FN_E_INVALID, std::string("model description: ") + e.what());
     }
+    // Without a fixed chunk the sample's size sets it: the workgroups per
+    // compute unit it is cut into at most, and the least events for which a
+    // workgroup's reduction pays.  The amplitude passes are bound by instruction
+    // issue at two workgroups per compute unit (the mixing ones hold no more
+    // registers), and a small sample gets one event per thread on as many
+    // workgroups as it has; the rows of free lineshapes are summed by many
+    // workgroups anyway, and four balance the compute units better (4M events:
+    // 120.4 us at four, 123.4 at two); the mixture's loads need eight, and below
+    // 1024 events its reduction costs more than it saves (1e5 events: 512 +30 %).
+    // NLL and gradient against the fixed chunks (2048; 4096 for the mixing
+    // models; 1024 for mixtures): three-body 20011 events 35.9 -> 31.5 us,
+    // four-body 20k .. 200k events 76-87 -> 39 us, mixture of 2^26 events 342 ->
+    // 207 us (65536 rows had gone through the level-2 workgroup, 135 us).
+    int cus = 0;
+    hip_check(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, m->device), "hipDeviceGetAttribute");
+    const bool mix = m->kind == kKindMix1d;
+    m->chunk_lo = mix ? m->chunk : kBlock;
+    const bool free_ls = m->kind == kKindDalitz3 && m->dal.free_ls;
+    m->chunk_slots = (mix ? 8 : (free_ls ? 4 : 2)) * (cus > 0 ? cus : 1);
     m->d_out.reserve(sizeof(double) * (2 + 2 * m->P));
     m->d_count.reserve(sizeof(unsigned long long));
     if (hipHostMalloc((void**)&m->h_out, sizeof(double) * (2 + 2 * m->P) + 64, hipHostMallocDefault) !=
@@ -890,6 +916,7 @@ fn_status fn_model_autotune(fn_model* m, const double* theta_host, const double*
     hipStream_t s = (hipStream_t)stream;
     const ParamBlock pb = make_block(m, theta_host);
     const int saved = m->chunk, saved_ept = m->ept;
+    const bool saved_fixed = m->chunk_fixed;
     int cus = 0;
     hip_check(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, m->device),
               "hipDeviceGetAttribute");
@@ -910,6 +937,7 @@ fn_status fn_model_autotune(fn_model* m, const double* theta_host, const double*
         m->ept = e + 1;
         for (int c = 0; c < count; ++c) {
           m->chunk = cand[c];
+          m->chunk_fixed = true;
           for (int w = 0; w < 3; ++w) run_nll(m, &pb, nullptr, ev, n, ld, true, nullptr, s);  // warm-up, buffers
           for (int r = 0; r < reps; ++r) {
             hip_check(hipEventRecord(evs[2 * r], s), "hipEventRecord");
@@ -930,6 +958,7 @@ fn_status fn_model_autotune(fn_model* m, const double* theta_host, const double*
       }
     } catch (...) {
       m->chunk = saved;
+      m->chunk_fixed = saved_fixed;
       m->ept = saved_ept;
       for (auto& e : evs) (void)hipEventDestroy(e);
       throw;

@@ -18,6 +18,22 @@ namespace fn {
 constexpr int kBlock = 256;           // threads per workgroup (4 wave64s)
 constexpr int kWaves = kBlock / 64;
 constexpr int kMaxParams = 96;
+constexpr int kMaxChunk = 1 << 22;    // most events per workgroup
+
+// Events per workgroup of a call on n events: lo, or (slots > 0) the smallest
+// multiple of kBlock from lo on that gives at most `slots` workgroups -- one
+// round of the workgroups that keep the device busy, each as long as the
+// sample allows.  A chunk fixed by the model's description or by the autotuner
+// has slots = 0.
+struct ChunkRule {
+  int lo, slots;
+  __host__ __device__ int operator()(int64_t n) const {
+    if (slots <= 0 || n <= (int64_t)lo * slots) return lo;
+    const int64_t per = (n + slots - 1) / slots;
+    const int64_t c = (per + kBlock - 1) / kBlock * kBlock;
+    return c < lo ? lo : (c > kMaxChunk ? kMaxChunk : (int)c);
+  }
+};
 
 // Parameter vector passed by value (kernel argument segment).
 struct ParamBlock {

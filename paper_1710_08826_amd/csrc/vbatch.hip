@@ -93,7 +93,8 @@ void check_events(fn_vbatch* b, const double* ev, int64_t n, int64_t ld) {
 }
 
 void reserve_part(fn_vbatch* b, int64_t n) {
-  const int64_t nch = (n + b->m->chunk - 1) / b->m->chunk;
+  const int chunk = b->m->rule()(n);
+  const int64_t nch = (n + chunk - 1) / chunk;
   const void* before = b->part.ptr;
   b->part.reserve(sizeof(double) * (size_t)nch * b->F * td4_nv(b->m->td4, true));
   if (b->part.ptr != before) b->drop_graph();  // a captured step holds the old address
@@ -121,13 +122,14 @@ void upload_fixed(fn_vbatch* b) {
 void launch_step(fn_vbatch* b, const double* ev, int64_t n, int64_t ld, double tol, int max_iter) {
   fn_model* m = b->m;
   const Td4Const& tc = m->td4;
-  const int64_t nch = (n + m->chunk - 1) / m->chunk;
+  const int chunk = m->rule()(n);
+  const int64_t nch = (n + chunk - 1) / chunk;
   const int stride = (int)(sizeof(VState) / sizeof(double));
   auto* tabs = (Td4Table*)b->tabs.ptr;
   auto* stat = (const int*)b->stat.ptr;
   td4_launch_prologue(tc, nullptr, (const double*)b->st.ptr, stride, (const Td4FitConst*)b->fc.ptr, stat, b->F, tabs,
                       b->stream);
-  td4_launch_events(*m->td4_jit, tc, tabs, stat, b->F, ev, ld, n, m->chunk, true, (double*)b->part.ptr,
+  td4_launch_events(*m->td4_jit, tc, tabs, stat, b->F, ev, ld, n, chunk, true, (double*)b->part.ptr,
                     b->stream);
   td4_launch_finalize(tc, tabs, stat, b->F, (const double*)b->part.ptr, nch, true, (const double*)b->Mc.ptr,
                       (double)n, (double*)b->out.ptr, 2 + 2 * b->P, nullptr, b->stream);
@@ -242,9 +244,10 @@ fn_status fn_vbatch_nll(fn_vbatch* b, const double* theta_host, const double* ev
     td4_launch_prologue(m->td4, nullptr, (const double*)b->theta.ptr, P, (const Td4FitConst*)b->fc.ptr, nullptr, F,
                         tabs, b->stream);
     build_matrices(b);
-    td4_launch_events(*m->td4_jit, m->td4, tabs, nullptr, F, ev, ld, n, m->chunk, grad, (double*)b->part.ptr,
+    const int chunk = m->rule()(n);
+    td4_launch_events(*m->td4_jit, m->td4, tabs, nullptr, F, ev, ld, n, chunk, grad, (double*)b->part.ptr,
                       b->stream);
-    const int64_t nch = (n + m->chunk - 1) / m->chunk;
+    const int64_t nch = (n + chunk - 1) / chunk;
     td4_launch_finalize(m->td4, tabs, nullptr, F, (const double*)b->part.ptr, nch, grad, (const double*)b->Mc.ptr,
                         (double)n, (double*)b->out.ptr, 2 + 2 * P, nullptr, b->stream);
     hip_check(hipGetLastError(), "kernel launch");
