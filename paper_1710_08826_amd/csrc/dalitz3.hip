@@ -418,7 +418,7 @@ std::shared_ptr<DalitzJit> dalitz_jit(const DalitzConst& dc, int ept) {
 }
 
 static void launch_pass(hipFunction_t f, const DalitzConst& dc, const DalitzTable* tab, const double* coef,
-                        const double* ev, int64_t ld, int64_t n, int chunk, int64_t nchunks, int i0, double* part,
+                        const CoefArg& ca, const double* ev, int64_t ld, int64_t n, int chunk, int64_t nchunks, int i0, double* part,
                         hipStream_t s, const double* Mc = nullptr, double* norm_out = nullptr,
                         hipEvent_t start = nullptr, hipEvent_t stop = nullptr,
                         unsigned long long* span = nullptr) {
@@ -426,6 +426,7 @@ static void launch_pass(hipFunction_t f, const DalitzConst& dc, const DalitzTabl
   DalitzConst c = dc;
   const DalitzTable* t = tab;
   const double* cf = coef;
+  CoefArg a = ca;
   const double* e = ev;
   int64_t l = ld, nn = n;
   int ch = chunk, ii = i0;
@@ -433,7 +434,7 @@ static void launch_pass(hipFunction_t f, const DalitzConst& dc, const DalitzTabl
   const double* m = Mc;
   double* no = norm_out;
   unsigned long long* sp = span;
-  void* args[] = {&c, &t, &cf, &e, &l, &nn, &ch, &ii, &p, &m, &no, &sp};
+  void* args[] = {&c, &t, &cf, &a, &e, &l, &nn, &ch, &ii, &p, &m, &no, &sp};
   jit_launch(f, (unsigned)nchunks, kBlock, s, args, start, stop);
 }
 
@@ -456,12 +457,12 @@ static DalFinal make_final(const double* npart, int64_t n_rows, int n_nv, const 
 }
 
 void dalitz_launch_events(const DalitzJit& j, const DalitzConst& dc, const DalitzTable* tab, const double* coef,
-                          const double* ev, int64_t ld, int64_t n, int chunk, int64_t nchunks, int grad, double* part,
+                          const CoefArg& ca, const double* ev, int64_t ld, int64_t n, int chunk, int64_t nchunks, int grad, double* part,
                           hipStream_t s, const double* Mc, double* out, hipEvent_t start, hipEvent_t stop,
                           unsigned long long* span) {
   if (nchunks == 0) return;
   const int P = dc.free_ls ? 4 * dc.K : 2 * dc.K;
-  launch_pass(j.ev[grad], dc, tab, coef, ev, ld, n, chunk, nchunks, 0, part, s, Mc,
+  launch_pass(j.ev[grad], dc, tab, coef, ca, ev, ld, n, chunk, nchunks, 0, part, s, Mc,
               Mc && out ? out + 1 + P : nullptr, start, stop, span);
 }
 
@@ -510,14 +511,14 @@ void dalitz_launch_finalize(const DalitzConst& dc, const DalitzTable* tab, const
 void dalitz_launch_grid(const DalitzJit& j, const DalitzConst& dc, const DalitzTable* tab, const double* coef,
                         const GridCell* cells, int64_t n_inside, int chunk, int64_t nchunks, int grad, double* part,
                         hipStream_t s) {
-  launch_pass(j.gr[grad], dc, tab, coef, reinterpret_cast<const double*>(cells), 0, n_inside, chunk, nchunks, 0,
+  launch_pass(j.gr[grad], dc, tab, coef, CoefArg{}, reinterpret_cast<const double*>(cells), 0, n_inside, chunk, nchunks, 0,
               part, s);
 }
 
 void dalitz_launch_mrows(const DalitzJit& j, const DalitzConst& dc, const DalitzTable* tab, int chunk,
                          int64_t nchunks, int i0, double* part, double* Mc, hipStream_t s) {
   const int64_t ncell = (int64_t)dc.nx * dc.ny;
-  launch_pass(j.mrows, dc, tab, nullptr, nullptr, 0, ncell, chunk, nchunks, i0, part, s);
+  launch_pass(j.mrows, dc, tab, nullptr, CoefArg{}, nullptr, 0, ncell, chunk, nchunks, i0, part, s);
   dalitz_launch_mrows_finalize(dc, part, nchunks, i0, Mc, s);
 }
 

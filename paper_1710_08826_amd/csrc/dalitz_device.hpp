@@ -197,7 +197,7 @@ __device__ __forceinline__ void dalitz_pair_terms(const DalitzConst& dc, double 
 // reciprocals), added to the coherent sum S = sum_k c_k A_k.
 template <class S, int MODE, bool KEEP_A, bool KEEP_T>
 __device__ __forceinline__ void dalitz_amps(const DalitzConst& dc, const double* __restrict__ r,
-                                            const double* __restrict__ coef, double s12, double s13, double s23,
+                                            cdouble* __restrict__ coef, double s12, double s13, double s23,
                                             double (&Are)[S::K], double (&Aim)[S::K], double (&Tre)[S::K],
                                             double (&Tim)[S::K], double (&Gk)[S::K], double& Sre, double& Sim) {
   constexpr int K = S::K;
@@ -247,7 +247,7 @@ __device__ __forceinline__ void dalitz_amps(const DalitzConst& dc, const double*
 // contributes exact zeros, so the sum is unchanged).
 template <class S, int MODE, int GRAD>
 __device__ __forceinline__ void dalitz_point(const DalitzConst& dc, const double* __restrict__ r,
-                                             const double* __restrict__ coef, double s12, double s13, bool valid,
+                                             cdouble* __restrict__ coef, double s12, double s13, bool valid,
                                              int i0, double (&acc)[dal_nv(MODE, GRAD, S::K)], LogProd& lp) {
   constexpr int K = S::K;
   constexpr bool KEEP_A = (GRAD >= 1) || MODE == kMRows;
@@ -331,7 +331,7 @@ __device__ __forceinline__ void dalitz_point(const DalitzConst& dc, const double
 // autotuner times them, the grid and matrix-row passes use one.
 template <class S, int MODE, int GRAD, int EPT = 1>
 __device__ inline void dalitz_chunk(const DalitzConst& dc, const DalitzTable* __restrict__ tab,
-                                    const double* __restrict__ coef0, const double* __restrict__ ev, int64_t ld,
+                                    cdouble* __restrict__ coef0, const double* __restrict__ ev, int64_t ld,
                                     int64_t n, int64_t chunk_idx, int chunk, int i0, double* __restrict__ out_row,
                                     double* lds) {
   constexpr int NV = dal_nv(MODE, GRAD, S::K);
@@ -361,7 +361,7 @@ __device__ inline void dalitz_chunk(const DalitzConst& dc, const DalitzTable* __
     int zero = 0;
     asm volatile("" : "+s"(zero));
     const double* r = r0 + zero;
-    const double* coef = coef0 + zero;
+    cdouble* coef = coef0 + zero;
 #pragma unroll
     for (int e = 0; e < EPT; ++e) {
       const int64_t j = i + e * kBlock;
@@ -410,7 +410,7 @@ __device__ inline void dalitz_chunk(const DalitzConst& dc, const DalitzTable* __
 // dI/dIm c_k = -2 Im X_k.  Writes out[0] = I and out[1 + 2k], out[2 + 2k];
 // all threads of the workgroup call it.
 template <class S>
-__device__ inline void dalitz_cached_norm(const double* __restrict__ M, const double* __restrict__ coef,
+__device__ inline void dalitz_cached_norm(const double* __restrict__ M, cdouble* __restrict__ coef,
                                           double* __restrict__ out) {
   constexpr int K = S::K;
   __shared__ double ip[K];
@@ -438,7 +438,8 @@ __device__ inline void dalitz_cached_norm(const double* __restrict__ M, const do
 }
 
 // One workgroup per chunk, one row of NV partial sums each.
-// coef: (Re c_k, Im c_k) of the resonances (theta's first 2K entries, or the
+// coef: (Re c_k, Im c_k) of the resonances (theta's first 2K entries, the
+// launch's own arguments, or the
 // table's copy of them); unused by kMRows.  Events pass with a cached grid
 // matrix (M not null): the last workgroup, whose chunk is the shortest,
 // also evaluates the normalization into norm_out (dalitz_cached_norm), so
@@ -446,7 +447,7 @@ __device__ inline void dalitz_cached_norm(const double* __restrict__ M, const do
 // (span_begin / span_end), null when the launch is not measured.
 template <class S, int MODE, int GRAD, int EPT = 1>
 __device__ inline void dalitz_pass_body(const DalitzConst& dc, const DalitzTable* __restrict__ tab,
-                                        const double* __restrict__ coef, const double* __restrict__ ev, int64_t ld,
+                                        cdouble* __restrict__ coef, const double* __restrict__ ev, int64_t ld,
                                         int64_t n, int chunk, int i0, double* __restrict__ part,
                                         const double* __restrict__ M, double* __restrict__ norm_out,
                                         unsigned long long* __restrict__ span) {
@@ -463,7 +464,7 @@ __device__ inline void dalitz_pass_body(const DalitzConst& dc, const DalitzTable
 // P~(s12, s13) = |sum_k c_k A_k|^2 at one point.
 template <class S>
 __device__ __forceinline__ double dalitz_value(const DalitzConst& dc, const double* __restrict__ r,
-                                               const double* __restrict__ coef, double s12, double s13) {
+                                               cdouble* __restrict__ coef, double s12, double s13) {
   constexpr int K = S::K;
   const double s23 = dc.msum - s12 - s13;
   double Are[K], Aim[K], Tre[K], Tim[K], Gk[K];
@@ -486,7 +487,7 @@ __device__ inline void dalitz_gridmax_body(const DalitzConst& dc, const DalitzTa
     const double s12 = grid_centre(dc.a12, ix, dc.d12);
     const double s13 = grid_centre(dc.a13, iy, dc.d13);
     if (!dalitz_inside(dc, s12, s13)) continue;
-    m = fmax(m, dalitz_value<S>(dc, r, tab->coef, s12, s13));
+    m = fmax(m, dalitz_value<S>(dc, r, (cdouble*)tab->coef, s12, s13));
   }
   lds[threadIdx.x] = m;
   __syncthreads();
@@ -523,7 +524,7 @@ __device__ inline void dalitz_gen_body(const DalitzConst& dc, const DalitzTable*
     const double s12 = lo12 + u1 * w12;
     const double s13 = lo13 + u2 * w13;
     if (!dalitz_inside(dc, s12, s13)) continue;
-    const double p = dalitz_value<S>(dc, r, tab->coef, s12, s13);
+    const double p = dalitz_value<S>(dc, r, (cdouble*)tab->coef, s12, s13);
     if (u3 * W < p) {
       x12 = s12;
       x13 = s13;
@@ -541,12 +542,15 @@ __device__ inline void dalitz_gen_body(const DalitzConst& dc, const DalitzTable*
 
 // Kernel NAME for shape S, mode, gradient level and events per thread and
 // iteration (used by the generated source).
+// coef null: the coefficients are the launch's arguments.
 #define FN_DALITZ_KERNEL(NAME, S, MODE, GRAD, EPT)                                                           \
   extern "C" __global__ __launch_bounds__(fn::kBlock) void NAME(                                               \
       fn::DalitzConst dc, const fn::DalitzTable* __restrict__ tab, const double* __restrict__ coef,           \
-      const double* __restrict__ ev, int64_t ld, int64_t n, int chunk, int i0, double* __restrict__ part,     \
-      const double* __restrict__ M, double* __restrict__ norm_out, unsigned long long* __restrict__ span) {    \
-    fn::dalitz_pass_body<S, MODE, GRAD, EPT>(dc, tab, coef, ev, ld, n, chunk, i0, part, M, norm_out, span);    \
+      fn::CoefArg ca, const double* __restrict__ ev, int64_t ld, int64_t n, int chunk, int i0,                 \
+      double* __restrict__ part, const double* __restrict__ M, double* __restrict__ norm_out,                  \
+      unsigned long long* __restrict__ span) {                                                                 \
+    fn::cdouble* c = coef ? (fn::cdouble*)coef : (fn::cdouble*)&ca.v[0];                                       \
+    fn::dalitz_pass_body<S, MODE, GRAD, EPT>(dc, tab, c, ev, ld, n, chunk, i0, part, M, norm_out, span);       \
   }
 
 // Grid maximum and accept-reject generator for shape S.

@@ -76,7 +76,8 @@ struct fn_model {
   int64_t n_inside = 0;          // their number
   double box[4] = {0.0, 0.0, 0.0, 0.0};  // Dalitz: kinematic box (s12 lo, hi, s13 lo, hi)
   fn::DevBuf d_theta;                    // tddp3: theta on the device for host-theta calls
-  double* h_out = nullptr;       // pinned
+  double* h_out = nullptr;       // pinned: results of synchronous calls (written by the level-2 step)
+  double* h_out_dev = nullptr;   // the same on the device
   long long stats_calls = 0;
   int timing = 0;                // time every timing-th event-pass launch with HIP events (0 = off,
                                  // -1: in-kernel spans of every Dalitz event-pass launch into d_span)

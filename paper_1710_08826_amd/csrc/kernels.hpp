@@ -58,11 +58,12 @@ int dalitz_nv_mrows(int kmax);
 void dalitz_launch_prologue(const DalitzConst& dc, const ParamBlock& pb, const double* theta_dev,
                             const double* fixed_ls, int n_fits, int theta_stride, DalitzTable* tab, hipStream_t s);
 // Events pass: one row of partial sums per chunk of events.
-// coef: (Re c_k, Im c_k) in device memory (theta itself, or the table's copy).
+// coef: (Re c_k, Im c_k) in device memory (theta itself, or the table's copy),
+// or null: ca, passed with the launch.
 // With the cached grid matrix Mc (fixed lineshapes) and the output buffer
 // out = [NLL, grad, I, dI], the pass also writes I and dI into out.
 void dalitz_launch_events(const DalitzJit& j, const DalitzConst& dc, const DalitzTable* tab, const double* coef,
-                          const double* ev, int64_t ld, int64_t n, int chunk, int64_t nchunks, int grad, double* part,
+                          const CoefArg& ca, const double* ev, int64_t ld, int64_t n, int chunk, int64_t nchunks, int grad, double* part,
                           hipStream_t s, const double* Mc = nullptr, double* out = nullptr,
                           hipEvent_t start = nullptr, hipEvent_t stop = nullptr,
                           unsigned long long* span = nullptr);

@@ -496,16 +496,14 @@ void run_nll(fn_model* m, const ParamBlock* pb, const double* theta_dev, const d
     const int nv = tddp_nv(dc.K, grad);
     const int64_t pre = presum_blocks(nch, nv, 0, 0);
     events_rows((size_t)(room + (ws ? pre : presum_blocks(room, nv, 0, 0))) * nv);
-    if (pb || !m->table_ready) {
+    if (!m->table_ready) {  // the lineshape constants; the coefficients are read from theta
       ParamBlock zero;
       dalitz_launch_prologue(dc, pb ? *pb : zero, pb ? nullptr : theta_dev, m->fixed(), 1, 0, m->table_dal(), s);
       m->table_ready = true;
     }
-    const double* coef = theta_dev;
-    if (pb) {
-      tddp_launch_copy_theta(*pb, m->P, (double*)m->d_theta.ptr, s);
-      coef = (const double*)m->d_theta.ptr;
-    }
+    const double* coef = pb ? nullptr : theta_dev;  // null: theta goes with the launches
+    TddpArg ca{};
+    if (pb) std::memcpy(ca.v, pb->v, sizeof(double) * m->P);
     if (!m->M_valid) {
       const int64_t ncell = (int64_t)dc.nx * dc.ny;
       const int64_t mrows = nchunks_for(ncell, m->grid_chunk);
@@ -514,12 +512,12 @@ void run_nll(fn_model* m, const ParamBlock* pb, const double* theta_dev, const d
       m->M_valid = true;
     }
     m->timed(launches, [&](hipEvent_t t0, hipEvent_t t1) {
-      tddp_launch_events(*m->tddp_jit, dc, m->table_dal(), m->tdt, coef, ev, ld, n, chunk, nch, grad,
+      tddp_launch_events(*m->tddp_jit, dc, m->table_dal(), m->tdt, coef, ca, ev, ld, n, chunk, nch, grad,
                          part, s, t0, t1);
     });
     // long row sets: pre-summed into the room after the rows
     launch_rows_presum(part, nch, nv, part + nch * nv, pre, nullptr, 0, 0, nullptr, 0, s);
-    tddp_launch_finalize(dc, m->table_dal(), m->tdt, coef, pre ? part + nch * nv : part, pre ? pre : nch, grad,
+    tddp_launch_finalize(dc, m->table_dal(), m->tdt, coef, ca, pre ? part + nch * nv : part, pre ? pre : nch, grad,
                          m->Mc(), (double)n, m->out(), out_user, s);
   } else if (m->kind == kKindTd4) {
     const Td4Const& tc = m->td4;
@@ -566,12 +564,17 @@ void run_nll(fn_model* m, const ParamBlock* pb, const double* theta_dev, const d
     // lineshapes are free) and a copy of the coefficients; with fixed lineshapes
     // and theta on the device, the passes read the coefficients from theta and
     // the table is built once.
-    if (dc.free_ls || pb || !m->table_ready) {
+    // With theta on the host they take them with the launch (except without
+    // events, where the level-2 step evaluates I from the table's copy).
+    const bool coef_arg = pb && !dc.free_ls && nch > 0;
+    if (dc.free_ls || (pb && !coef_arg) || !m->table_ready) {
       ParamBlock zero;
       dalitz_launch_prologue(dc, pb ? *pb : zero, pb ? nullptr : theta_dev, m->fixed(), 1, 0, m->table_dal(), s);
       if (!dc.free_ls) m->table_ready = true;
     }
-    const double* coef = theta_dev ? theta_dev : m->table_dal()->coef;
+    CoefArg ca{};
+    if (coef_arg) std::memcpy(ca.v, pb->v, sizeof(double) * 2 * dc.K);
+    const double* coef = theta_dev ? theta_dev : (coef_arg ? nullptr : m->table_dal()->coef);
     double* grid_rows = nullptr;
     int64_t nrows = 0;
     int nnv = 0;
@@ -611,7 +614,7 @@ void run_nll(fn_model* m, const ParamBlock* pb, const double* theta_dev, const d
       span = (unsigned long long*)m->d_span.ptr;
     }
     m->timed(launches, [&](hipEvent_t t0, hipEvent_t t1) {
-      dalitz_launch_events(m->ept == 2 ? *m->dal_jit2 : *m->dal_jit, dc, m->table_dal(), coef, ev, ld, n, chunk,
+      dalitz_launch_events(m->ept == 2 ? *m->dal_jit2 : *m->dal_jit, dc, m->table_dal(), coef, ca, ev, ld, n, chunk,
                            nch, g, part, s,
                            norm_in_pass ? m->Mc() : nullptr, norm_in_pass ? m->out() : nullptr, t0, t1, span);
     });
@@ -640,9 +643,8 @@ void nll_host(fn_model* m, const double* theta_host, const double* ev, int64_t n
   check_events_args(m, ev, n, ld);
   const ParamBlock pb = make_block(m, theta_host);
   const bool g = grad != nullptr;
-  run_nll(m, &pb, nullptr, ev, n, ld, g, nullptr, s);
-  const size_t cnt = (size_t)(g ? 1 + m->P : 1);
-  hip_check(hipMemcpyAsync(m->h_out, m->out(), sizeof(double) * cnt, hipMemcpyDeviceToHost, s), "hipMemcpyAsync");
+  // the level-2 step writes the results into pinned host memory itself
+  run_nll(m, &pb, nullptr, ev, n, ld, g, m->h_out_dev, s);
   hip_check(hipStreamSynchronize(s), "hipStreamSynchronize");
   const double v = m->h_out[0];
   m->stats_calls += 1;
@@ -674,10 +676,8 @@ void nll_binned_host(fn_model* m, const double* theta_host, const BinnedData& bd
   m->d_part.reserve(sizeof(double) * (size_t)nch * mix1d_nv_binned(mix1d_kmax(mc.K), g));
   m->d_gen.reserve(3 * sizeof(unsigned long long));
   mix1d_launch_binned(mc, m->table_mix(), bd.counts, bd.nb, m->chunk, nch, bd.stat, g, m->part(),
-                      (double*)m->d_gen.ptr, m->out(), s);
+                      (double*)m->d_gen.ptr, m->h_out_dev, s);
   hip_check(hipGetLastError(), "kernel launch");
-  const size_t cnt = (size_t)(g ? 1 + m->P : 1);
-  hip_check(hipMemcpyAsync(m->h_out, m->out(), sizeof(double) * cnt, hipMemcpyDeviceToHost, s), "hipMemcpyAsync");
   hip_check(hipStreamSynchronize(s), "hipStreamSynchronize");
   m->stats_calls += 1;
   const double v = m->h_out[0];
@@ -843,6 +843,7 @@ fn_status fn_model_create(fn_ctx* ctx, const char* desc_json, fn_model** out) {
       m->h_out = nullptr;
       throw Error(FN_E_NOMEM, "hipHostMalloc failed");
     }
+    hip_check(hipHostGetDevicePointer((void**)&m->h_out_dev, m->h_out, 0), "hipHostGetDevicePointer");
     *out = m;
   });
   if (st != FN_OK && m) {

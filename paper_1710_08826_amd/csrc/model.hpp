@@ -40,6 +40,11 @@ struct ParamBlock {
   double v[kMaxParams];
 };
 
+// Uniform read-only doubles: a pointer into the constant address space, whose
+// loads at uniform offsets are scalar ones wherever it points (device memory
+// or the kernel arguments).
+typedef const __attribute__((address_space(4))) double cdouble;
+
 // ---------------------------------------------------------------- mix1d
 constexpr int kMixMaxComp = 8;
 enum MixType : int { kGauss = 0, kExp = 1, kArgus = 2, kBW = 3 };
@@ -94,6 +99,15 @@ struct DalitzConst {
   int chan[kDalMaxRes];           // 0 = "12", 1 = "13", 2 = "23"
   int L[kDalMaxRes];
   DalitzChan ch[3];
+};
+
+// The coefficients (Re c_k, Im c_k) of a call with theta on the host, passed
+// with the launch; the time-dependent model's whole theta (c, cbar, x, y).
+struct CoefArg {
+  double v[2 * kDalMaxRes];
+};
+struct TddpArg {
+  double v[4 * kDalMaxRes + 2];
 };
 
 // A grid cell inside the physical region: column ix (s12) and row iy (s13).

@@ -81,12 +81,14 @@ struct TddpFinalLds {
 //   dZ/dRe c_i = U_i, dZ/dIm c_i = -i U_i, dZ/dRe cbar_j = V_j, dZ/dIm cbar_j = i V_j.
 // out = [NLL, grad(P), I, dI(P)].
 __global__ __launch_bounds__(kFinalBlock) void tddp_finalize(DalitzConst dc, const DalitzTable* __restrict__ tab,
-                                                             TddpTime tt, const double* __restrict__ coef,
-                                                             const double* __restrict__ part, int64_t nrows, int nv,
+                                                             TddpTime tt, const double* __restrict__ coef_dev,
+                                                             TddpArg ca, const double* __restrict__ part,
+                                                             int64_t nrows, int nv,
                                                              int with_grad, const double* __restrict__ Mc,
                                                              double n_events, double* __restrict__ out,
                                                              double* __restrict__ out_user) {
   __shared__ TddpFinalLds L;
+  const double* coef = coef_dev ? coef_dev : ca.v;  // null: theta is the launch's argument
   const int K = dc.K;
   const int P = 4 * K + 2;
   const int t = threadIdx.x;
@@ -252,25 +254,26 @@ void tddp_launch_gen(const TddpJit& j, const DalitzConst& dc, const DalitzTable*
 }
 
 void tddp_launch_events(const TddpJit& j, const DalitzConst& dc, const DalitzTable* tab, const TddpTime& tt,
-                        const double* coef, const double* ev, int64_t ld, int64_t n, int chunk, int64_t nchunks,
-                        bool grad, double* part, hipStream_t s, hipEvent_t start, hipEvent_t stop) {
+                        const double* coef, const TddpArg& ca, const double* ev, int64_t ld, int64_t n, int chunk,
+                        int64_t nchunks, bool grad, double* part, hipStream_t s, hipEvent_t start, hipEvent_t stop) {
   if (nchunks == 0) return;
   DalitzConst c = dc;
   const DalitzTable* t = tab;
   TddpTime tm = tt;
   const double* cf = coef;
+  TddpArg a = ca;
   const double* e = ev;
   int64_t l = ld, nn = n;
   int ch = chunk;
   double* p = part;
-  void* args[] = {&c, &t, &tm, &cf, &e, &l, &nn, &ch, &p};
+  void* args[] = {&c, &t, &tm, &cf, &a, &e, &l, &nn, &ch, &p};
   jit_launch(j.ev[grad ? 1 : 0], (unsigned)nchunks, kBlock, s, args, start, stop);
 }
 
 void tddp_launch_finalize(const DalitzConst& dc, const DalitzTable* tab, const TddpTime& tt, const double* coef,
-                          const double* part, int64_t nrows, bool grad, const double* Mc, double n_events,
+                          const TddpArg& ca, const double* part, int64_t nrows, bool grad, const double* Mc, double n_events,
                           double* out, double* out_user, hipStream_t s) {
-  hipLaunchKernelGGL(tddp_finalize, dim3(1), dim3(kFinalBlock), 0, s, dc, tab, tt, coef, part, nrows,
+  hipLaunchKernelGGL(tddp_finalize, dim3(1), dim3(kFinalBlock), 0, s, dc, tab, tt, coef, ca, part, nrows,
                      tddp_nv(dc.K, grad), grad ? 1 : 0, Mc, n_events, out, out_user);
 }
 

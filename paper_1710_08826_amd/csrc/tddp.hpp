@@ -24,12 +24,12 @@ void tddp_launch_mmatrices(const TddpJit& j, const DalitzConst& dc, const Dalitz
                            double* part, double* Mc, hipStream_t s);
 // Events pass: one row of partial sums per chunk.  coef: theta on the device.
 void tddp_launch_events(const TddpJit& j, const DalitzConst& dc, const DalitzTable* tab, const TddpTime& tt,
-                        const double* coef, const double* ev, int64_t ld, int64_t n, int chunk, int64_t nchunks,
-                        bool grad, double* part, hipStream_t s, hipEvent_t start = nullptr,
+                        const double* coef, const TddpArg& ca, const double* ev, int64_t ld, int64_t n, int chunk,
+                        int64_t nchunks, bool grad, double* part, hipStream_t s, hipEvent_t start = nullptr,
                         hipEvent_t stop = nullptr);
 // Level-2 and NLL assembly: out = [NLL, grad(P), I, dI(P)].
 void tddp_launch_finalize(const DalitzConst& dc, const DalitzTable* tab, const TddpTime& tt, const double* coef,
-                          const double* part, int64_t nrows, bool grad, const double* Mc, double n_events,
+                          const TddpArg& ca, const double* part, int64_t nrows, bool grad, const double* Mc, double n_events,
                           double* out, double* out_user, hipStream_t s);
 // Toy generation: vmax (zeroed by the caller) receives the bits of the largest
 // (|A| + |Abar|)^2 over the grid; the generator writes n events (3 rows,

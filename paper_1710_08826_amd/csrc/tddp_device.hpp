@@ -109,7 +109,7 @@ __device__ __forceinline__ void tddp_point(const DalitzConst& dc, const double* 
 // The coherent sum of set SIDE, sum_k c_k H T_k, the factor H applied once per
 // pair and spin.
 template <class S, int SIDE>
-__device__ __forceinline__ cplx tddp_sum(const TddpPoint<S>& p, const double* __restrict__ c) {
+__device__ __forceinline__ cplx tddp_sum(const TddpPoint<S>& p, cdouble* __restrict__ c) {
   cplx A = {0.0, 0.0};
 #pragma unroll
   for (int C = 0; C < 3; ++C)
@@ -173,7 +173,7 @@ __device__ __forceinline__ void tddp_basis2(const DalitzConst& dc, const double*
 // coef: theta on the device, (c, cbar, x, y).
 template <class S, bool GRAD>
 __device__ inline void tddp_events_body(const DalitzConst& dc, const DalitzTable* __restrict__ tab,
-                                        const TddpTime& tt, const double* __restrict__ coef0,
+                                        const TddpTime& tt, cdouble* __restrict__ coef0,
                                         const double* __restrict__ ev, int64_t ld, int64_t n, int chunk,
                                         double* __restrict__ part) {
   constexpr int K = S::K;
@@ -202,7 +202,7 @@ __device__ inline void tddp_events_body(const DalitzConst& dc, const DalitzTable
     int zero = 0;
     asm volatile("" : "+s"(zero));
     const double* r = r0 + zero;
-    const double* coef = coef0 + zero;
+    cdouble* coef = coef0 + zero;
     TimeFns T;
     time_fns<GRAD>((&tt.tk)[zero], tt.wa + zero, tt.wL, coef[4 * K], coef[4 * K + 1], t, T);
     TddpPoint<S> pt;
@@ -289,7 +289,7 @@ __device__ inline void tddp_mrows_body(const DalitzConst& dc, const DalitzTable*
 // A and Abar at one point.
 template <class S>
 __device__ __forceinline__ void tddp_amps(const DalitzConst& dc, const double* __restrict__ r,
-                                          const double* __restrict__ coef, double s12, double s13, cplx& A,
+                                          cdouble* __restrict__ coef, double s12, double s13, cplx& A,
                                           cplx& Ab) {
   TddpPoint<S> p;
   tddp_point<S>(dc, r, s12, s13, p);
@@ -312,7 +312,7 @@ __device__ inline void tddp_gridmax_body(const DalitzConst& dc, const DalitzTabl
     const double s13 = grid_centre(dc.a13, iy, dc.d13);
     if (!dalitz_inside(dc, s12, s13)) continue;
     cplx A, Ab;
-    tddp_amps<S>(dc, r, coef, s12, s13, A, Ab);
+    tddp_amps<S>(dc, r, (cdouble*)coef, s12, s13, A, Ab);
     const double e = sqrt(A.re * A.re + A.im * A.im) + sqrt(Ab.re * Ab.re + Ab.im * Ab.im);
     m = fmax(m, e * e);
   }
@@ -358,7 +358,7 @@ __device__ inline void tddp_gen_body(const DalitzConst& dc, const DalitzTable* _
     if (!dalitz_inside(dc, s12, s13)) continue;
     const double t = -log1p(-u3) / lam;
     cplx A, Ab;
-    tddp_amps<S>(dc, r, coef, s12, s13, A, Ab);
+    tddp_amps<S>(dc, r, (cdouble*)coef, s12, s13, A, Ab);
     const double a2 = A.re * A.re + A.im * A.im, b2 = Ab.re * Ab.re + Ab.im * Ab.im;
     const double zr = A.re * Ab.re + A.im * Ab.im, zi = A.re * Ab.im - A.im * Ab.re;
     const double gt = G * t;
@@ -389,12 +389,14 @@ __device__ inline void tddp_gen_body(const DalitzConst& dc, const DalitzTable* _
 }  // namespace fn
 
 // Kernels for shape S (used by the generated source).
+// (coef null: theta is the launch's argument)
 #define FN_TDDP_EVENTS(NAME, S, GRAD)                                                                          \
   extern "C" __global__ __launch_bounds__(fn::kBlock) __attribute__((amdgpu_waves_per_eu(2))) void NAME(       \
       fn::DalitzConst dc, const fn::DalitzTable* __restrict__ tab, fn::TddpTime tt,                            \
-      const double* __restrict__ coef, const double* __restrict__ ev, int64_t ld, int64_t n, int chunk,       \
-      double* __restrict__ part) {                                                                             \
-    fn::tddp_events_body<S, GRAD>(dc, tab, tt, coef, ev, ld, n, chunk, part);                                 \
+      const double* __restrict__ coef, fn::TddpArg ca, const double* __restrict__ ev, int64_t ld, int64_t n,   \
+      int chunk, double* __restrict__ part) {                                                                  \
+    fn::cdouble* c = coef ? (fn::cdouble*)coef : (fn::cdouble*)&ca.v[0];                                       \
+    fn::tddp_events_body<S, GRAD>(dc, tab, tt, c, ev, ld, n, chunk, part);                                    \
   }
 #define FN_TDDP_MROWS(NAME, S, WHICH)                                                                          \
   extern "C" __global__ __launch_bounds__(fn::kBlock) void NAME(                                               \
