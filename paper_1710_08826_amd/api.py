@@ -32,28 +32,43 @@ def context(device: int = 0):
 
 
 def _dbl(a):
-    a = np.ascontiguousarray(np.asarray(a, dtype=np.float64))
-    return a, a.ctypes.data_as(C.POINTER(C.c_double))
+    """A contiguous float64 array of a and a ctypes view of it (kept alive by it)."""
+    a = np.ascontiguousarray(a, dtype=np.float64)
+    if not a.flags.writeable:
+        a = a.copy()
+    return a, _cdbl(a)
+
+
+def _cdbl(a: np.ndarray):
+    # a ctypes array over a's own memory: a third of the cost of ctypes.data_as
+    return (C.c_double * a.size).from_buffer(a) if a.size else (C.c_double * 1)()
+
+
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 
 def _stream_ptr(stream):
     if stream is None:
+        if _raw_stream is not None:  # the current stream's handle without a Stream object
+            return _raw_stream(torch.cuda.current_device())
         stream = torch.cuda.current_stream()
-    return C.c_void_p(stream.cuda_stream)
+    return stream.cuda_stream
 
 
 def _events(ev: torch.Tensor, n_obs: int):
+    """(address, n, ld) of an event tensor."""
     if not isinstance(ev, torch.Tensor) or not ev.is_cuda or ev.dtype != torch.float64:
         raise TypeError("events must be a float64 CUDA tensor")
     if ev.dim() == 1:
         ev = ev.unsqueeze(0)
-    if ev.dim() != 2 or ev.shape[0] != n_obs:
+    shape = ev.shape
+    if len(shape) != 2 or shape[0] != n_obs:
         raise ValueError(f"events must have shape ({n_obs}, n)")
-    n = ev.shape[1]
-    if n > 1 and ev.stride(1) != 1:
+    n = shape[1]
+    stride = ev.stride()
+    if n > 1 and stride[1] != 1:
         raise ValueError("events must be contiguous along the event axis")
-    ld = ev.stride(0) if n_obs > 1 else n
-    return C.c_void_p(ev.data_ptr() if n > 0 else 0), n, ld
+    return ev.data_ptr() if n > 0 else 0, n, stride[0] if n_obs > 1 else n
 
 
 @dataclass
@@ -82,6 +97,9 @@ class Model:
         self.n_params, self.n_obs, self.chunk = p.value, o.value, c.value
         self.events_per_thread = int(self.desc.get("events_per_thread", 1))
         self.tune_table = {}
+        # buffers of the evaluation call, set up once: theta in, value and gradient out
+        self._th, self._g, self._v = np.zeros(self.n_params), np.zeros(self.n_params), C.c_double()
+        self._th_c, self._g_c, self._v_ref = _cdbl(self._th), _cdbl(self._g), C.byref(self._v)
 
     def close(self):
         if getattr(self, "_h", None):
@@ -102,13 +120,14 @@ class Model:
 
     def nll(self, theta, events: torch.Tensor, grad: bool = False, stream=None):
         """NLL (and gradient as a numpy array when grad=True)."""
-        th, thp = self._theta(theta)
+        th = np.asarray(theta, dtype=np.float64)
+        if th.size != self.n_params:
+            raise ValueError(f"theta must have {self.n_params} entries")
+        self._th[:] = th.reshape(-1)
         evp, n, ld = _events(events, self.n_obs)
-        out = C.c_double()
-        g = np.zeros(self.n_params)
-        gp = g.ctypes.data_as(C.POINTER(C.c_double)) if grad else None
-        check(self._lib.fn_nll(self._h, thp, evp, n, ld, C.byref(out), gp, _stream_ptr(stream)))
-        return (out.value, g) if grad else out.value
+        check(self._lib.fn_nll(self._h, self._th_c, evp, n, ld, self._v_ref, self._g_c if grad else None,
+                               _stream_ptr(stream)))
+        return (self._v.value, self._g.copy()) if grad else self._v.value
 
     def nll_async(self, theta_dev: torch.Tensor, events: torch.Tensor, out_dev: torch.Tensor,
                   with_grad: bool = True, stream=None):
@@ -116,9 +135,8 @@ class Model:
         evp, n, ld = _events(events, self.n_obs)
         assert theta_dev.is_cuda and theta_dev.dtype == torch.float64 and theta_dev.numel() >= self.n_params
         assert out_dev.is_cuda and out_dev.dtype == torch.float64 and out_dev.numel() >= 1 + self.n_params
-        check(self._lib.fn_nll_async(self._h, C.c_void_p(theta_dev.data_ptr()), evp, n, ld,
-                                     C.c_void_p(out_dev.data_ptr()), 1 if with_grad else 0,
-                                     _stream_ptr(stream)))
+        check(self._lib.fn_nll_async(self._h, theta_dev.data_ptr(), evp, n, ld, out_dev.data_ptr(),
+                                     1 if with_grad else 0, _stream_ptr(stream)))
 
     def nll_async_noalloc(self, theta_dev: torch.Tensor, events: torch.Tensor, out_dev: torch.Tensor,
                           with_grad: bool = True, stream=None):
@@ -127,9 +145,8 @@ class Model:
         evp, n, ld = _events(events, self.n_obs)
         assert theta_dev.is_cuda and theta_dev.dtype == torch.float64 and theta_dev.numel() >= self.n_params
         assert out_dev.is_cuda and out_dev.dtype == torch.float64 and out_dev.numel() >= 1 + self.n_params
-        check(self._lib.fn_nll_async_noalloc(self._h, C.c_void_p(theta_dev.data_ptr()), evp, n, ld,
-                                             C.c_void_p(out_dev.data_ptr()), 1 if with_grad else 0,
-                                             _stream_ptr(stream)))
+        check(self._lib.fn_nll_async_noalloc(self._h, theta_dev.data_ptr(), evp, n, ld, out_dev.data_ptr(),
+                                             1 if with_grad else 0, _stream_ptr(stream)))
 
     def norm(self, theta, stream=None):
         """(I, dI/dtheta)."""
@@ -392,7 +409,7 @@ class Batch:
         lds = (C.c_int64 * max(F, 1))()
         for f, ev in enumerate(evs):
             p, n, ld = _events(ev, 1)
-            ptrs[f], ns[f], lds[f] = p.value, n, ld
+            ptrs[f], ns[f], lds[f] = p, n, ld
         torch.cuda.current_stream().synchronize()  # theta0_dev must be ready
         check(self._lib.fn_batch_set(self._h, F, ptrs, ns, lds,
                                      C.c_void_p(theta0_dev.data_ptr() if F > 0 else 0)))
