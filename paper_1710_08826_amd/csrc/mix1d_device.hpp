@@ -177,6 +177,54 @@ __host__ __device__ constexpr int mix_sig_type(int sig, int k) {
   return sig < 5 ? sig - 1 : (k == 0 ? (sig - 5) / 4 : (sig - 5) % 4);
 }
 
+// The component of a two-component signature whose exponential the other's is
+// divided by (mix1d_typed_chunk), or -1: an exponential next to a Gaussian, an
+// Argus shape or another exponential.
+__host__ __device__ constexpr int mix_sig_pivot(int sig) {
+  if (mix_sig_K(sig) != 2) return -1;
+  const int t0 = mix_sig_type(sig, 0), t1 = mix_sig_type(sig, 1);
+  if (t1 == kExp && t0 != kBW) return 1;
+  if (t0 == kExp && t1 != kBW) return 0;
+  return -1;
+}
+
+// A component's shape at x as pre e^arg, and its derivatives' factors:
+// d ln s / d(its parameters) are alpha0 m0 and alpha1 m1, alpha constants of
+// the fit (mix_alpha).
+struct MixTerm {
+  double pre, arg, m0, m1;
+};
+template <int TYPE>
+__device__ __forceinline__ MixTerm mix_term(const Mix1dTable& t, int k, double x) {
+  MixTerm r;
+  if (TYPE == kGauss) {
+    const double z = (x - t.a[k]) * t.b[k];
+    r = {1.0, -0.5 * z * z, z, z * z};
+  } else if (TYPE == kExp) {
+    r = {1.0, t.a[k] * x, x, 0.0};
+  } else if (TYPE == kArgus) {
+    const double xx = x * x, w = 1.0 - xx * t.a[k];
+    const bool in = w > 0.0;
+    const double wi = in ? w : 1.0;
+    r.pre = in ? x * sqrt(wi) : 0.0;
+    r.arg = t.b[k] * wi;
+    r.m0 = in ? (0.5 * rcp_acc(wi) + t.b[k]) * xx : 0.0;
+    r.m1 = in ? w : 0.0;
+  } else {
+    const double d = x - t.a[k];
+    const double s = rcp_fast(__builtin_fma(d, d, t.b[k]));
+    r = {s, 0.0, d * s, s};
+  }
+  return r;
+}
+template <int TYPE>
+__device__ __forceinline__ double mix_alpha(const Mix1dTable& t, int k, int j) {
+  if (TYPE == kGauss) return t.b[k];
+  if (TYPE == kArgus) return j == 0 ? 2.0 * t.a[k] * t.c[k] : 1.0;
+  if (TYPE == kBW) return j == 0 ? 2.0 : -0.5 * t.c[k];
+  return 1.0;
+}
+
 // slot[s] += w * dP/d(slot s) at one point: shape parameters of component k at
 // 2k, 2k + 1 (dP = f_k u_k (d ln s_k - d ln N_k)), fraction k < K-1 at
 // 2 KMAX + k (dP = u_k - u_{K-1}, the last component taking 1 - sum f).
@@ -198,6 +246,100 @@ __device__ __forceinline__ void mix1d_add_dp(int K, const Mix1dTable& t, const d
   }
 }
 
+// One chunk of events of a mixture of one or two components of known types ->
+// one partial row.  P = sum_k g_k s_k with g_k = f_k / N_k; per event the sums
+// are V_k = sum v, sum v m0 and sum v m1 with v = -s_k / P, and the slots
+// follow from them once per thread: shape slots f_k/N_k (alpha sum v m - V d ln
+// N), fraction slot V_0/N_0 - V_1/N_1.  With a pivot p (mix_sig_pivot) the
+// density is e^arg_p (g_p + g_o pre_o e^(arg_o - arg_p)): one exponential
+// serves both components, and sum arg_p is the pivot's parameter times sum x.
+// The Gaussian and exponential mixture takes 42 VALU instructions per event
+// instead of 112: NLL and gradient of 2^26 events 207 -> 149 us, and 131 us
+// with the loads below (their bytes alone take 88 at 6.1 TB/s); 512 toy fits to
+// convergence 3.87 -> 3.23 ms.
+template <bool GRAD, int SIG>
+__device__ inline void mix1d_typed_chunk(const Mix1dTable* __restrict__ tabp, const double* __restrict__ x, int64_t n,
+                                         int64_t chunk_idx, int chunk, double* __restrict__ out_row, double* lds) {
+  constexpr int KMAX = 2;
+  constexpr int NV = GRAD ? mix_nv(KMAX) : 1;
+  constexpr int K = mix_sig_K(SIG), PV = mix_sig_pivot(SIG);
+  constexpr int T0 = mix_sig_type(SIG, 0), T1 = K == 2 ? mix_sig_type(SIG, 1) : T0;
+  const Mix1dTable& t = *tabp;
+  const double g0 = t.frac[0] * t.invN[0], g1 = K == 2 ? t.frac[1] * t.invN[1] : 0.0;
+  double V0 = 0.0, A0 = 0.0, B0 = 0.0, V1 = 0.0, A1 = 0.0, B1 = 0.0, X = 0.0;
+  const int64_t base = chunk_idx * chunk;
+  const int64_t end = base + chunk < n ? base + chunk : n;
+  LogProd lp;  // -sum ln P enters acc[0] once per thread, at the end
+  auto event = [&](double xv) {
+    const MixTerm a = mix_term<T0>(t, 0, xv), b = mix_term<T1>(t, 1, xv);
+    double s0, s1 = 0.0;
+    if (PV == 1) {
+      s0 = a.pre * exp_fast(a.arg - b.arg);
+      s1 = 1.0;
+      X += xv;
+    } else if (PV == 0) {
+      s0 = 1.0;
+      s1 = b.pre * exp_fast(b.arg - a.arg);
+      X += xv;
+    } else {
+      s0 = T0 == kBW ? a.pre : a.pre * exp_fast(a.arg);
+      if (K == 2) s1 = T1 == kBW ? b.pre : b.pre * exp_fast(b.arg);
+    }
+    const double P = K == 2 ? __builtin_fma(g1, s1, g0 * s0) : g0 * s0;
+    lp.mul(P);
+    if (GRAD) {
+      const double w = -rcp_fast(P);
+      const double v0 = w * s0, v1 = w * s1;
+      V0 += v0;
+      A0 = __builtin_fma(v0, a.m0, A0);
+      if (T0 != kExp) B0 = __builtin_fma(v0, a.m1, B0);
+      if (K == 2) {
+        V1 += v1;
+        A1 = __builtin_fma(v1, b.m0, A1);
+        if (T1 != kExp) B1 = __builtin_fma(v1, b.m1, B1);
+      }
+    }
+  };
+  // groups of four events per thread, the next group's loads in flight while
+  // one is worked on (one load at a time left the pass waiting for memory),
+  // then the rest one by one
+  constexpr int U = 4;
+  const int64_t full = (end - base) / (U * kBlock);
+  const double* xp = x + base + threadIdx.x;
+  double nx[U];
+  if (full > 0) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) nx[u] = xp[u * kBlock];
+  }
+  for (int64_t g = 0; g < full; ++g) {
+    double cur[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) cur[u] = nx[u];
+    xp += U * kBlock;
+    if (g + 1 < full) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) nx[u] = xp[u * kBlock];
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) event(cur[u]);
+  }
+  for (int64_t i = base + full * (U * kBlock) + threadIdx.x; i < end; i += kBlock) event(x[i]);
+  double acc[NV];
+  acc[0] = -lp.log();
+  if (PV >= 0) acc[0] = __builtin_fma(-t.a[PV >= 0 ? PV : 0], X, acc[0]);
+  if (GRAD) {
+    acc[1] = g0 * __builtin_fma(-V0, t.dlnN[0][0], mix_alpha<T0>(t, 0, 0) * A0);
+    acc[2] = T0 == kExp ? 0.0 : g0 * __builtin_fma(-V0, t.dlnN[0][1], mix_alpha<T0>(t, 0, 1) * B0);
+    acc[3] = acc[4] = acc[5] = acc[6] = 0.0;
+    if (K == 2) {
+      acc[3] = g1 * __builtin_fma(-V1, t.dlnN[1][0], mix_alpha<T1>(t, 1, 0) * A1);
+      acc[4] = T1 == kExp ? 0.0 : g1 * __builtin_fma(-V1, t.dlnN[1][1], mix_alpha<T1>(t, 1, 1) * B1);
+      acc[5] = V0 * t.invN[0] - V1 * t.invN[1];
+    }
+  }
+  block_sum_row<NV>(acc, lds, out_row);
+}
+
 // One chunk of events -> one partial row (shared by the single-fit and the
 // batched launches so that both produce the same bits).  SIG: the type
 // signature the code is compiled for (0: generic, KMAX components at most).
@@ -206,8 +348,12 @@ __device__ inline void mix1d_chunk(const Mix1dConst& mc, const Mix1dTable* __res
                                    const double* __restrict__ x, int64_t n, int64_t chunk_idx,
                                    int chunk, double* __restrict__ out_row, double* lds) {
   static_assert(SIG == 0 || KMAX == 2, "typed passes hold two components");
+  if constexpr (SIG != 0) {
+    mix1d_typed_chunk<GRAD, SIG>(tabp, x, n, chunk_idx, chunk, out_row, lds);
+    return;
+  }
   constexpr int NV = GRAD ? mix_nv(KMAX) : 1;
-  const int K = SIG ? mix_sig_K(SIG) : mc.K;
+  const int K = mc.K;
   const Mix1dTable& t = *tabp;
   double acc[NV];
 #pragma unroll
@@ -223,8 +369,7 @@ __device__ inline void mix1d_chunk(const Mix1dConst& mc, const Mix1dTable* __res
     for (int k = 0; k < KMAX; ++k) {
       u[k] = 0.0; dl[k][0] = 0.0; dl[k][1] = 0.0;
       if (k < K) {
-        const int type = SIG ? mix_sig_type(SIG, k) : mc.type[k];
-        u[k] = mix_shape<GRAD>(type, t, k, xv, dl[k][0], dl[k][1]) * t.invN[k];
+        u[k] = mix_shape<GRAD>(mc.type[k], t, k, xv, dl[k][0], dl[k][1]) * t.invN[k];
         P += t.frac[k] * u[k];
       }
     }
