@@ -215,22 +215,57 @@ __global__ __launch_bounds__(kBlock) void rows_presum(const double* __restrict__
   if ((int)threadIdx.x < nv) (first ? o0 : o1)[bb * nv + threadIdx.x] = res[threadIdx.x];
 }
 
-// Level-2 of the M-row passes: rows i0..i0+3 of M (scaled by dA) into Mc.
-__global__ __launch_bounds__(kBlock) void dalitz_mrows_finalize(DalitzConst dc, const double* __restrict__ part,
-                                                                int64_t nrows, int nv, int kmax, int i0,
-                                                                double* __restrict__ Mc) {
-  __shared__ double scratch[kBlock];
-  __shared__ double res[kBlock];
-  sum_rows(part, nrows, nv, scratch, res);
-  const int K = dc.K;
-  for (int t = threadIdx.x; t < kMRowBlock * kmax; t += kBlock) {
-    const int ib = t / kmax, j = t - ib * kmax;
-    const int i = i0 + ib;
-    if (i < K && j < K) {
-      Mc[2 * (i * K + j)] = dc.dA * res[2 * t];
-      Mc[2 * (i * K + j) + 1] = dc.dA * res[2 * t + 1];
+// Level 2 of the matrix passes (gram_device.hpp): workgroup (b, f) adds
+// columns 32 b .. 32 b + 31 of fit f's rows (eight groups of threads each take
+// every eighth row in order, eight loads in flight; then the groups in order),
+// scales them and writes the matrix elements (i, j) and (j, i).
+//   kGramSquare  M (ldm x ldm complex)
+//   kGramMixing  of the 2K vector (A, B): MAA, MBB, MAB (K x K complex each, in this order)
+__global__ __launch_bounds__(kBlock) void gram_finalize(const double* __restrict__ part, int64_t rows, int C,
+                                                        int mode, int ldm, double scale,
+                                                        const int* __restrict__ sel, double* __restrict__ M,
+                                                        int64_t m_stride) {
+  __shared__ double s[8][32];
+  const int f = blockIdx.y;
+  if (sel && !sel[f]) return;
+  const int ncol = 2 * gram_count(C);
+  const int c = blockIdx.x * 32 + (threadIdx.x & 31), g = threadIdx.x >> 5;
+  const double* p = part + (int64_t)f * rows * ncol + (c < ncol ? c : 0);
+  double a = 0.0;
+  for (int64_t r = g; r < rows; r += 64) {
+    double x[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      x[u] = 0.0;
+      if (r + 8 * u < rows) x[u] = p[(r + 8 * u) * ncol];
     }
+#pragma unroll
+    for (int u = 0; u < 8; ++u) a += x[u];
   }
+  s[g][threadIdx.x & 31] = a;
+  __syncthreads();
+  if (g != 0 || c >= ncol) return;
+  for (int u = 1; u < 8; ++u) a += s[u][threadIdx.x];
+  a *= scale;
+  const int e = c >> 1, im = c & 1;
+  int i = 0;
+  while (gram_index(i + 1, 0) <= e) ++i;
+  const int j = e - gram_index(i, 0);
+  double* out = M + f * m_stride;
+  if (mode == kGramMixing) {
+    const int K = C / 2, nn = 2 * K * K;
+    if (i >= K && j < K) {
+      out[2 * nn + 2 * (j * K + i - K) + im] = a;
+      return;
+    }
+    if (i >= K) out += nn;
+    const int ii = i >= K ? i - K : i, jj = i >= K ? j - K : j;
+    out[2 * (ii * K + jj) + im] = a;
+    if (i != j) out[2 * (jj * K + ii) + im] = im ? -a : a;
+    return;
+  }
+  out[2 * (i * ldm + j) + im] = a;
+  if (i != j) out[2 * (j * ldm + i) + im] = im ? -a : a;
 }
 
 // P~(x_i)/I per event (I read from the finalize output).
@@ -341,7 +376,16 @@ int64_t dalitz_build_grid_cells(const DalitzConst& dc, DevBuf& cells, hipStream_
 
 int dalitz_kmax(int K) { return K; }  // partial rows hold exactly the model's resonances
 int dalitz_nv_events(int kmax, int grad) { return dal_nv(kEvents, grad, kmax); }
-int dalitz_nv_mrows(int kmax) { return dal_nv(kMRows, 0, kmax); }
+int gram_chunk(int64_t n) {
+  const int64_t c = ((n + kGramRows - 1) / kGramRows + kBlock - 1) / kBlock * kBlock;
+  return (int)std::min<int64_t>(std::max<int64_t>(c, kBlock), int64_t(1) << 30);
+}
+
+void launch_gram_finalize(const double* part, int64_t rows, int C, int mode, int ldm, double scale, int n_fits,
+                          const int* sel, double* M, int64_t m_stride, hipStream_t s) {
+  hipLaunchKernelGGL(gram_finalize, dim3((unsigned)((2 * gram_count(C) + 31) / 32), (unsigned)n_fits), dim3(kBlock), 0,
+                     s, part, rows, C, mode, ldm, scale, sel, M, m_stride);
+}
 
 void dalitz_launch_prologue(const DalitzConst& dc, const ParamBlock& pb, const double* theta_dev,
                             const double* fixed_ls, int n_fits, int theta_stride, DalitzTable* tab, hipStream_t s) {
@@ -374,7 +418,7 @@ std::string dalitz_jit_source(const DalitzConst& dc, int ept) {
   if (!dc.free_ls) {
     o << "FN_DALITZ_KERNEL(fn_dal_ev0, fn_shape, fn::kEvents, 0, 1)\n"
          "FN_DALITZ_KERNEL(fn_dal_ev1, fn_shape, fn::kEvents, 1, 1)\n"
-         "FN_DALITZ_KERNEL(fn_dal_mrows, fn_shape, fn::kMRows, 0, 1)\n";
+         "FN_DALITZ_GRAM(fn_dal_gram, fn_shape)\n";
   } else {
     o << "FN_DALITZ_KERNEL(fn_dal_ev0, fn_shape, fn::kEvents, 0, 1)\n"
          "FN_DALITZ_KERNEL(fn_dal_ev2, fn_shape, fn::kEvents, 2, 1)\n"
@@ -395,7 +439,7 @@ std::shared_ptr<DalitzJit> dalitz_jit(const DalitzConst& dc, int ept) {
     j->ev[dc.free_ls ? 2 : 1] = j->prog->fns[1];
     return j;
   }
-  if (!dc.free_ls) names = {"fn_dal_ev0", "fn_dal_ev1", "fn_dal_mrows"};
+  if (!dc.free_ls) names = {"fn_dal_ev0", "fn_dal_ev1", "fn_dal_gram"};
   else names = {"fn_dal_ev0", "fn_dal_ev2", "fn_dal_gr0", "fn_dal_gr2"};
   const size_t ngen = names.size();
   names.push_back("fn_dal_gmax");
@@ -405,7 +449,7 @@ std::shared_ptr<DalitzJit> dalitz_jit(const DalitzConst& dc, int ept) {
   if (!dc.free_ls) {
     j->ev[0] = f[0];
     j->ev[1] = f[1];
-    j->mrows = f[2];
+    j->gram = f[2];
   } else {
     j->ev[0] = f[0];
     j->ev[2] = f[1];
@@ -418,7 +462,7 @@ std::shared_ptr<DalitzJit> dalitz_jit(const DalitzConst& dc, int ept) {
 }
 
 static void launch_pass(hipFunction_t f, const DalitzConst& dc, const DalitzTable* tab, const double* coef,
-                        const CoefArg& ca, const double* ev, int64_t ld, int64_t n, int chunk, int64_t nchunks, int i0, double* part,
+                        const CoefArg& ca, const double* ev, int64_t ld, int64_t n, int chunk, int64_t nchunks, double* part,
                         hipStream_t s, const double* Mc = nullptr, double* norm_out = nullptr,
                         hipEvent_t start = nullptr, hipEvent_t stop = nullptr,
                         unsigned long long* span = nullptr) {
@@ -429,12 +473,12 @@ static void launch_pass(hipFunction_t f, const DalitzConst& dc, const DalitzTabl
   CoefArg a = ca;
   const double* e = ev;
   int64_t l = ld, nn = n;
-  int ch = chunk, ii = i0;
+  int ch = chunk;
   double* p = part;
   const double* m = Mc;
   double* no = norm_out;
   unsigned long long* sp = span;
-  void* args[] = {&c, &t, &cf, &a, &e, &l, &nn, &ch, &ii, &p, &m, &no, &sp};
+  void* args[] = {&c, &t, &cf, &a, &e, &l, &nn, &ch, &p, &m, &no, &sp};
   jit_launch(f, (unsigned)nchunks, kBlock, s, args, start, stop);
 }
 
@@ -462,7 +506,7 @@ void dalitz_launch_events(const DalitzJit& j, const DalitzConst& dc, const Dalit
                           unsigned long long* span) {
   if (nchunks == 0) return;
   const int P = dc.free_ls ? 4 * dc.K : 2 * dc.K;
-  launch_pass(j.ev[grad], dc, tab, coef, ca, ev, ld, n, chunk, nchunks, 0, part, s, Mc,
+  launch_pass(j.ev[grad], dc, tab, coef, ca, ev, ld, n, chunk, nchunks, part, s, Mc,
               Mc && out ? out + 1 + P : nullptr, start, stop, span);
 }
 
@@ -511,22 +555,20 @@ void dalitz_launch_finalize(const DalitzConst& dc, const DalitzTable* tab, const
 void dalitz_launch_grid(const DalitzJit& j, const DalitzConst& dc, const DalitzTable* tab, const double* coef,
                         const GridCell* cells, int64_t n_inside, int chunk, int64_t nchunks, int grad, double* part,
                         hipStream_t s) {
-  launch_pass(j.gr[grad], dc, tab, coef, CoefArg{}, reinterpret_cast<const double*>(cells), 0, n_inside, chunk, nchunks, 0,
+  launch_pass(j.gr[grad], dc, tab, coef, CoefArg{}, reinterpret_cast<const double*>(cells), 0, n_inside, chunk, nchunks,
               part, s);
 }
 
-void dalitz_launch_mrows(const DalitzJit& j, const DalitzConst& dc, const DalitzTable* tab, int chunk,
-                         int64_t nchunks, int i0, double* part, double* Mc, hipStream_t s) {
-  const int64_t ncell = (int64_t)dc.nx * dc.ny;
-  launch_pass(j.mrows, dc, tab, nullptr, CoefArg{}, nullptr, 0, ncell, chunk, nchunks, i0, part, s);
-  dalitz_launch_mrows_finalize(dc, part, nchunks, i0, Mc, s);
-}
-
-void dalitz_launch_mrows_finalize(const DalitzConst& dc, const double* part, int64_t nchunks, int i0, double* Mc,
-                                  hipStream_t s) {
-  const int kmax = dalitz_kmax(dc.K);
-  hipLaunchKernelGGL(dalitz_mrows_finalize, dim3(1), dim3(kBlock), 0, s, dc, part, nchunks,
-                     dal_nv(kMRows, 0, kmax), kmax, i0, Mc);
+void dalitz_launch_gram(const DalitzJit& j, const DalitzConst& dc, const DalitzTable* tab, int chunk, int64_t rows,
+                        double* part, double* Mc, hipStream_t s) {
+  if (!j.gram) throw Error(FN_E_INVALID, "this model was not compiled with the requested pass");
+  DalitzConst c = dc;
+  const DalitzTable* t = tab;
+  int ch = chunk;
+  double* p = part;
+  void* args[] = {&c, &t, &ch, &p};
+  jit_launch(j.gram, (unsigned)rows, kBlock, s, args);
+  launch_gram_finalize(part, rows, dc.K, kGramSquare, dc.K, dc.dA, 1, nullptr, Mc, 0, s);
 }
 
 void dalitz_launch_gridmax(const DalitzJit& j, const DalitzConst& dc, const DalitzTable* tab,

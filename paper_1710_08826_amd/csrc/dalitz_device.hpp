@@ -27,20 +27,21 @@
 // Modes of the chunk routine:
 //   kEvents  -ln P~ over an event chunk (+ adjoint gradient)          -> NLL
 //   kGrid    P~ over a chunk of grid cells inside the region (+ dP~)  -> I
-//   kMRows   rows i0..i0+3 of sum_cells A_i conj(A_j)                 -> cached M
+// and a matrix pass: sum over the cells inside the region of A_i conj(A_j)
+// (gram_device.hpp), the cached M of fixed lineshapes.
 #pragma once
 #include "device_common.hpp"
 #include "fastmath.hpp"
+#include "gram_device.hpp"
 #include "model.hpp"
 #include "philox.hpp"
 
 namespace fn {
 
-enum DalMode : int { kEvents = 0, kGrid = 1, kMRows = 2 };
-constexpr int kMRowBlock = 4;
+enum DalMode : int { kEvents = 0, kGrid = 1 };
 
 __host__ __device__ constexpr int dal_nv(int mode, int grad, int k) {
-  return mode == kMRows ? 2 * kMRowBlock * k : 1 + (grad == 0 ? 0 : (grad == 1 ? 2 * k : 4 * k));
+  return 1 + (grad == 0 ? 0 : (grad == 1 ? 2 * k : 4 * k));
 }
 
 struct PairTerms {
@@ -194,8 +195,8 @@ __device__ __forceinline__ void dalitz_pair_terms(const DalitzConst& dc, double 
 }
 
 // Amplitudes of all resonances (in model order, four at a time for the
-// reciprocals), added to the coherent sum S = sum_k c_k A_k.
-template <class S, int MODE, bool KEEP_A, bool KEEP_T>
+// reciprocals), added to the coherent sum S = sum_k c_k A_k (SUM).
+template <class S, bool KEEP_A, bool KEEP_T, bool SUM = true>
 __device__ __forceinline__ void dalitz_amps(const DalitzConst& dc, const double* __restrict__ r,
                                             cdouble* __restrict__ coef, double s12, double s13, double s23,
                                             double (&Are)[S::K], double (&Aim)[S::K], double (&Tre)[S::K],
@@ -232,7 +233,7 @@ __device__ __forceinline__ void dalitz_amps(const DalitzConst& dc, const double*
         bw_amplitude(rk, pt.H[L], a[j], b[j], D[j], ar, ai);
         if (KEEP_A) { Are[k] = ar; Aim[k] = ai; }
         if (KEEP_T) { Tre[k] = a[j] * D[j]; Tim[k] = b[j] * D[j]; Gk[k] = pt.G[L]; }
-        if (MODE != kMRows) {
+        if (SUM) {
           // S += c_k A_k as four chained FMAs
           const double cr = coef[2 * k], ci = coef[2 * k + 1];
           Sre = __builtin_fma(cr, ar, __builtin_fma(-ci, ai, Sre));
@@ -248,36 +249,20 @@ __device__ __forceinline__ void dalitz_amps(const DalitzConst& dc, const double*
 template <class S, int MODE, int GRAD>
 __device__ __forceinline__ void dalitz_point(const DalitzConst& dc, const double* __restrict__ r,
                                              cdouble* __restrict__ coef, double s12, double s13, bool valid,
-                                             int i0, double (&acc)[dal_nv(MODE, GRAD, S::K)], LogProd& lp) {
+                                             double (&acc)[dal_nv(MODE, GRAD, S::K)], LogProd& lp) {
   constexpr int K = S::K;
-  constexpr bool KEEP_A = (GRAD >= 1) || MODE == kMRows;
+  constexpr bool KEEP_A = GRAD >= 1;
   constexpr bool KEEP_T = GRAD == 2;
   const double s23 = dc.msum - s12 - s13;
   double Are[K], Aim[K], Tre[K], Tim[K], Gk[K];
   double Sre = 0.0, Sim = 0.0;
-  dalitz_amps<S, MODE, KEEP_A, KEEP_T>(dc, r, coef, s12, s13, s23, Are, Aim, Tre, Tim, Gk, Sre, Sim);
+  dalitz_amps<S, KEEP_A, KEEP_T>(dc, r, coef, s12, s13, s23, Are, Aim, Tre, Tim, Gk, Sre, Sim);
   auto add = [&](int idx, double v) { acc[idx] += valid ? v : 0.0; };
   // acc[idx] += x1 y1 + x2 y2 as two chained FMAs
   auto add2 = [&](int idx, double x1, double y1, double x2, double y2) {
     const double t = __builtin_fma(x2, y2, __builtin_fma(x1, y1, acc[idx]));
     acc[idx] = valid ? t : acc[idx];
   };
-  if (MODE == kMRows) {
-#pragma unroll
-    for (int ib = 0; ib < kMRowBlock; ++ib) {
-      // A_i for i = i0 + ib, selected from registers with uniform guards
-      double xr = 0.0, xi = 0.0;
-#pragma unroll
-      for (int k = 0; k < K; ++k)
-        if (k == i0 + ib) { xr = Are[k]; xi = Aim[k]; }
-#pragma unroll
-      for (int j = 0; j < K; ++j) {
-        add2(2 * (ib * K + j), xr, Are[j], xi, Aim[j]);
-        add2(2 * (ib * K + j) + 1, xi, Are[j], -xr, Aim[j]);
-      }
-    }
-    return;
-  }
   const double Pt = __builtin_fma(Sre, Sre, Sim * Sim);
   double w;  // multiplies dP~/dtheta
   if (MODE == kEvents) {
@@ -328,11 +313,11 @@ __device__ __forceinline__ void dalitz_point(const DalitzConst& dc, const double
 // scheduler to interleave); each thread still adds its points in index order.
 // Two per iteration measured slower than one for the eight-resonance model on
 // MI355X (more VGPRs); the events passes come in both forms and the
-// autotuner times them, the grid and matrix-row passes use one.
+// autotuner times them, the grid passes use one.
 template <class S, int MODE, int GRAD, int EPT = 1>
 __device__ inline void dalitz_chunk(const DalitzConst& dc, const DalitzTable* __restrict__ tab,
                                     cdouble* __restrict__ coef0, const double* __restrict__ ev, int64_t ld,
-                                    int64_t n, int64_t chunk_idx, int chunk, int i0, double* __restrict__ out_row,
+                                    int64_t n, int64_t chunk_idx, int chunk, double* __restrict__ out_row,
                                     double* lds) {
   constexpr int NV = dal_nv(MODE, GRAD, S::K);
   double acc[NV];
@@ -342,16 +327,6 @@ __device__ inline void dalitz_chunk(const DalitzConst& dc, const DalitzTable* __
   const int64_t end = base + chunk < n ? base + chunk : n;
   const double* const r0 = &tab->r[0][0];
   LogProd lp;
-  // matrix-row passes over the whole grid, one cell per thread and
-  // iteration: the cell's (ix, iy) advanced by kBlock cells per iteration
-  // instead of a 64-bit division, and the region's bounds computed once per
-  // grid column
-  int64_t gx = 0, gy = 0, row_ix = -1;
-  double row_lo = 0.0, row_hi = 0.0;
-  if (MODE == kMRows && EPT == 1) {
-    gx = (base + threadIdx.x) / dc.ny;
-    gy = (base + threadIdx.x) - gx * dc.ny;
-  }
   for (int64_t i = base + threadIdx.x; i < end; i += EPT * kBlock) {
     // The per-resonance constants are read through the scalar cache on every
     // event: an empty asm makes a zero offset opaque to the loop so that the
@@ -365,39 +340,19 @@ __device__ inline void dalitz_chunk(const DalitzConst& dc, const DalitzTable* __
 #pragma unroll
     for (int e = 0; e < EPT; ++e) {
       const int64_t j = i + e * kBlock;
-      bool valid = e == 0 || j < end;
+      const bool valid = e == 0 || j < end;
       const int64_t jj = valid ? j : i;  // a valid index; its terms are masked out
       double s12, s13;
       if (MODE == kEvents) {
         s12 = ev[jj];
         s13 = ev[ld + jj];
-      } else if (MODE == kGrid) {
+      } else {
         // grid passes walk the list of the cells inside the region (ev)
         const GridCell g = reinterpret_cast<const GridCell*>(ev)[jj];
         s12 = grid_centre(dc.a12, g.ix, dc.d12);
         s13 = grid_centre(dc.a13, g.iy, dc.d13);
-      } else if (EPT == 1) {
-        const int64_t ix = gx, iy = gy;
-        gy += kBlock;
-        while (gy >= dc.ny) {
-          gy -= dc.ny;
-          ++gx;
-        }
-        s12 = grid_centre(dc.a12, ix, dc.d12);
-        s13 = grid_centre(dc.a13, iy, dc.d13);
-        if (ix != row_ix) {
-          dalitz_row_bounds(dc, s12, row_lo, row_hi);
-          row_ix = ix;
-        }
-        if (!dalitz_in_row(dc, s12, s13, row_lo, row_hi)) continue;
-      } else {
-        const int64_t ix = jj / dc.ny;
-        const int64_t iy = jj - ix * dc.ny;
-        s12 = grid_centre(dc.a12, ix, dc.d12);
-        s13 = grid_centre(dc.a13, iy, dc.d13);
-        valid = valid && dalitz_inside(dc, s12, s13);
       }
-      dalitz_point<S, MODE, GRAD>(dc, r, coef, s12, s13, valid, i0, acc, lp);
+      dalitz_point<S, MODE, GRAD>(dc, r, coef, s12, s13, valid, acc, lp);
     }
   }
   if (MODE == kEvents) acc[0] = -lp.log();
@@ -440,7 +395,7 @@ __device__ inline void dalitz_cached_norm(const double* __restrict__ M, cdouble*
 // One workgroup per chunk, one row of NV partial sums each.
 // coef: (Re c_k, Im c_k) of the resonances (theta's first 2K entries, the
 // launch's own arguments, or the
-// table's copy of them); unused by kMRows.  Events pass with a cached grid
+// table's copy of them).  Events pass with a cached grid
 // matrix (M not null): the last workgroup, whose chunk is the shortest,
 // also evaluates the normalization into norm_out (dalitz_cached_norm), so
 // that the level-2 step only sums rows.  span: the launch's span record
@@ -448,16 +403,58 @@ __device__ inline void dalitz_cached_norm(const double* __restrict__ M, cdouble*
 template <class S, int MODE, int GRAD, int EPT = 1>
 __device__ inline void dalitz_pass_body(const DalitzConst& dc, const DalitzTable* __restrict__ tab,
                                         cdouble* __restrict__ coef, const double* __restrict__ ev, int64_t ld,
-                                        int64_t n, int chunk, int i0, double* __restrict__ part,
+                                        int64_t n, int chunk, double* __restrict__ part,
                                         const double* __restrict__ M, double* __restrict__ norm_out,
                                         unsigned long long* __restrict__ span) {
   constexpr int NV = dal_nv(MODE, GRAD, S::K);
   __shared__ double lds[block_sum_lds(NV)];
   if (span) span_begin(span);
-  dalitz_chunk<S, MODE, GRAD, EPT>(dc, tab, coef, ev, ld, n, blockIdx.x, chunk, i0,
+  dalitz_chunk<S, MODE, GRAD, EPT>(dc, tab, coef, ev, ld, n, blockIdx.x, chunk,
                                    part + (int64_t)blockIdx.x * NV, lds);
   if (MODE == kEvents && M && blockIdx.x == gridDim.x - 1) dalitz_cached_norm<S>(M, coef, norm_out);
   if (span) span_end(span);
+}
+
+// Grid cell c (column-major over the whole grid, nx ny < 2^30): its centre and
+// whether it lies inside the region.
+__device__ __forceinline__ bool dalitz_cell(const DalitzConst& dc, uint32_t c, double& s12, double& s13) {
+  const uint32_t ix = c / (uint32_t)dc.ny;
+  s12 = grid_centre(dc.a12, ix, dc.d12);
+  s13 = grid_centre(dc.a13, c - ix * (uint32_t)dc.ny, dc.d13);
+  return dalitz_inside(dc, s12, s13);
+}
+
+// One workgroup per chunk of grid cells, one row of sum A_i conj(A_j) each
+// (Gram); a wave whose 64 cells all lie outside the region skips them.
+template <class S>
+__device__ inline void dalitz_gram_body(const DalitzConst& dc, const DalitzTable* __restrict__ tab, int chunk,
+                                        double* __restrict__ part) {
+  constexpr int K = S::K;
+  using G = Gram<K>;
+  __shared__ double lds[G::LDS];
+  G g;
+  g.init(lds);
+  const uint32_t ncell = (uint32_t)dc.nx * (uint32_t)dc.ny;
+  const uint32_t base = blockIdx.x * (uint32_t)chunk;
+  const uint32_t end = base + chunk < ncell ? base + chunk : ncell;
+  const double* const r0 = &tab->r[0][0];
+  for (uint32_t i = base + (threadIdx.x & ~63u); i < end; i += kBlock) {
+    const uint32_t c = i + (threadIdx.x & 63u);
+    double s12, s13;
+    const bool in = dalitz_cell(dc, c < end ? c : i, s12, s13) && c < end;
+    if (!__any(in)) continue;
+    int zero = 0;
+    asm volatile("" : "+s"(zero));
+    double Are[K], Aim[K], Tre[K], Tim[K], Gk[K], Sre = 0.0, Sim = 0.0;
+    dalitz_amps<S, true, false, false>(dc, r0 + zero, (cdouble*)nullptr, s12, s13, dc.msum - s12 - s13, Are, Aim, Tre,
+                                       Tim, Gk, Sre, Sim);
+    if (!in) {
+#pragma unroll
+      for (int k = 0; k < K; ++k) Are[k] = Aim[k] = 0.0;
+    }
+    g.add(Are, Aim, lds);
+  }
+  g.reduce(lds, part + (int64_t)blockIdx.x * 2 * gram_count(K));
 }
 
 // ---------------------------------------------------------------- toy events
@@ -469,7 +466,7 @@ __device__ __forceinline__ double dalitz_value(const DalitzConst& dc, const doub
   const double s23 = dc.msum - s12 - s13;
   double Are[K], Aim[K], Tre[K], Tim[K], Gk[K];
   double Sre = 0.0, Sim = 0.0;
-  dalitz_amps<S, kGrid, false, false>(dc, r, coef, s12, s13, s23, Are, Aim, Tre, Tim, Gk, Sre, Sim);
+  dalitz_amps<S, false, false>(dc, r, coef, s12, s13, s23, Are, Aim, Tre, Tim, Gk, Sre, Sim);
   return __builtin_fma(Sre, Sre, Sim * Sim);
 }
 
@@ -546,11 +543,18 @@ __device__ inline void dalitz_gen_body(const DalitzConst& dc, const DalitzTable*
 #define FN_DALITZ_KERNEL(NAME, S, MODE, GRAD, EPT)                                                           \
   extern "C" __global__ __launch_bounds__(fn::kBlock) void NAME(                                               \
       fn::DalitzConst dc, const fn::DalitzTable* __restrict__ tab, const double* __restrict__ coef,           \
-      fn::CoefArg ca, const double* __restrict__ ev, int64_t ld, int64_t n, int chunk, int i0,                 \
+      fn::CoefArg ca, const double* __restrict__ ev, int64_t ld, int64_t n, int chunk,                         \
       double* __restrict__ part, const double* __restrict__ M, double* __restrict__ norm_out,                  \
       unsigned long long* __restrict__ span) {                                                                 \
     fn::cdouble* c = coef ? (fn::cdouble*)coef : (fn::cdouble*)&ca.v[0];                                       \
-    fn::dalitz_pass_body<S, MODE, GRAD, EPT>(dc, tab, c, ev, ld, n, chunk, i0, part, M, norm_out, span);       \
+    fn::dalitz_pass_body<S, MODE, GRAD, EPT>(dc, tab, c, ev, ld, n, chunk, part, M, norm_out, span);       \
+  }
+
+// Matrix pass for shape S.
+#define FN_DALITZ_GRAM(NAME, S)                                                                               \
+  extern "C" __global__ __launch_bounds__(fn::kBlock) void NAME(                                               \
+      fn::DalitzConst dc, const fn::DalitzTable* __restrict__ tab, int chunk, double* __restrict__ part) {     \
+    fn::dalitz_gram_body<S>(dc, tab, chunk, part);                                                             \
   }
 
 // Grid maximum and accept-reject generator for shape S.

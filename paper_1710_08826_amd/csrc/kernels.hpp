@@ -45,7 +45,7 @@ struct DalitzJit {
   std::shared_ptr<JitProgram> prog;
   hipFunction_t ev[3] = {nullptr, nullptr, nullptr};  // by gradient level
   hipFunction_t gr[3] = {nullptr, nullptr, nullptr};
-  hipFunction_t mrows = nullptr;
+  hipFunction_t gram = nullptr;                 // normalization matrix of fixed lineshapes
   hipFunction_t gmax = nullptr, gen = nullptr;  // toy generation: grid maximum, accept-reject
 };
 // ept: events per thread and loop iteration of the events passes (1, or 2
@@ -54,7 +54,14 @@ std::string dalitz_jit_source(const DalitzConst& dc, int ept = 1);
 std::shared_ptr<DalitzJit> dalitz_jit(const DalitzConst& dc, int ept = 1);
 int dalitz_kmax(int K);
 int dalitz_nv_events(int kmax, int grad);
-int dalitz_nv_mrows(int kmax);
+// Matrix passes (gram_device.hpp): points per workgroup for n of them (at most
+// kGramRows workgroups per fit, two per compute unit: one row each), and the
+// level-2 step over `rows` rows per fit, see gram_finalize.
+constexpr int kGramRows = 512;
+enum GramMode : int { kGramSquare = 0, kGramMixing = 1 };
+int gram_chunk(int64_t n);
+void launch_gram_finalize(const double* part, int64_t rows, int C, int mode, int ldm, double scale, int n_fits,
+                          const int* sel, double* M, int64_t m_stride, hipStream_t s);
 void dalitz_launch_prologue(const DalitzConst& dc, const ParamBlock& pb, const double* theta_dev,
                             const double* fixed_ls, int n_fits, int theta_stride, DalitzTable* tab, hipStream_t s);
 // Events pass: one row of partial sums per chunk of events.
@@ -93,12 +100,10 @@ int64_t dalitz_build_grid_cells(const DalitzConst& dc, DevBuf& cells, hipStream_
 void dalitz_launch_grid(const DalitzJit& j, const DalitzConst& dc, const DalitzTable* tab, const double* coef,
                         const GridCell* cells, int64_t n_inside, int chunk, int64_t nchunks, int grad, double* part,
                         hipStream_t s);
-// Level-2 of a row-block pass of K x K matrices (rows i0..i0+3, 2 K doubles
-// each per chunk row) into Mc, scaled by the cell area.
-void dalitz_launch_mrows_finalize(const DalitzConst& dc, const double* part, int64_t nchunks, int i0, double* Mc,
-                                  hipStream_t s);
-void dalitz_launch_mrows(const DalitzJit& j, const DalitzConst& dc, const DalitzTable* tab, int chunk,
-                         int64_t nchunks, int i0, double* part, double* Mc, hipStream_t s);
+// Normalization matrix Mc (K x K complex) of a model with fixed lineshapes
+// from all grid cells; part holds rows (= ceil(cells / chunk)) x K (K + 1) doubles.
+void dalitz_launch_gram(const DalitzJit& j, const DalitzConst& dc, const DalitzTable* tab, int chunk, int64_t rows,
+                        double* part, double* Mc, hipStream_t s);
 // Toy events: vmax (zeroed by the caller) receives the bits of the largest P~
 // over the grid cells inside the region; the generator writes n events (SoA,
 // leading dimension ld) by accept-reject under envelope W from the box

@@ -505,10 +505,8 @@ void run_nll(fn_model* m, const ParamBlock* pb, const double* theta_dev, const d
     TddpArg ca{};
     if (pb) std::memcpy(ca.v, pb->v, sizeof(double) * m->P);
     if (!m->M_valid) {
-      const int64_t ncell = (int64_t)dc.nx * dc.ny;
-      const int64_t mrows = nchunks_for(ncell, m->grid_chunk);
-      norm_rows((size_t)mrows * 2 * kMRowBlock * dc.K);
-      tddp_launch_mmatrices(*m->tddp_jit, dc, m->table_dal(), m->grid_chunk, npart, m->Mc(), s);
+      norm_rows(tddp_gram_doubles(dc));
+      tddp_launch_mmatrices(*m->tddp_jit, dc, m->table_dal(), npart, m->Mc(), s);
       m->M_valid = true;
     }
     m->timed(launches, [&](hipEvent_t t0, hipEvent_t t1) {
@@ -529,11 +527,8 @@ void run_nll(fn_model* m, const ParamBlock* pb, const double* theta_dev, const d
     const Td4FitConst* fc = (const Td4FitConst*)m->d_fixed.ptr;
     td4_launch_prologue(tc, pb, theta_dev, m->P, fc, nullptr, 1, m->table_td4(), s);
     if (!m->M_valid) {
-      const int mchunk = 1024;
-      const int64_t mrows = nchunks_for(m->n_mc, mchunk);
-      norm_rows((size_t)mrows * 2 * td4_row_block(tc.K) * kmax);
-      td4_launch_mmatrix(*m->td4_jit, tc, m->table_td4(), 1, (const double*)m->d_mc.ptr, m->n_mc, m->n_mc, mchunk,
-                         npart,
+      norm_rows(td4_gram_doubles(tc, m->n_mc));
+      td4_launch_mmatrix(*m->td4_jit, tc, m->table_td4(), 1, (const double*)m->d_mc.ptr, m->n_mc, m->n_mc, npart,
                          m->Mc(), s);
       m->M_valid = true;
     }
@@ -589,10 +584,10 @@ void run_nll(fn_model* m, const ParamBlock* pb, const double* theta_dev, const d
     } else if (!m->M_valid) {
       // fixed lineshapes: reduce the grid once to M_ij = dA sum A_i conj(A_j)
       const int64_t ncell = (int64_t)dc.nx * dc.ny;
-      const int64_t mrows = nchunks_for(ncell, m->grid_chunk);
-      norm_rows((size_t)mrows * dalitz_nv_mrows(kmax));
-      for (int i0 = 0; i0 < dc.K; i0 += 4)
-        dalitz_launch_mrows(*m->dal_jit, dc, m->table_dal(), m->grid_chunk, mrows, i0, npart, m->Mc(), s);
+      const int gchunk = gram_chunk(ncell);
+      const int64_t mrows = nchunks_for(ncell, gchunk);
+      norm_rows((size_t)mrows * dc.K * (dc.K + 1));
+      dalitz_launch_gram(*m->dal_jit, dc, m->table_dal(), gchunk, mrows, npart, m->Mc(), s);
       m->M_valid = true;
     }
     // cached M: the events pass evaluates I = c^H M c in its last workgroup

@@ -12,6 +12,7 @@
 
 #include "internal.hpp"
 #include "jit.hpp"
+#include "kernels.hpp"
 #include "td4.hpp"
 #include "td4_device.hpp"
 
@@ -138,28 +139,6 @@ __global__ __launch_bounds__(kTd4PrologueThreads) void td4_prologue(Td4Const tc,
   }
   const bool bad = __syncthreads_or(!ok);
   if (j == 0) t.valid = bad ? 0.0 : 1.0;
-}
-
-// ---------------------------------------------------- normalization matrix
-__global__ __launch_bounds__(kFinalBlock) void td4_mrows_finalize(Td4Const tc, const int* __restrict__ sel,
-                                                                  const double* __restrict__ part, int64_t nch,
-                                                                  int nv, int kmax, int i0, int rb, double inv_n,
-                                                                  double* __restrict__ Mc) {
-  __shared__ double scratch[kFinalBlock];
-  __shared__ double res[kBlock];
-  const int f = blockIdx.x;
-  if (sel && !sel[f]) return;
-  sum_rows_t<kFinalBlock>(part + (int64_t)f * nch * nv, nch, nv, scratch, res);
-  const int K = tc.K;
-  double* M = Mc + (int64_t)f * 2 * kTd4MaxAmp * kTd4MaxAmp;
-  for (int t = threadIdx.x; t < rb * kmax; t += kFinalBlock) {
-    const int ib = t / kmax, j = t - ib * kmax;
-    const int i = i0 + ib;
-    if (i < K && j < K) {
-      M[2 * (i * kTd4MaxAmp + j)] = inv_n * res[2 * t];
-      M[2 * (i * kTd4MaxAmp + j) + 1] = inv_n * res[2 * t + 1];
-    }
-  }
 }
 
 // ---------------------------------------------------------------- finalize
@@ -399,42 +378,42 @@ std::string td4_jit_source(const Td4Const& tc) {
   o << "};\n"
        "FN_TD4_EVENTS(fn_td4_ev0, fn_td4_shape, false)\n"
        "FN_TD4_EVENTS(fn_td4_ev1, fn_td4_shape, true)\n"
-       "FN_TD4_MROWS(fn_td4_mrows, fn_td4_shape)\n"
+       "FN_TD4_GRAM(fn_td4_gram, fn_td4_shape)\n"
        "FN_TD4_GEN(fn_td4_envmax, fn_td4_gen, fn_td4_shape)\n";
   return o.str();
 }
 
 std::shared_ptr<Td4Jit> td4_jit(const Td4Const& tc) {
   auto j = std::make_shared<Td4Jit>();
-  j->prog = jit_load(td4_jit_source(tc), {"fn_td4_ev0", "fn_td4_ev1", "fn_td4_mrows", "fn_td4_envmax", "fn_td4_gen"});
+  j->prog = jit_load(td4_jit_source(tc), {"fn_td4_ev0", "fn_td4_ev1", "fn_td4_gram", "fn_td4_envmax", "fn_td4_gen"});
   j->ev[0] = j->prog->fns[0];
   j->ev[1] = j->prog->fns[1];
-  j->mrows = j->prog->fns[2];
+  j->gram = j->prog->fns[2];
   j->envmax = j->prog->fns[3];
   j->gen = j->prog->fns[4];
   return j;
 }
 
+size_t td4_gram_doubles(const Td4Const& tc, int64_t n_mc) {
+  const int chunk = gram_chunk(n_mc);
+  return (size_t)((n_mc + chunk - 1) / chunk) * 2 * gram_count(tc.K);
+}
+
 void td4_launch_mmatrix(const Td4Jit& j, const Td4Const& tc, const Td4Table* tabs, int n_fits, const double* mc,
-                        int64_t ld_mc, int64_t n_mc, int chunk, double* part, double* Mc, hipStream_t s,
-                        const int* sel) {
-  const int kmax = td4_kmax(tc.K);
+                        int64_t ld_mc, int64_t n_mc, double* part, double* Mc, hipStream_t s, const int* sel) {
+  const int chunk = gram_chunk(n_mc);
   const int64_t nch = (n_mc + chunk - 1) / chunk;
-  const int rb = td4_row_block(tc.K);
-  const int nv = 2 * rb * kmax;
-  for (int i0 = 0; i0 < tc.K; i0 += rb) {
-    Td4Const c = tc;
-    const Td4Table* t = tabs;
-    const int* se = sel;
-    const double* m = mc;
-    int64_t l = ld_mc, nn = n_mc, nc = nch;
-    int ck = chunk, nf = n_fits, ii = i0;
-    double* p = part;
-    void* args[] = {&c, &t, &se, &m, &l, &nn, &ck, &nc, &nf, &ii, &p};
-    jit_launch(j.mrows, (unsigned)td4_blocks(nch, n_fits), kBlock, s, args);
-    hipLaunchKernelGGL(td4_mrows_finalize, dim3(n_fits), dim3(kFinalBlock), 0, s, tc, sel, part, nch, nv, kmax, i0,
-                       rb, 1.0 / (double)n_mc, Mc);
-  }
+  Td4Const c = tc;
+  const Td4Table* t = tabs;
+  const int* se = sel;
+  const double* m = mc;
+  int64_t l = ld_mc, nn = n_mc, nc = nch;
+  int ck = chunk, nf = n_fits;
+  double* p = part;
+  void* args[] = {&c, &t, &se, &m, &l, &nn, &ck, &nc, &nf, &p};
+  jit_launch(j.gram, (unsigned)td4_blocks(nch, n_fits), kBlock, s, args);
+  launch_gram_finalize(part, nch, tc.K, kGramSquare, kTd4MaxAmp, 1.0 / (double)n_mc, n_fits, sel, Mc,
+                       2 * kTd4MaxAmp * kTd4MaxAmp, s);
 }
 
 void td4_launch_events(const Td4Jit& j, const Td4Const& tc, const Td4Table* tabs, const int* status, int n_fits,

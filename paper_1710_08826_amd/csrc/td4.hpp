@@ -13,7 +13,7 @@ struct JitProgram;
 struct Td4Jit {
   std::shared_ptr<JitProgram> prog;
   hipFunction_t ev[2] = {nullptr, nullptr};  // without, with the gradient
-  hipFunction_t mrows = nullptr;
+  hipFunction_t gram = nullptr;  // normalization matrix
   hipFunction_t envmax = nullptr, gen = nullptr;  // toy generation
 };
 std::string td4_jit_source(const Td4Const& tc);
@@ -50,8 +50,10 @@ void td4_launch_prologue(const Td4Const& tc, const ParamBlock* pb, const double*
 // Normalization matrices of n_fits fits (only those with sel[f] != 0 when
 // sel, a device array, is not null).
 void td4_launch_mmatrix(const Td4Jit& j, const Td4Const& tc, const Td4Table* tabs, int n_fits, const double* mc,
-                        int64_t ld_mc, int64_t n_mc, int chunk, double* part, double* Mc, hipStream_t s,
+                        int64_t ld_mc, int64_t n_mc, double* part, double* Mc, hipStream_t s,
                         const int* sel = nullptr);
+// Doubles of `part` it needs per fit.
+size_t td4_gram_doubles(const Td4Const& tc, int64_t n_mc);
 // Events pass for n_fits fits sharing one event sample (fit-major items); a
 // fit whose status entry is not running is skipped (status may be null).
 void td4_launch_events(const Td4Jit& j, const Td4Const& tc, const Td4Table* tabs, const int* status, int n_fits,

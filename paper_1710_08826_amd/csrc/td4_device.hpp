@@ -24,6 +24,7 @@
 #pragma once
 #include "device_common.hpp"
 #include "fastmath.hpp"
+#include "gram_device.hpp"
 #include "philox.hpp"
 #include "td4_types.hpp"
 
@@ -444,18 +445,6 @@ __device__ __forceinline__ void td4_sum_grad(const Td4Point<S>& p, cplx l, doubl
   }
 }
 
-// Makes the compiler treat a point's values as new ones, so that basis
-// functions formed after it are recomputed from the lineshapes instead of
-// being kept in registers from an earlier loop.
-template <class S>
-__device__ __forceinline__ void td4_opaque(Td4Point<S>& p) {
-#pragma unroll
-  for (int r = 0; r < S::N12; ++r) asm volatile("" : "+v"(p.a12[r].re), "+v"(p.a12[r].im));
-#pragma unroll
-  for (int r = 0; r < S::N34; ++r) asm volatile("" : "+v"(p.a34[r].re), "+v"(p.a34[r].im));
-  asm volatile("" : "+v"(p.c12), "+v"(p.c34), "+v"(p.ssc), "+v"(p.sss));
-}
-
 // All basis amplitudes B_k of one kinematic point under one fit's lineshapes.
 template <class S>
 __device__ __forceinline__ void td4_basis_s(const Td4Const& tc, const Td4Table& tb, double m12, double m34, double c12,
@@ -721,53 +710,43 @@ __device__ inline void td4_envmax_body(const Td4Const& tc, const Td4Table* __res
   if (threadIdx.x == 0) atomicMax(vmax, (unsigned long long)__double_as_longlong(lds[0]));
 }
 
-// Rows i0..i0+RB-1 of M = sum over the phase-space sample of B_i conj(B_j)
-// (per fit; fits with sel[f] == 0 are skipped, sel may be null).
+// M = sum over the phase-space sample of B_i conj(B_j) (Gram), one row per
+// workgroup and fit (fits with sel[f] == 0 are skipped, sel may be null).
 template <class S>
-__device__ inline void td4_mrows_body(const Td4Const& tc, const Td4Table* __restrict__ tabs,
-                                      const int* __restrict__ sel, const double* __restrict__ mc, int64_t ld,
-                                      int64_t n, int chunk, int64_t nch, int n_fits, int i0,
-                                      double* __restrict__ part) {
+__device__ inline void td4_gram_body(const Td4Const& tc, const Td4Table* __restrict__ tabs,
+                                     const int* __restrict__ sel, const double* __restrict__ mc, int64_t ld,
+                                     int64_t n, int chunk, int64_t nch, int n_fits, double* __restrict__ part) {
   constexpr int K = S::K;
-  constexpr int RB = td4_row_block(K);
-  constexpr int NV = 2 * RB * K;
-  __shared__ double lds[block_sum_lds(NV)];
+  using G = Gram<K>;
+  __shared__ double lds[G::LDS];
   int64_t ch;
   int f;
   if (!td4_block_item(nch, n_fits, ch, f)) return;
   if (sel && !sel[f]) return;
-  double acc[NV];
-#pragma unroll
-  for (int i = 0; i < NV; ++i) acc[i] = 0.0;
+  G g;
+  g.init(lds);
   const int64_t base = ch * chunk;
   const int64_t end = base + chunk < n ? base + chunk : n;
-  for (int64_t i = base + threadIdx.x; i < end; i += kBlock) {
+  for (int64_t i = base + (threadIdx.x & ~63); i < end; i += kBlock) {
+    const int64_t p = i + (threadIdx.x & 63);
+    const int64_t q = p < end ? p : i;
     int zero = 0;
     asm volatile("" : "+s"(zero));
-    const Td4Table& tb = tabs[f + zero];
-    Td4Point<S> pt;
-    td4_point_s<S>(tc, tb, mc[i], mc[ld + i], mc[2 * ld + i], mc[3 * ld + i], mc[4 * ld + i], pt);
-    cplx bi[RB];
+    cplx B[K];
+    td4_basis_s<S>(tc, tabs[f + zero], mc[q], mc[ld + q], mc[2 * ld + q], mc[3 * ld + q], mc[4 * ld + q], B);
+    double re[K], im[K];
 #pragma unroll
-    for (int ib = 0; ib < RB; ++ib) {
-      bi[ib] = {0.0, 0.0};
-#pragma unroll
-      for (int k = 0; k < K; ++k)
-        if (k == i0 + ib) bi[ib] = td4_bk<S>(pt, k);
+    for (int k = 0; k < K; ++k) {
+      re[k] = B[k].re;
+      im[k] = B[k].im;
     }
-    td4_opaque<S>(pt);
+    if (p >= end) {
 #pragma unroll
-    for (int j = 0; j < K; ++j) {
-      const cplx bj = td4_bk<S>(pt, j);
-#pragma unroll
-      for (int ib = 0; ib < RB; ++ib) {
-        acc[2 * (ib * K + j)] = __builtin_fma(bi[ib].re, bj.re, __builtin_fma(bi[ib].im, bj.im, acc[2 * (ib * K + j)]));
-        acc[2 * (ib * K + j) + 1] =
-            __builtin_fma(bi[ib].im, bj.re, __builtin_fma(-bi[ib].re, bj.im, acc[2 * (ib * K + j) + 1]));
-      }
+      for (int k = 0; k < K; ++k) re[k] = im[k] = 0.0;
     }
+    g.add(re, im, lds);
   }
-  block_sum_row<NV>(acc, lds, part + ((int64_t)f * nch + ch) * NV);
+  g.reduce(lds, part + ((int64_t)f * nch + ch) * 2 * gram_count(K));
 }
 
 }  // namespace fn
@@ -780,12 +759,12 @@ __device__ inline void td4_mrows_body(const Td4Const& tc, const Td4Table* __rest
       double* __restrict__ part) {                                                                              \
     fn::td4_events_body<S, GRAD>(tc, tabs, status, ev, ld, n, chunk, nch, n_fits, part);                       \
   }
-#define FN_TD4_MROWS(NAME, S)                                                                                  \
+#define FN_TD4_GRAM(NAME, S)                                                                                   \
   extern "C" __global__ __launch_bounds__(fn::kBlock) void NAME(                                                \
       fn::Td4Const tc, const fn::Td4Table* __restrict__ tabs, const int* __restrict__ sel,                     \
-      const double* __restrict__ mc, int64_t ld, int64_t n, int chunk, int64_t nch, int n_fits, int i0,        \
+      const double* __restrict__ mc, int64_t ld, int64_t n, int chunk, int64_t nch, int n_fits,                \
       double* __restrict__ part) {                                                                              \
-    fn::td4_mrows_body<S>(tc, tabs, sel, mc, ld, n, chunk, nch, n_fits, i0, part);                              \
+    fn::td4_gram_body<S>(tc, tabs, sel, mc, ld, n, chunk, nch, n_fits, part);                                  \
   }
 #define FN_TD4_GEN(ENVMAX, GEN, S)                                                                             \
   extern "C" __global__ __launch_bounds__(fn::kBlock) void ENVMAX(                                             \

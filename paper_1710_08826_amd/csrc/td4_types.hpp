@@ -9,10 +9,6 @@ constexpr int kTd4MaxAmp = 20;   // basis amplitudes
 constexpr int kTd4MaxRes = 6;    // resonances per pair
 constexpr int kWeidN = 40;       // terms of the Faddeeva rational approximation
 
-// Rows of the normalization matrix accumulated per pass over the phase-space
-// sample (2 x rows x K doubles per thread).
-__host__ __device__ constexpr int td4_row_block(int K) { return K > 12 ? 2 : 4; }
-
 // w(i y) = exp(y^2) erfc(y) on y >= 0: kErfcK and the coefficients in Z =
 // (K - y)/(K + y) of (K + y) w(i y), rising powers (Chebyshev expansion of
 // degree 23 computed with 50 digits, rounded once).

@@ -36,23 +36,21 @@ std::string tddp_jit_source(const DalitzConst& dc, const double* fixed_ls) {
   o << "};\n};\n";
   o << "FN_TDDP_EVENTS(fn_tddp_ev0, fn_shape, false)\n"
        "FN_TDDP_EVENTS(fn_tddp_ev1, fn_shape, true)\n"
-       "FN_TDDP_MROWS(fn_tddp_maa, fn_shape, 0)\n"
-       "FN_TDDP_MROWS(fn_tddp_mbb, fn_shape, 1)\n"
-       "FN_TDDP_MROWS(fn_tddp_mab, fn_shape, 2)\n"
+       "FN_TDDP_GRAM(fn_tddp_gram, fn_shape)\n"
        "FN_TDDP_GEN(fn_tddp_gmax, fn_tddp_gen, fn_shape)\n";
   return o.str();
 }
 
 std::shared_ptr<TddpJit> tddp_jit(const DalitzConst& dc, const double* fixed_ls) {
   auto j = std::make_shared<TddpJit>();
-  j->prog = jit_load(tddp_jit_source(dc, fixed_ls), {"fn_tddp_ev0", "fn_tddp_ev1", "fn_tddp_maa", "fn_tddp_mbb", "fn_tddp_mab",
-                                           "fn_tddp_gmax", "fn_tddp_gen"});
+  j->prog = jit_load(tddp_jit_source(dc, fixed_ls), {"fn_tddp_ev0", "fn_tddp_ev1", "fn_tddp_gram", "fn_tddp_gmax",
+                                                     "fn_tddp_gen"});
   const auto& f = j->prog->fns;
   j->ev[0] = f[0];
   j->ev[1] = f[1];
-  for (int w = 0; w < 3; ++w) j->mrows[w] = f[2 + w];
-  j->gmax = f[5];
-  j->gen = f[6];
+  j->gram = f[2];
+  j->gmax = f[3];
+  j->gen = f[4];
   return j;
 }
 
@@ -203,24 +201,23 @@ void tddp_launch_copy_theta(const ParamBlock& pb, int P, double* dst, hipStream_
   hipLaunchKernelGGL(tddp_copy_theta, dim3(1), dim3(kBlock), 0, s, pb, P, dst);
 }
 
-void tddp_launch_mmatrices(const TddpJit& j, const DalitzConst& dc, const DalitzTable* tab, int grid_chunk,
-                           double* part, double* Mc, hipStream_t s) {
+size_t tddp_gram_doubles(const DalitzConst& dc) {
   const int64_t ncell = (int64_t)dc.nx * dc.ny;
-  const int64_t nch = (ncell + grid_chunk - 1) / grid_chunk;
-  const int K = dc.K;
-  for (int w = 0; w < 3; ++w) {
-    for (int i0 = 0; i0 < K; i0 += kMRowBlock) {
-      DalitzConst c = dc;
-      const DalitzTable* t = tab;
-      int ch = grid_chunk, ii = i0;
-      double* p = part;
-      void* args[] = {&c, &t, &ch, &ii, &p};
-      jit_launch(j.mrows[w], (unsigned)nch, kBlock, s, args);
-      // the level-2 step of the three-body normalization matrix writes the
-      // same layout (rows i0..i0+3, dA applied)
-      dalitz_launch_mrows_finalize(dc, part, nch, i0, Mc + (int64_t)w * 2 * K * K, s);
-    }
-  }
+  const int chunk = gram_chunk(ncell);
+  return (size_t)((ncell + chunk - 1) / chunk) * 2 * gram_count(2 * dc.K);
+}
+
+void tddp_launch_mmatrices(const TddpJit& j, const DalitzConst& dc, const DalitzTable* tab, double* part, double* Mc,
+                           hipStream_t s) {
+  const int64_t ncell = (int64_t)dc.nx * dc.ny;
+  DalitzConst c = dc;
+  const DalitzTable* t = tab;
+  int ch = gram_chunk(ncell);
+  const int64_t nch = (ncell + ch - 1) / ch;
+  double* p = part;
+  void* args[] = {&c, &t, &ch, &p};
+  jit_launch(j.gram, (unsigned)nch, kBlock, s, args);
+  launch_gram_finalize(part, nch, 2 * dc.K, kGramMixing, dc.K, dc.dA, 1, nullptr, Mc, 0, s);
 }
 
 void tddp_launch_gridmax(const TddpJit& j, const DalitzConst& dc, const DalitzTable* tab, const double* coef,

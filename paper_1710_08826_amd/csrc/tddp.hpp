@@ -12,16 +12,17 @@ struct JitProgram;
 struct TddpJit {
   std::shared_ptr<JitProgram> prog;
   hipFunction_t ev[2] = {nullptr, nullptr};   // without, with the gradient
-  hipFunction_t mrows[3] = {nullptr, nullptr, nullptr};  // MAA, MBB, MAB row blocks
+  hipFunction_t gram = nullptr;  // MAA, MBB, MAB
   hipFunction_t gmax = nullptr, gen = nullptr;            // toy generation
 };
 std::string tddp_jit_source(const DalitzConst& dc, const double* fixed_ls);
 std::shared_ptr<TddpJit> tddp_jit(const DalitzConst& dc, const double* fixed_ls);
 int tddp_nv(int K, bool grad);
-// The three normalization matrices (each K x K complex, dA included) into
-// Mc, Mc + 2K^2 and Mc + 4K^2; part holds one chunk of rows.
-void tddp_launch_mmatrices(const TddpJit& j, const DalitzConst& dc, const DalitzTable* tab, int grid_chunk,
-                           double* part, double* Mc, hipStream_t s);
+// The normalization matrices MAA, MBB and MAB (K x K complex each) from all
+// grid cells into Mc, Mc + 2K^2 and Mc + 4K^2; part holds tddp_gram_doubles.
+size_t tddp_gram_doubles(const DalitzConst& dc);
+void tddp_launch_mmatrices(const TddpJit& j, const DalitzConst& dc, const DalitzTable* tab, double* part, double* Mc,
+                           hipStream_t s);
 // Events pass: one row of partial sums per chunk.  coef: theta on the device.
 void tddp_launch_events(const TddpJit& j, const DalitzConst& dc, const DalitzTable* tab, const TddpTime& tt,
                         const double* coef, const TddpArg& ca, const double* ev, int64_t ld, int64_t n, int chunk,

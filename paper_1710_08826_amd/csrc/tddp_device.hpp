@@ -232,57 +232,43 @@ __device__ inline void tddp_events_body(const DalitzConst& dc, const DalitzTable
   block_sum_row<NV>(acc, lds, part + (int64_t)blockIdx.x * NV);
 }
 
-// Rows i0..i0+3 of one normalization matrix over one chunk of grid cells:
-// WHICH 0: A_i conj(A_j), 1: B_i conj(B_j), 2: conj(A_i) B_j (re, im pairs).
-template <class S, int WHICH>
-__device__ inline void tddp_mrows_body(const DalitzConst& dc, const DalitzTable* __restrict__ tab, int chunk,
-                                       int i0, double* __restrict__ part) {
+// The normalization matrices over one chunk of grid cells: the Gram sums of
+// the 2K vector (A, B), whose blocks are MAA, MBB and (B_j conj(A_i)) MAB_ij.
+template <class S>
+__device__ inline void tddp_gram_body(const DalitzConst& dc, const DalitzTable* __restrict__ tab, int chunk,
+                                      double* __restrict__ part) {
   constexpr int K = S::K;
-  constexpr int NV = 2 * kMRowBlock * K;
-  __shared__ double lds[block_sum_lds(NV)];
-  double acc[NV];
-#pragma unroll
-  for (int i = 0; i < NV; ++i) acc[i] = 0.0;
-  const int64_t ncell = (int64_t)dc.nx * dc.ny;
-  const int64_t base = (int64_t)blockIdx.x * chunk;
-  const int64_t end = base + chunk < ncell ? base + chunk : ncell;
+  using G = Gram<2 * K>;
+  __shared__ double lds[G::LDS];
+  G g;
+  g.init(lds);
+  const uint32_t ncell = (uint32_t)dc.nx * (uint32_t)dc.ny;
+  const uint32_t base = blockIdx.x * (uint32_t)chunk;
+  const uint32_t end = base + chunk < ncell ? base + chunk : ncell;
   const double* const r0 = &tab->r[0][0];
-  for (int64_t c = base + threadIdx.x; c < end; c += kBlock) {
+  for (uint32_t i = base + (threadIdx.x & ~63u); i < end; i += kBlock) {
+    const uint32_t c = i + (threadIdx.x & 63u);
+    double s12, s13;
+    const bool in = dalitz_cell(dc, c < end ? c : i, s12, s13) && c < end;
+    if (!__any(in)) continue;
     int zero = 0;
     asm volatile("" : "+s"(zero));
-    const double* r = r0 + zero;
-    const int64_t ix = c / dc.ny, iy = c - ix * dc.ny;
-    const double s12 = grid_centre(dc.a12, ix, dc.d12);
-    const double s13 = grid_centre(dc.a13, iy, dc.d13);
-    if (!dalitz_inside(dc, s12, s13)) continue;
-    double Are[K], Aim[K], Bre[K], Bim[K], Lre[K], Lim[K], Rre[K], Rim[K];
-    tddp_basis2<S>(dc, r, s12, s13, Are, Aim, Bre, Bim);
+    double are[K], aim[K], bre[K], bim[K], re[2 * K], im[2 * K];
+    tddp_basis2<S>(dc, r0 + zero, s12, s13, are, aim, bre, bim);
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-      Lre[k] = WHICH == 1 ? Bre[k] : Are[k];
-      Lim[k] = WHICH == 1 ? Bim[k] : Aim[k];
-      Rre[k] = WHICH == 0 ? Are[k] : Bre[k];
-      Rim[k] = WHICH == 0 ? Aim[k] : Bim[k];
+      re[k] = are[k];
+      im[k] = aim[k];
+      re[K + k] = bre[k];
+      im[K + k] = bim[k];
     }
+    if (!in) {
 #pragma unroll
-    for (int ib = 0; ib < kMRowBlock; ++ib) {
-      double xr = 0.0, xi = 0.0;  // left factor i = i0 + ib, selected with uniform guards
-#pragma unroll
-      for (int k = 0; k < K; ++k)
-        if (k == i0 + ib) {
-          xr = Lre[k];
-          xi = WHICH == 2 ? -Lim[k] : Lim[k];
-        }
-#pragma unroll
-      for (int j = 0; j < K; ++j) {
-        // (xr + i xi) times conj(R_j) for WHICH 0/1, times R_j for WHICH 2
-        const double rr = Rre[j], ri = WHICH == 2 ? Rim[j] : -Rim[j];
-        acc[2 * (ib * K + j)] = __builtin_fma(xr, rr, __builtin_fma(-xi, ri, acc[2 * (ib * K + j)]));
-        acc[2 * (ib * K + j) + 1] = __builtin_fma(xr, ri, __builtin_fma(xi, rr, acc[2 * (ib * K + j) + 1]));
-      }
+      for (int k = 0; k < 2 * K; ++k) re[k] = im[k] = 0.0;
     }
+    g.add(re, im, lds);
   }
-  block_sum_row<NV>(acc, lds, part + (int64_t)blockIdx.x * NV);
+  g.reduce(lds, part + (int64_t)blockIdx.x * 2 * gram_count(2 * K));
 }
 
 // ---------------------------------------------------------------- toy events
@@ -398,11 +384,10 @@ __device__ inline void tddp_gen_body(const DalitzConst& dc, const DalitzTable* _
     fn::cdouble* c = coef ? (fn::cdouble*)coef : (fn::cdouble*)&ca.v[0];                                       \
     fn::tddp_events_body<S, GRAD>(dc, tab, tt, c, ev, ld, n, chunk, part);                                    \
   }
-#define FN_TDDP_MROWS(NAME, S, WHICH)                                                                          \
-  extern "C" __global__ __launch_bounds__(fn::kBlock) void NAME(                                               \
-      fn::DalitzConst dc, const fn::DalitzTable* __restrict__ tab, int chunk, int i0,                          \
-      double* __restrict__ part) {                                                                             \
-    fn::tddp_mrows_body<S, WHICH>(dc, tab, chunk, i0, part);                                                   \
+#define FN_TDDP_GRAM(NAME, S)                                                                                  \
+  extern "C" __global__ __launch_bounds__(fn::kBlock) __attribute__((amdgpu_waves_per_eu(2))) void NAME(       \
+      fn::DalitzConst dc, const fn::DalitzTable* __restrict__ tab, int chunk, double* __restrict__ part) {    \
+    fn::tddp_gram_body<S>(dc, tab, chunk, part);                                                               \
   }
 #define FN_TDDP_GEN(GRIDMAX, GEN, S)                                                                           \
   extern "C" __global__ __launch_bounds__(fn::kBlock) void GRIDMAX(                                            \

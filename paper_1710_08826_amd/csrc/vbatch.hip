@@ -104,11 +104,9 @@ void reserve_part(fn_vbatch* b, int64_t n) {
 void build_matrices(fn_vbatch* b) {
   fn_model* m = b->m;
   if (b->M_valid && b->mc_gen == m->mc_gen) return;
-  const int mchunk = 1024;
-  const int64_t rows = (m->n_mc + mchunk - 1) / mchunk;
-  b->mpart.reserve(sizeof(double) * (size_t)rows * b->F * 2 * td4_row_block(m->td4.K) * td4_kmax(m->td4.K));
+  b->mpart.reserve(sizeof(double) * td4_gram_doubles(m->td4, m->n_mc) * b->F);
   td4_launch_mmatrix(*m->td4_jit, m->td4, (const Td4Table*)b->tabs.ptr, b->F, (const double*)m->d_mc.ptr, m->n_mc,
-                     m->n_mc, mchunk, (double*)b->mpart.ptr, (double*)b->Mc.ptr, b->stream);
+                     m->n_mc, (double*)b->mpart.ptr, (double*)b->Mc.ptr, b->stream);
   hip_check(hipGetLastError(), "kernel launch");
   b->M_valid = true;
   b->mc_gen = m->mc_gen;
@@ -418,11 +416,9 @@ fn_status fn_vbatch_serve(fn_vbatch* b, const fn_vrequest* reqs, int32_t n_req, 
         const int* sel = (const int*)b->sel.ptr;
         td4_launch_prologue(tc, nullptr, (const double*)b->st.ptr, stride, (const Td4FitConst*)b->fc.ptr, sel, F,
                             (Td4Table*)b->tabs.ptr, b->stream);
-        const int mchunk = 1024;
-        const int64_t rows = (m->n_mc + mchunk - 1) / mchunk;
-        b->mpart.reserve(sizeof(double) * (size_t)rows * F * 2 * td4_row_block(tc.K) * td4_kmax(tc.K));
+        b->mpart.reserve(sizeof(double) * td4_gram_doubles(tc, m->n_mc) * F);
         td4_launch_mmatrix(*m->td4_jit, tc, (const Td4Table*)b->tabs.ptr, F, (const double*)m->d_mc.ptr, m->n_mc,
-                           m->n_mc, mchunk, (double*)b->mpart.ptr, (double*)b->Mc.ptr, b->stream, sel);
+                           m->n_mc, (double*)b->mpart.ptr, (double*)b->Mc.ptr, b->stream, sel);
         hip_check(hipGetLastError(), "kernel launch");
         // the pinned staging of this round must not change before the copies ran
         hip_check(hipStreamSynchronize(b->stream), "hipStreamSynchronize");
