@@ -29,8 +29,9 @@ FLAGS = [
 
 # Device headers compiled again at run time (hipRTC) with a model's structure
 # as compile-time constants; their text is embedded in the library.
-EMBEDDED = ["model.hpp", "fastmath.hpp", "device_common.hpp", "philox.hpp", "gram_device.hpp",
-            "dalitz_device.hpp", "td4_types.hpp", "td4_device.hpp", "tddp_device.hpp"]
+EMBEDDED = ["model.hpp", "fastmath.hpp", "device_common.hpp", "philox.hpp",
+            "accept_device.hpp", "gram_device.hpp", "dalitz_device.hpp", "td4_types.hpp", "td4_device.hpp",
+            "tddp_device.hpp"]
 DELIM = "FNSRC"
 
 

@@ -571,10 +571,26 @@ void dalitz_launch_gram(const DalitzJit& j, const DalitzConst& dc, const DalitzT
   launch_gram_finalize(part, rows, dc.K, kGramSquare, dc.K, dc.dA, 1, nullptr, Mc, 0, s);
 }
 
+// Record of a toy generation call (GenRec): cleared, then the envelope -- the
+// caller's, or factor times the largest density found; zero when the
+// parameters are invalid, which makes the generator return at once.
+__global__ void gen_reset(GenRec* r) { *r = GenRec{0ull, {0ull, 0ull}, 0.0, 1.0}; }
+__global__ void gen_envelope(GenRec* r, double factor, double user, const double* valid) {
+  const double v = valid ? *valid : 1.0;
+  const double w = user > 0.0 ? user : factor * __longlong_as_double((long long)r->vmax);
+  r->W = v != 0.0 ? w : 0.0;
+  r->valid = v;
+}
+
+void launch_gen_reset(GenRec* r, hipStream_t s) { hipLaunchKernelGGL(gen_reset, dim3(1), dim3(1), 0, s, r); }
+void launch_gen_envelope(GenRec* r, double factor, double user, const double* valid, hipStream_t s) {
+  hipLaunchKernelGGL(gen_envelope, dim3(1), dim3(1), 0, s, r, factor, user, valid);
+}
+
 void dalitz_launch_gridmax(const DalitzJit& j, const DalitzConst& dc, const DalitzTable* tab,
                            unsigned long long* vmax, hipStream_t s) {
   const int64_t ncell = (int64_t)dc.nx * dc.ny;
-  const int64_t blocks = std::min<int64_t>((ncell + kBlock - 1) / kBlock, 4096);
+  const int64_t blocks = std::min<int64_t>((ncell + kBlock - 1) / kBlock, kMaxBlocks);
   DalitzConst c = dc;
   const DalitzTable* t = tab;
   unsigned long long* v = vmax;
@@ -583,19 +599,20 @@ void dalitz_launch_gridmax(const DalitzJit& j, const DalitzConst& dc, const Dali
 }
 
 void dalitz_launch_gen(const DalitzJit& j, const DalitzConst& dc, const DalitzTable* tab, uint32_t k0, uint32_t k1,
-                       int64_t n, double W, const double box[4], int max_attempts, double* ev, int64_t ld,
+                       int64_t n, const double* W, const double box[4], int max_attempts, double* ev, int64_t ld,
                        unsigned long long* bad, hipStream_t s) {
   if (n == 0) return;
   DalitzConst c = dc;
   const DalitzTable* t = tab;
   uint32_t a0 = k0, a1 = k1;
   int64_t nn = n, l = ld;
-  double w = W, b0 = box[0], b1 = box[1], b2 = box[2], b3 = box[3];
-  int ma = max_attempts;
+  const double* w = W;
+  double b0 = box[0], b1 = box[1], b2 = box[2], b3 = box[3];
+  int pw = gen_per_wave(n), ma = max_attempts;
   double* e = ev;
   unsigned long long* b = bad;
-  void* args[] = {&c, &t, &a0, &a1, &nn, &w, &b0, &b1, &b2, &b3, &ma, &e, &l, &b};
-  jit_launch(j.gen, (unsigned)((n + kBlock - 1) / kBlock), kBlock, s, args);
+  void* args[] = {&c, &t, &a0, &a1, &nn, &w, &b0, &b1, &b2, &b3, &pw, &ma, &e, &l, &b};
+  jit_launch(j.gen, gen_blocks(n), kBlock, s, args);
 }
 
 void dalitz_launch_eval(const DalitzConst& dc, const DalitzTable* tab, const double* ev, int64_t ld, int64_t n,

@@ -30,6 +30,7 @@
 // and a matrix pass: sum over the cells inside the region of A_i conj(A_j)
 // (gram_device.hpp), the cached M of fixed lineshapes.
 #pragma once
+#include "accept_device.hpp"
 #include "device_common.hpp"
 #include "fastmath.hpp"
 #include "gram_device.hpp"
@@ -475,24 +476,15 @@ __device__ __forceinline__ double dalitz_value(const DalitzConst& dc, const doub
 template <class S>
 __device__ inline void dalitz_gridmax_body(const DalitzConst& dc, const DalitzTable* __restrict__ tab,
                                            unsigned long long* __restrict__ vmax) {
-  __shared__ double lds[kBlock];
-  const int64_t ncell = (int64_t)dc.nx * dc.ny;
+  const uint32_t ncell = (uint32_t)dc.nx * (uint32_t)dc.ny;
   const double* r = &tab->r[0][0];
   double m = 0.0;
-  for (int64_t c = (int64_t)blockIdx.x * kBlock + threadIdx.x; c < ncell; c += (int64_t)gridDim.x * kBlock) {
-    const int64_t ix = c / dc.ny, iy = c - ix * dc.ny;
-    const double s12 = grid_centre(dc.a12, ix, dc.d12);
-    const double s13 = grid_centre(dc.a13, iy, dc.d13);
-    if (!dalitz_inside(dc, s12, s13)) continue;
+  for (uint32_t c = blockIdx.x * kBlock + threadIdx.x; c < ncell; c += gridDim.x * kBlock) {
+    double s12, s13;
+    if (!dalitz_cell(dc, c, s12, s13)) continue;
     m = fmax(m, dalitz_value<S>(dc, r, (cdouble*)tab->coef, s12, s13));
   }
-  lds[threadIdx.x] = m;
-  __syncthreads();
-  for (int h = kBlock / 2; h > 0; h >>= 1) {
-    if (threadIdx.x < h) lds[threadIdx.x] = fmax(lds[threadIdx.x], lds[threadIdx.x + h]);
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) atomicMax(vmax, (unsigned long long)__double_as_longlong(lds[0]));
+  block_max(m, vmax);
 }
 
 // Events distributed as P~ by accept-reject from the bounding box
@@ -505,34 +497,39 @@ __device__ inline void dalitz_gridmax_body(const DalitzConst& dc, const DalitzTa
 // within max_attempts is NaN and counts in bad[1].
 template <class S>
 __device__ inline void dalitz_gen_body(const DalitzConst& dc, const DalitzTable* __restrict__ tab, uint32_t k0,
-                                       uint32_t k1, int64_t n, double W, double lo12, double hi12, double lo13,
-                                       double hi13, int max_attempts, double* __restrict__ ev, int64_t ld,
+                                       uint32_t k1, int64_t n, const double* __restrict__ Wp, double lo12,
+                                       double hi12, double lo13, double hi13, int per_wave, int max_attempts,
+                                       double* __restrict__ ev, int64_t ld,
                                        unsigned long long* __restrict__ bad) {
 #pragma clang fp contract(off)
-  const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (i >= n) return;
+  __shared__ AcceptLds lds;
+  const double W = *Wp;
+  if (!(W > 0.0 && W < __builtin_inf())) return;  // the host reports it
   const double* r = &tab->r[0][0];
   const double w12 = hi12 - lo12, w13 = hi13 - lo13;
-  double x12 = __builtin_nan(""), x13 = __builtin_nan(""), px = 0.0;
-  for (int a = 0; a < max_attempts; ++a) {
-    double u1, u2, u3, unused;
-    philox_uniforms((uint64_t)i, 2u * a, 1u, k0, k1, u1, u2);
-    philox_uniforms((uint64_t)i, 2u * a + 1u, 1u, k0, k1, u3, unused);
-    const double s12 = lo12 + u1 * w12;
-    const double s13 = lo13 + u2 * w13;
-    if (!dalitz_inside(dc, s12, s13)) continue;
-    const double p = dalitz_value<S>(dc, r, (cdouble*)tab->coef, s12, s13);
-    if (u3 * W < p) {
-      x12 = s12;
-      x13 = s13;
-      px = p;
-      break;
-    }
-  }
-  ev[i] = x12;
-  ev[ld + i] = x13;
-  if (px > W) atomicAdd(bad, 1ull);
-  if (x12 != x12) atomicAdd(bad + 1, 1ull);
+  double s12, s13, p;
+  accept_reject(
+      lds, n, per_wave, max_attempts,
+      [&](int64_t i, int a) {
+#pragma clang fp contract(off)
+        double u1, u2, u3, unused;
+        philox_uniforms((uint64_t)i, 2u * a, 1u, k0, k1, u1, u2);
+        s12 = lo12 + u1 * w12;
+        s13 = lo13 + u2 * w13;
+        if (!dalitz_inside(dc, s12, s13)) return false;
+        philox_uniforms((uint64_t)i, 2u * a + 1u, 1u, k0, k1, u3, unused);
+        p = dalitz_value<S>(dc, r, (cdouble*)tab->coef, s12, s13);
+        return u3 * W < p;
+      },
+      [&](int64_t i) {
+        ev[i] = s12;
+        ev[ld + i] = s13;
+        if (p > W) atomicAdd(bad, 1ull);
+      },
+      [&](int64_t i) {
+        ev[i] = ev[ld + i] = __builtin_nan("");
+        atomicAdd(bad + 1, 1ull);
+      });
 }
 
 }  // namespace fn
@@ -565,7 +562,8 @@ __device__ inline void dalitz_gen_body(const DalitzConst& dc, const DalitzTable*
   }                                                                                                            \
   extern "C" __global__ __launch_bounds__(fn::kBlock) void GEN(                                                \
       fn::DalitzConst dc, const fn::DalitzTable* __restrict__ tab, uint32_t k0, uint32_t k1, int64_t n,        \
-      double W, double lo12, double hi12, double lo13, double hi13, int max_attempts,                          \
-      double* __restrict__ ev, int64_t ld, unsigned long long* __restrict__ bad) {                             \
-    fn::dalitz_gen_body<S>(dc, tab, k0, k1, n, W, lo12, hi12, lo13, hi13, max_attempts, ev, ld, bad);         \
+      const double* __restrict__ W, double lo12, double hi12, double lo13, double hi13, int per_wave,          \
+      int max_attempts, double* __restrict__ ev, int64_t ld, unsigned long long* __restrict__ bad) {           \
+    fn::dalitz_gen_body<S>(dc, tab, k0, k1, n, W, lo12, hi12, lo13, hi13, per_wave, max_attempts, ev, ld,      \
+                           bad);                                                                                \
   }

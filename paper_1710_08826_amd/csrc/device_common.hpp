@@ -144,6 +144,23 @@ __device__ inline void sum_rows(const double* __restrict__ part, int64_t nrows, 
   sum_rows_t<kBlock>(part, nrows, nv, scratch, res);
 }
 
+// The largest of the workgroup's values m >= 0 into *vmax, as the bit pattern
+// of a non-negative double (ordered like the value).  One atomic per workgroup:
+// 4096 of them on one address took most of a 50 us pass, so such passes run
+// kMaxBlocks workgroups.
+constexpr int kMaxBlocks = 512;
+__device__ inline void block_max(double m, unsigned long long* vmax) {
+  __shared__ double lds[kBlock / 64];
+#pragma unroll
+  for (int d = 32; d > 0; d >>= 1) m = fmax(m, __shfl_xor(m, d));
+  if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = m;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < kBlock / 64; ++w) m = fmax(m, lds[w]);
+    atomicMax(vmax, (unsigned long long)__double_as_longlong(m));
+  }
+}
+
 // Kernel span (measurement support, used only when a launch is given a span
 // record): span[0] the sum over launches of (last workgroup end - earliest
 // workgroup start) on the device wall clock, span[1] the number of launches,

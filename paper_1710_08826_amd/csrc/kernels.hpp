@@ -104,15 +104,37 @@ void dalitz_launch_grid(const DalitzJit& j, const DalitzConst& dc, const DalitzT
 // from all grid cells; part holds rows (= ceil(cells / chunk)) x K (K + 1) doubles.
 void dalitz_launch_gram(const DalitzJit& j, const DalitzConst& dc, const DalitzTable* tab, int chunk, int64_t rows,
                         double* part, double* Mc, hipStream_t s);
+// Record of a toy generation call on the device: the largest density found
+// (bits of a non-negative double), kept points above the envelope and
+// unresolved events, the envelope, the parameters' validity.
+struct GenRec {
+  unsigned long long vmax;
+  unsigned long long bad[2];
+  double W;
+  double valid;
+};
+void launch_gen_reset(GenRec* r, hipStream_t s);
+void launch_gen_envelope(GenRec* r, double factor, double user, const double* valid, hipStream_t s);
+// Accept-reject launches: events per wave (accept_device.hpp) -- one for small
+// samples, whose 64 lanes then try one event's attempts side by side, up to
+// 128 -- and workgroups.
+inline int gen_per_wave(int64_t n) {
+  const int64_t p = (n + 4095) / 4096;
+  return (int)(p < 1 ? 1 : (p > 128 ? 128 : p));
+}
+inline unsigned gen_blocks(int64_t n) {
+  const int64_t per_block = (int64_t)gen_per_wave(n) * kWaves;
+  return (unsigned)((n + per_block - 1) / per_block);
+}
 // Toy events: vmax (zeroed by the caller) receives the bits of the largest P~
 // over the grid cells inside the region; the generator writes n events (SoA,
-// leading dimension ld) by accept-reject under envelope W from the box
+// leading dimension ld) by accept-reject under envelope *W (device) from the box
 // box = {lo12, hi12, lo13, hi13}; bad[0] counts accepted points above W,
 // bad[1] events left unresolved after max_attempts (zeroed by the caller).
 void dalitz_launch_gridmax(const DalitzJit& j, const DalitzConst& dc, const DalitzTable* tab,
                            unsigned long long* vmax, hipStream_t s);
 void dalitz_launch_gen(const DalitzJit& j, const DalitzConst& dc, const DalitzTable* tab, uint32_t k0, uint32_t k1,
-                       int64_t n, double W, const double box[4], int max_attempts, double* ev, int64_t ld,
+                       int64_t n, const double* W, const double box[4], int max_attempts, double* ev, int64_t ld,
                        unsigned long long* bad, hipStream_t s);
 void dalitz_launch_eval(const DalitzConst& dc, const DalitzTable* tab, const double* ev, int64_t ld, int64_t n,
                         const double* norm, double* p, hipStream_t s);

@@ -689,6 +689,25 @@ void nll_binned_host(fn_model* m, const double* theta_host, const BinnedData& bd
   if (gbad) throw Error(FN_E_NONFINITE, "gradient is not finite");
 }
 
+// Waits for a generation call and reports its record: the envelope used, then
+// the first fault found.
+static void finish_generation(fn_model* m, const GenRec* g, const char* vanishes, double* envelope_used,
+                              hipStream_t s) {
+  hip_check(hipGetLastError(), "kernel launch");
+  static_assert(sizeof(GenRec) <= 5 * sizeof(double), "fits the pinned results of a model with one parameter");
+  hip_check(hipMemcpyAsync(m->h_out, g, sizeof(GenRec), hipMemcpyDeviceToHost, s), "hipMemcpyAsync");
+  hip_check(hipStreamSynchronize(s), "hipStreamSynchronize");
+  GenRec r;
+  std::memcpy(&r, m->h_out, sizeof(r));
+  if (r.valid == 0.0) throw Error(FN_E_INVALID, "invalid lineshape parameters");
+  if (!(r.W > 0.0) || !std::isfinite(r.W)) throw Error(FN_E_INVALID, vanishes);
+  if (envelope_used) *envelope_used = r.W;
+  if (r.bad[0])
+    throw Error(FN_E_DOMAIN, std::to_string(r.bad[0]) + " accepted events lie above the envelope " +
+                                 std::to_string(r.W) + ": raise it");
+  if (r.bad[1]) throw Error(FN_E_DOMAIN, std::to_string(r.bad[1]) + " events not resolved within the attempt limit");
+}
+
 void generate_td4(fn_model* m, const double* theta_host, uint32_t seed, uint32_t fit, int64_t n, double envelope,
                   double* ev_dev, int64_t ld, double* envelope_used, hipStream_t s) {
   if (n < 0 || (n > 0 && !ev_dev)) throw Error(FN_E_INVALID, "bad output");
@@ -701,34 +720,17 @@ void generate_td4(fn_model* m, const double* theta_host, uint32_t seed, uint32_t
   const Td4FitConst* fc = (const Td4FitConst*)m->d_fixed.ptr;
   td4_launch_prologue(tc, &pb, nullptr, m->P, fc, nullptr, 1, m->table_td4(), s);
   const Td4Proposal pr = td4_proposal(tc, td4_fit_const(tc, m->fixed_ls.data()));
-  m->d_gen.reserve(3 * sizeof(unsigned long long));
-  unsigned long long* g = (unsigned long long*)m->d_gen.ptr;
-  hip_check(hipMemsetAsync(g, 0, 3 * sizeof(unsigned long long), s), "hipMemsetAsync");
-  double W = envelope;
-  if (W == 0.0) {
+  m->d_gen.reserve(sizeof(GenRec));
+  GenRec* g = (GenRec*)m->d_gen.ptr;
+  launch_gen_reset(g, s);
+  if (envelope == 0.0) {
     if (m->n_mc <= 0)
       throw Error(FN_E_INVALID, "td4: the automatic envelope needs the normalization sample (or give an envelope)");
-    td4_launch_envmax(*m->td4_jit, tc, m->table_td4(), pr, (const double*)m->d_mc.ptr, m->n_mc, m->n_mc, g, s);
-    hip_check(hipGetLastError(), "kernel launch");
-    unsigned long long bits = 0;
-    hip_check(hipMemcpyAsync(&bits, g, sizeof(bits), hipMemcpyDeviceToHost, s), "hipMemcpyAsync");
-    hip_check(hipStreamSynchronize(s), "hipStreamSynchronize");
-    double vmax;
-    std::memcpy(&vmax, &bits, sizeof(vmax));
-    if (!(vmax > 0.0) || !std::isfinite(vmax)) throw Error(FN_E_INVALID, "the amplitudes vanish on the sample");
-    W = kGenEnvelopeFactor * vmax;
+    td4_launch_envmax(*m->td4_jit, tc, m->table_td4(), pr, (const double*)m->d_mc.ptr, m->n_mc, m->n_mc, &g->vmax, s);
   }
-  if (envelope_used) *envelope_used = W;
-  if (n == 0) return;
-  td4_launch_gen(*m->td4_jit, tc, m->table_td4(), pr, seed, fit, n, W, kGenMaxAttemptsTd4, ev_dev, ld, g + 1, s);
-  hip_check(hipGetLastError(), "kernel launch");
-  unsigned long long bad[2] = {0, 0};
-  hip_check(hipMemcpyAsync(bad, g + 1, sizeof(bad), hipMemcpyDeviceToHost, s), "hipMemcpyAsync");
-  hip_check(hipStreamSynchronize(s), "hipStreamSynchronize");
-  if (bad[0])
-    throw Error(FN_E_DOMAIN, std::to_string(bad[0]) + " accepted events lie above the envelope " + std::to_string(W) +
-                                 ": raise it");
-  if (bad[1]) throw Error(FN_E_DOMAIN, std::to_string(bad[1]) + " events not resolved within the attempt limit");
+  launch_gen_envelope(g, kGenEnvelopeFactor, envelope, nullptr, s);
+  td4_launch_gen(*m->td4_jit, tc, m->table_td4(), pr, seed, fit, n, &g->W, kGenMaxAttemptsTd4, ev_dev, ld, g->bad, s);
+  finish_generation(m, g, "the amplitudes vanish on the sample", envelope_used, s);
 }
 
 }  // namespace fn
@@ -1102,43 +1104,21 @@ fn_status fn_generate(fn_model* m, const double* theta_host, uint32_t seed, uint
     const double* coef = (const double*)m->d_theta.ptr;
     if (td && !(std::fabs(theta_host[m->P - 1]) < 1.0))
       throw Error(FN_E_INVALID, "tddp3 generation needs |y| < 1");
-    m->d_gen.reserve(3 * sizeof(unsigned long long));
-    unsigned long long* g = (unsigned long long*)m->d_gen.ptr;
-    hip_check(hipMemsetAsync(g, 0, 3 * sizeof(unsigned long long), s), "hipMemsetAsync");
-    double valid = 0.0;
-    hip_check(hipMemcpyAsync(&valid, &m->table_dal()->valid, sizeof(double), hipMemcpyDeviceToHost, s),
-              "hipMemcpyAsync");
-    hip_check(hipStreamSynchronize(s), "hipStreamSynchronize");
-    if (valid == 0.0) throw Error(FN_E_INVALID, "invalid lineshape parameters");
-    double W = envelope;
-    if (W == 0.0) {
-      if (td) tddp_launch_gridmax(*m->tddp_jit, dc, m->table_dal(), coef, g, s);
-      else dalitz_launch_gridmax(*m->dal_jit, dc, m->table_dal(), g, s);
-      hip_check(hipGetLastError(), "kernel launch");
-      unsigned long long bits = 0;
-      hip_check(hipMemcpyAsync(&bits, g, sizeof(bits), hipMemcpyDeviceToHost, s), "hipMemcpyAsync");
-      hip_check(hipStreamSynchronize(s), "hipStreamSynchronize");
-      double vmax;
-      std::memcpy(&vmax, &bits, sizeof(vmax));
-      if (!(vmax > 0.0) || !std::isfinite(vmax)) throw Error(FN_E_INVALID, "the density vanishes on the grid");
-      W = kGenEnvelopeFactor * vmax;
+    m->d_gen.reserve(sizeof(GenRec));
+    GenRec* g = (GenRec*)m->d_gen.ptr;
+    launch_gen_reset(g, s);
+    if (envelope == 0.0) {
+      if (td) tddp_launch_gridmax(*m->tddp_jit, dc, m->table_dal(), coef, &g->vmax, s);
+      else dalitz_launch_gridmax(*m->dal_jit, dc, m->table_dal(), &g->vmax, s);
     }
-    if (envelope_used) *envelope_used = W;
-    if (n == 0) return;
+    launch_gen_envelope(g, kGenEnvelopeFactor, envelope, &m->table_dal()->valid, s);
     if (td)
-      tddp_launch_gen(*m->tddp_jit, dc, m->table_dal(), coef, m->tdt, seed, fit, n, W, m->box, kGenMaxAttemptsModel,
-                      ev_dev, ld, g + 1, s);
+      tddp_launch_gen(*m->tddp_jit, dc, m->table_dal(), coef, m->tdt, seed, fit, n, &g->W, m->box,
+                      kGenMaxAttemptsModel, ev_dev, ld, g->bad, s);
     else
-      dalitz_launch_gen(*m->dal_jit, dc, m->table_dal(), seed, fit, n, W, m->box, kGenMaxAttemptsModel, ev_dev, ld,
-                        g + 1, s);
-    hip_check(hipGetLastError(), "kernel launch");
-    unsigned long long bad[2] = {0, 0};
-    hip_check(hipMemcpyAsync(bad, g + 1, sizeof(bad), hipMemcpyDeviceToHost, s), "hipMemcpyAsync");
-    hip_check(hipStreamSynchronize(s), "hipStreamSynchronize");
-    if (bad[0])
-      throw Error(FN_E_DOMAIN, std::to_string(bad[0]) + " accepted events lie above the envelope " +
-                                   std::to_string(W) + ": raise it");
-    if (bad[1]) throw Error(FN_E_DOMAIN, std::to_string(bad[1]) + " events not resolved within the attempt limit");
+      dalitz_launch_gen(*m->dal_jit, dc, m->table_dal(), seed, fit, n, &g->W, m->box, kGenMaxAttemptsModel, ev_dev,
+                        ld, g->bad, s);
+    finish_generation(m, g, "the density vanishes on the grid", envelope_used, s);
   });
 }
 

@@ -518,7 +518,7 @@ Td4Proposal td4_proposal(const Td4Const& tc, const Td4FitConst& fc) {
 
 void td4_launch_envmax(const Td4Jit& j, const Td4Const& tc, const Td4Table* tab, const Td4Proposal& pr,
                        const double* mc, int64_t ld, int64_t n, unsigned long long* vmax, hipStream_t s) {
-  const int64_t blocks = std::min<int64_t>((n + kBlock - 1) / kBlock, 4096);
+  const int64_t blocks = std::min<int64_t>((n + kBlock - 1) / kBlock, kMaxBlocks);
   Td4Const c = tc;
   const Td4Table* t = tab;
   Td4Proposal q = pr;
@@ -530,7 +530,7 @@ void td4_launch_envmax(const Td4Jit& j, const Td4Const& tc, const Td4Table* tab,
 }
 
 void td4_launch_gen(const Td4Jit& j, const Td4Const& tc, const Td4Table* tab, const Td4Proposal& pr, uint32_t k0,
-                    uint32_t k1, int64_t n, double W, int max_attempts, double* ev, int64_t ld,
+                    uint32_t k1, int64_t n, const double* W, int max_attempts, double* ev, int64_t ld,
                     unsigned long long* bad, hipStream_t s) {
   if (n == 0) return;
   Td4Const c = tc;
@@ -538,12 +538,12 @@ void td4_launch_gen(const Td4Jit& j, const Td4Const& tc, const Td4Table* tab, co
   Td4Proposal q = pr;
   uint32_t a0 = k0, a1 = k1;
   int64_t nn = n, l = ld;
-  double w = W;
-  int ma = max_attempts;
+  const double* w = W;
+  int pw = gen_per_wave(n), ma = max_attempts;
   double* e = ev;
   unsigned long long* b = bad;
-  void* args[] = {&c, &t, &q, &a0, &a1, &nn, &w, &ma, &e, &l, &b};
-  jit_launch(j.gen, (unsigned)((n + kBlock - 1) / kBlock), kBlock, s, args);
+  void* args[] = {&c, &t, &q, &a0, &a1, &nn, &w, &pw, &ma, &e, &l, &b};
+  jit_launch(j.gen, gen_blocks(n), kBlock, s, args);
 }
 
 }  // namespace fn

@@ -39,7 +39,7 @@ Td4Proposal td4_proposal(const Td4Const& tc, const Td4FitConst& fc);
 void td4_launch_envmax(const Td4Jit& j, const Td4Const& tc, const Td4Table* tab, const Td4Proposal& pr,
                        const double* mc, int64_t ld, int64_t n, unsigned long long* vmax, hipStream_t s);
 void td4_launch_gen(const Td4Jit& j, const Td4Const& tc, const Td4Table* tab, const Td4Proposal& pr, uint32_t k0,
-                    uint32_t k1, int64_t n, double W, int max_attempts, double* ev, int64_t ld,
+                    uint32_t k1, int64_t n, const double* W, int max_attempts, double* ev, int64_t ld,
                     unsigned long long* bad, hipStream_t s);
 // theta: n_fits rows of theta_stride doubles on the device, or (pb != null,
 // n_fits == 1) the parameter block passed by value.

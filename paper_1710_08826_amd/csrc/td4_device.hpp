@@ -22,6 +22,7 @@
 // I is the phase-space average of the t-integrated rate, a quadratic form in the
 // coefficients through the per-fit matrix M_ij = <B_i conj(B_j)>.
 #pragma once
+#include "accept_device.hpp"
 #include "device_common.hpp"
 #include "fastmath.hpp"
 #include "gram_device.hpp"
@@ -626,64 +627,77 @@ __device__ inline double td4_env(const Td4Const& tc, const Td4Table& tb, double 
 // events above the bound, bad[1] events left NaN.
 template <class S>
 __device__ inline void td4_gen_body(const Td4Const& tc, const Td4Table* __restrict__ tab, const Td4Proposal& pr,
-                                    uint32_t k0, uint32_t k1, int64_t n, double W, int max_attempts,
-                                    double* __restrict__ ev, int64_t ld, unsigned long long* __restrict__ bad) {
+                                    uint32_t k0, uint32_t k1, int64_t n, const double* __restrict__ Wp, int per_wave,
+                                    int max_attempts, double* __restrict__ ev, int64_t ld,
+                                    unsigned long long* __restrict__ bad) {
 #pragma clang fp contract(off)
   constexpr int K = S::K;
-  const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (i >= n) return;
+  __shared__ AcceptLds lds;
+  const double W = *Wp;
+  if (!(W > 0.0 && W < __builtin_inf())) return;  // the host reports it
   const Td4Table& tb = *tab;
   const double G = tc.gamma, x = tb.x, y = tb.y;
   const double lam = G * (1.0 - fabs(y));
-  double out[6];
-  for (int j = 0; j < 6; ++j) out[j] = __builtin_nan("");
-  double ratio = 0.0;
-  for (int a = 0; a < max_attempts; ++a) {
-    double u1, u2, u3, u4, u5, u6, u7, u8, u9, u10;
-    philox_uniforms((uint64_t)i, 5u * a, 4u, k0, k1, u1, u2);
-    philox_uniforms((uint64_t)i, 5u * a + 1u, 4u, k0, k1, u3, u4);
-    philox_uniforms((uint64_t)i, 5u * a + 2u, 4u, k0, k1, u5, u6);
-    philox_uniforms((uint64_t)i, 5u * a + 3u, 4u, k0, k1, u7, u8);
-    philox_uniforms((uint64_t)i, 5u * a + 4u, 4u, k0, k1, u9, u10);
-    const double m12 = td4_prop_draw(pr.p12, u1, u3);
-    const double m34 = td4_prop_draw(pr.p34, u2, u4);
-    if (!(m12 + m34 < tc.M)) continue;
-    const double w = td4_ps_weight(tc, m12, m34);
-    if (!(w > 0.0)) continue;
-    const double c12 = 2.0 * u5 - 1.0, c34 = 2.0 * u6 - 1.0, phi = (2.0 * u7 - 1.0) * 3.14159265358979323846;
-    const double t = -log1p(-u8) / lam;
-    cplx B[K];
-    td4_basis_s<S>(tc, tb, m12, m34, c12, c34, phi, B);
-    cplx A = {0.0, 0.0}, Ab = {0.0, 0.0};
+  double m12, m34, c12, c34, phi, t, ratio;
+  accept_reject(
+      lds, n, per_wave, max_attempts,
+      [&](int64_t i, int a) {
+#pragma clang fp contract(off)
+        double u1, u2, u3, u4, u5, u6, u7, u8, u9, u10;
+        philox_uniforms((uint64_t)i, 5u * a, 4u, k0, k1, u1, u2);
+        philox_uniforms((uint64_t)i, 5u * a + 1u, 4u, k0, k1, u3, u4);
+        m12 = td4_prop_draw(pr.p12, u1, u3);
+        m34 = td4_prop_draw(pr.p34, u2, u4);
+        if (!(m12 + m34 < tc.M)) return false;
+        const double w = td4_ps_weight(tc, m12, m34);
+        if (!(w > 0.0)) return false;
+        philox_uniforms((uint64_t)i, 5u * a + 2u, 4u, k0, k1, u5, u6);
+        philox_uniforms((uint64_t)i, 5u * a + 3u, 4u, k0, k1, u7, u8);
+        philox_uniforms((uint64_t)i, 5u * a + 4u, 4u, k0, k1, u9, u10);
+        c12 = 2.0 * u5 - 1.0;
+        c34 = 2.0 * u6 - 1.0;
+        phi = (2.0 * u7 - 1.0) * 3.14159265358979323846;
+        t = -log1p(-u8) / lam;
+        cplx B[K];
+        td4_basis_s<S>(tc, tb, m12, m34, c12, c34, phi, B);
+        cplx A = {0.0, 0.0}, Ab = {0.0, 0.0};
 #pragma unroll
-    for (int k = 0; k < K; ++k) {
-      const cplx p = cmul({tb.c[k][0], tb.c[k][1]}, B[k]);
-      const cplx q = cmul({tb.cb[k][0], tb.cb[k][1]}, B[k]);
-      A = {A.re + p.re, A.im + p.im};
-      Ab = {Ab.re + q.re, Ab.im + q.im};
-    }
-    const double a2 = A.re * A.re + A.im * A.im, b2 = Ab.re * Ab.re + Ab.im * Ab.im;
-    const double zr = A.re * Ab.re + A.im * Ab.im, zi = A.re * Ab.im - A.im * Ab.re;
-    const double gt = G * t;
-    const double ep = exp(y * gt), em = exp(-y * gt);
-    double sx, cx;
-    sincos(x * gt, &sx, &cx);
-    const double R = 0.5 * exp(-gt) *
-                     ((a2 + b2) * (0.5 * (ep + em)) + (a2 - b2) * cx - 2.0 * zr * (0.5 * (ep - em)) - 2.0 * zi * sx);
-    const double q12 = td4_prop_density(pr.p12, m12), q34 = td4_prop_density(pr.p34, m34);
-    if (u9 * W * q12 * q34 * exp(-lam * t) < w * R) {
-      out[0] = m12; out[1] = m34; out[2] = c12; out[3] = c34; out[4] = phi; out[5] = t;
-      const double e = sqrt(a2) + sqrt(b2);
-      ratio = w * (e * e) / (q12 * q34);
-      break;
-    }
-  }
-  double v1, v2;
-  philox_uniforms((uint64_t)i, 0u, 5u, k0, k1, v1, v2);
-  out[5] = out[5] + tb.sigma * (sqrt(-2.0 * log1p(-v1)) * cos(2.0 * 3.14159265358979323846 * v2));
-  for (int j = 0; j < 6; ++j) ev[j * ld + i] = out[j];
-  if (ratio > W) atomicAdd(bad, 1ull);
-  if (out[0] != out[0]) atomicAdd(bad + 1, 1ull);
+        for (int k = 0; k < K; ++k) {
+          const cplx p = cmul({tb.c[k][0], tb.c[k][1]}, B[k]);
+          const cplx q = cmul({tb.cb[k][0], tb.cb[k][1]}, B[k]);
+          A = {A.re + p.re, A.im + p.im};
+          Ab = {Ab.re + q.re, Ab.im + q.im};
+        }
+        const double a2 = A.re * A.re + A.im * A.im, b2 = Ab.re * Ab.re + Ab.im * Ab.im;
+        const double zr = A.re * Ab.re + A.im * Ab.im, zi = A.re * Ab.im - A.im * Ab.re;
+        const double gt = G * t;
+        const double ep = exp(y * gt), em = exp(-y * gt);
+        double sx, cx;
+        sincos(x * gt, &sx, &cx);
+        const double R = 0.5 * exp(-gt) *
+                         ((a2 + b2) * (0.5 * (ep + em)) + (a2 - b2) * cx - 2.0 * zr * (0.5 * (ep - em)) -
+                          2.0 * zi * sx);
+        const double q12 = td4_prop_density(pr.p12, m12), q34 = td4_prop_density(pr.p34, m34);
+        const double e = sqrt(a2) + sqrt(b2);
+        ratio = w * (e * e) / (q12 * q34);
+        return u9 * W * q12 * q34 * exp(-lam * t) < w * R;
+      },
+      [&](int64_t i) {
+#pragma clang fp contract(off)
+        double v1, v2;
+        philox_uniforms((uint64_t)i, 0u, 5u, k0, k1, v1, v2);
+        ev[i] = m12;
+        ev[ld + i] = m34;
+        ev[2 * ld + i] = c12;
+        ev[3 * ld + i] = c34;
+        ev[4 * ld + i] = phi;
+        ev[5 * ld + i] = t + tb.sigma * (sqrt(-2.0 * log1p(-v1)) * cos(2.0 * 3.14159265358979323846 * v2));
+        if (ratio > W) atomicAdd(bad, 1ull);
+      },
+      [&](int64_t i) {
+        for (int j = 0; j < 6; ++j) ev[j * ld + i] = __builtin_nan("");
+        atomicAdd(bad + 1, 1ull);
+      });
 }
 
 // Largest w (|A| + |Abar|)^2 / (q12 q34) over the points of a phase-space
@@ -692,7 +706,6 @@ template <class S>
 __device__ inline void td4_envmax_body(const Td4Const& tc, const Td4Table* __restrict__ tab, const Td4Proposal& pr,
                                        const double* __restrict__ mc, int64_t ld, int64_t n,
                                        unsigned long long* __restrict__ vmax) {
-  __shared__ double lds[kBlock];
   const Td4Table& tb = *tab;
   double m = 0.0;
   for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < n; i += (int64_t)gridDim.x * kBlock) {
@@ -701,13 +714,7 @@ __device__ inline void td4_envmax_body(const Td4Const& tc, const Td4Table* __res
     const double r = td4_ps_weight(tc, m12, m34) * e / (td4_prop_density(pr.p12, m12) * td4_prop_density(pr.p34, m34));
     m = fmax(m, r);
   }
-  lds[threadIdx.x] = m;
-  __syncthreads();
-  for (int h = kBlock / 2; h > 0; h >>= 1) {
-    if (threadIdx.x < h) lds[threadIdx.x] = fmax(lds[threadIdx.x], lds[threadIdx.x + h]);
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) atomicMax(vmax, (unsigned long long)__double_as_longlong(lds[0]));
+  block_max(m, vmax);
 }
 
 // M = sum over the phase-space sample of B_i conj(B_j) (Gram), one row per
@@ -774,7 +781,7 @@ __device__ inline void td4_gram_body(const Td4Const& tc, const Td4Table* __restr
   }                                                                                                            \
   extern "C" __global__ __launch_bounds__(fn::kBlock) void GEN(                                                \
       fn::Td4Const tc, const fn::Td4Table* __restrict__ tab, fn::Td4Proposal pr, uint32_t k0, uint32_t k1,     \
-      int64_t n, double W, int max_attempts, double* __restrict__ ev, int64_t ld,                              \
-      unsigned long long* __restrict__ bad) {                                                                  \
-    fn::td4_gen_body<S>(tc, tab, pr, k0, k1, n, W, max_attempts, ev, ld, bad);                                 \
+      int64_t n, const double* __restrict__ W, int per_wave, int max_attempts, double* __restrict__ ev,        \
+      int64_t ld, unsigned long long* __restrict__ bad) {                                                      \
+    fn::td4_gen_body<S>(tc, tab, pr, k0, k1, n, W, per_wave, max_attempts, ev, ld, bad);                       \
   }

@@ -223,7 +223,7 @@ void tddp_launch_mmatrices(const TddpJit& j, const DalitzConst& dc, const Dalitz
 void tddp_launch_gridmax(const TddpJit& j, const DalitzConst& dc, const DalitzTable* tab, const double* coef,
                          unsigned long long* vmax, hipStream_t s) {
   const int64_t ncell = (int64_t)dc.nx * dc.ny;
-  const int64_t blocks = std::min<int64_t>((ncell + kBlock - 1) / kBlock, 4096);
+  const int64_t blocks = std::min<int64_t>((ncell + kBlock - 1) / kBlock, kMaxBlocks);
   DalitzConst c = dc;
   const DalitzTable* t = tab;
   const double* cf = coef;
@@ -233,7 +233,7 @@ void tddp_launch_gridmax(const TddpJit& j, const DalitzConst& dc, const DalitzTa
 }
 
 void tddp_launch_gen(const TddpJit& j, const DalitzConst& dc, const DalitzTable* tab, const double* coef,
-                     const TddpTime& tt, uint32_t k0, uint32_t k1, int64_t n, double W, const double box[4],
+                     const TddpTime& tt, uint32_t k0, uint32_t k1, int64_t n, const double* W, const double box[4],
                      int max_attempts, double* ev, int64_t ld, unsigned long long* bad, hipStream_t s) {
   if (n == 0) return;
   DalitzConst c = dc;
@@ -242,12 +242,13 @@ void tddp_launch_gen(const TddpJit& j, const DalitzConst& dc, const DalitzTable*
   TddpTime tm = tt;
   uint32_t a0 = k0, a1 = k1;
   int64_t nn = n, l = ld;
-  double w = W, b0 = box[0], b1 = box[1], b2 = box[2], b3 = box[3];
-  int ma = max_attempts;
+  const double* w = W;
+  double b0 = box[0], b1 = box[1], b2 = box[2], b3 = box[3];
+  int pw = gen_per_wave(n), ma = max_attempts;
   double* e = ev;
   unsigned long long* b = bad;
-  void* args[] = {&c, &t, &cf, &tm, &a0, &a1, &nn, &w, &b0, &b1, &b2, &b3, &ma, &e, &l, &b};
-  jit_launch(j.gen, (unsigned)((n + kBlock - 1) / kBlock), kBlock, s, args);
+  void* args[] = {&c, &t, &cf, &tm, &a0, &a1, &nn, &w, &b0, &b1, &b2, &b3, &pw, &ma, &e, &l, &b};
+  jit_launch(j.gen, gen_blocks(n), kBlock, s, args);
 }
 
 void tddp_launch_events(const TddpJit& j, const DalitzConst& dc, const DalitzTable* tab, const TddpTime& tt,

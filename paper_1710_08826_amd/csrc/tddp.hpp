@@ -38,7 +38,7 @@ void tddp_launch_finalize(const DalitzConst& dc, const DalitzTable* tab, const T
 void tddp_launch_gridmax(const TddpJit& j, const DalitzConst& dc, const DalitzTable* tab, const double* coef,
                          unsigned long long* vmax, hipStream_t s);
 void tddp_launch_gen(const TddpJit& j, const DalitzConst& dc, const DalitzTable* tab, const double* coef,
-                     const TddpTime& tt, uint32_t k0, uint32_t k1, int64_t n, double W, const double box[4],
+                     const TddpTime& tt, uint32_t k0, uint32_t k1, int64_t n, const double* W, const double box[4],
                      int max_attempts, double* ev, int64_t ld, unsigned long long* bad, hipStream_t s);
 // theta (P doubles) passed by value -> device copy.
 void tddp_launch_copy_theta(const ParamBlock& pb, int P, double* dst, hipStream_t s);
