@@ -268,31 +268,6 @@ __global__ __launch_bounds__(kBlock) void gram_finalize(const double* __restrict
   if (i != j) out[2 * (j * ldm + i) + im] = im ? -a : a;
 }
 
-// P~(x_i)/I per event (I read from the finalize output).
-__global__ void dalitz_eval(DalitzConst dc, const DalitzTable* __restrict__ tab, const double* __restrict__ ev,
-                            int64_t ld, int64_t n, const double* __restrict__ norm, double* __restrict__ p) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const double s12 = ev[i], s13 = ev[ld + i];
-  const double s23 = dc.msum - s12 - s13;
-  PairTerms pt[3];
-  pair_terms(dc.ch[0], s12, s13, s23, dc.r2, dc.rD2, pt[0]);
-  pair_terms(dc.ch[1], s13, s12, s23, dc.r2, dc.rD2, pt[1]);
-  pair_terms(dc.ch[2], s23, s12, s13, dc.r2, dc.rD2, pt[2]);
-  double Sre = 0.0, Sim = 0.0;
-  for (int k = 0; k < dc.K; ++k) {
-    const PairTerms& q = pt[dc.chan[k]];
-    const double* rk = tab->r[k];
-    const double a = rk[dM0SQ] - q.s, b = rk[dKW] * q.G[dc.L[k]];
-    const double d = 1.0 / (a * a + b * b);
-    const double kh = rk[dKA] * q.H[dc.L[k]];
-    const double ar = kh * a * d, ai = kh * b * d;
-    Sre += rk[dCRE] * ar - rk[dCIM] * ai;
-    Sim += rk[dCRE] * ai + rk[dCIM] * ar;
-  }
-  p[i] = (Sre * Sre + Sim * Sim) / *norm;
-}
-
 __global__ void dalitz_check(DalitzConst dc, const double* __restrict__ ev, int64_t ld, int64_t n,
                              unsigned long long* __restrict__ bad) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -425,7 +400,7 @@ std::string dalitz_jit_source(const DalitzConst& dc, int ept) {
          "FN_DALITZ_KERNEL(fn_dal_gr0, fn_shape, fn::kGrid, 0, 1)\n"
          "FN_DALITZ_KERNEL(fn_dal_gr2, fn_shape, fn::kGrid, 2, 1)\n";
   }
-  o << "FN_DALITZ_GEN(fn_dal_gmax, fn_dal_gen, fn_shape)\n";
+  o << "FN_DALITZ_GEN(fn_dal_gmax, fn_dal_gen, fn_shape)\nFN_DALITZ_EVAL(fn_dal_eval, fn_shape)\n";
   return o.str();
 }
 
@@ -444,6 +419,7 @@ std::shared_ptr<DalitzJit> dalitz_jit(const DalitzConst& dc, int ept) {
   const size_t ngen = names.size();
   names.push_back("fn_dal_gmax");
   names.push_back("fn_dal_gen");
+  names.push_back("fn_dal_eval");
   j->prog = jit_load(dalitz_jit_source(dc, 1), names);
   const auto& f = j->prog->fns;
   if (!dc.free_ls) {
@@ -458,6 +434,7 @@ std::shared_ptr<DalitzJit> dalitz_jit(const DalitzConst& dc, int ept) {
   }
   j->gmax = f[ngen];
   j->gen = f[ngen + 1];
+  j->eval = f[ngen + 2];
   return j;
 }
 
@@ -615,10 +592,16 @@ void dalitz_launch_gen(const DalitzJit& j, const DalitzConst& dc, const DalitzTa
   jit_launch(j.gen, gen_blocks(n), kBlock, s, args);
 }
 
-void dalitz_launch_eval(const DalitzConst& dc, const DalitzTable* tab, const double* ev, int64_t ld, int64_t n,
-                        const double* norm, double* p, hipStream_t s) {
+void dalitz_launch_eval(const DalitzJit& j, const DalitzConst& dc, const DalitzTable* tab, const double* ev,
+                        int64_t ld, int64_t n, const double* norm, double* p, hipStream_t s) {
   if (n == 0) return;
-  hipLaunchKernelGGL(dalitz_eval, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, dc, tab, ev, ld, n, norm, p);
+  DalitzConst c = dc;
+  const DalitzTable* t = tab;
+  const double *e = ev, *no = norm;
+  int64_t l = ld, nn = n;
+  double* o = p;
+  void* args[] = {&c, &t, &e, &l, &nn, &no, &o};
+  jit_launch(j.eval, (unsigned)((n + kBlock - 1) / kBlock), kBlock, s, args);
 }
 
 void dalitz_launch_check(const DalitzConst& dc, const double* ev, int64_t ld, int64_t n, unsigned long long* bad,

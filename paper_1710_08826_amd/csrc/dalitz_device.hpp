@@ -95,18 +95,6 @@ __device__ __forceinline__ void pair_terms_t(const DalitzChan& ch, double s_ab, 
   pair_terms_is<U1, U2>(ch, s_ab, rcp_fast(s_ab), s_ac, s_bc, r2, rD2, o);
 }
 
-// The same with the spins used by the pair given at run time.
-__device__ __forceinline__ void pair_terms(const DalitzChan& ch, double s_ab, double s_ac, double s_bc, double r2,
-                                           double rD2, PairTerms& o) {
-  if (ch.useL[2]) {
-    if (ch.useL[1]) pair_terms_t<true, true>(ch, s_ab, s_ac, s_bc, r2, rD2, o);
-    else pair_terms_t<false, true>(ch, s_ab, s_ac, s_bc, r2, rD2, o);
-  } else {
-    if (ch.useL[1]) pair_terms_t<true, false>(ch, s_ab, s_ac, s_bc, r2, rD2, o);
-    else pair_terms_t<false, false>(ch, s_ab, s_ac, s_bc, r2, rD2, o);
-  }
-}
-
 // Centre of cell i along a grid axis that starts at a with cells of size d,
 // as the plain IEEE evaluation (no contraction), so that every pass and the
 // cell list see the same bits.
@@ -471,6 +459,24 @@ __device__ __forceinline__ double dalitz_value(const DalitzConst& dc, const doub
   return __builtin_fma(Sre, Sre, Sim * Sim);
 }
 
+// P~(x_i) / I per event (I: the level-2 step's output): the events pass's own
+// amplitudes for the model's structure, one event per thread.  Bound by their
+// FP64 instructions, as that pass.
+template <class S>
+__device__ inline void dalitz_eval_body(const DalitzConst& dc, const DalitzTable* __restrict__ tab,
+                                        const double* __restrict__ ev, int64_t ld, int64_t n,
+                                        const double* __restrict__ norm, double* __restrict__ p) {
+  constexpr int K = S::K;
+  const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  if (i >= n) return;
+  const double s12 = ev[i], s13 = ev[ld + i];
+  double Are[K], Aim[K], Tre[K], Tim[K], Gk[K];
+  double Sre = 0.0, Sim = 0.0;
+  dalitz_amps<S, false, false>(dc, &tab->r[0][0], (cdouble*)tab->coef, s12, s13, dc.msum - s12 - s13, Are,
+                               Aim, Tre, Tim, Gk, Sre, Sim);
+  p[i] = __builtin_fma(Sre, Sre, Sim * Sim) / *norm;
+}
+
 // Largest P~ over the centres of the grid cells inside the region, as the
 // bit pattern of a non-negative double (ordered like the value) in *vmax.
 template <class S>
@@ -545,6 +551,14 @@ __device__ inline void dalitz_gen_body(const DalitzConst& dc, const DalitzTable*
       unsigned long long* __restrict__ span) {                                                                 \
     fn::cdouble* c = coef ? (fn::cdouble*)coef : (fn::cdouble*)&ca.v[0];                                       \
     fn::dalitz_pass_body<S, MODE, GRAD, EPT>(dc, tab, c, ev, ld, n, chunk, part, M, norm_out, span);       \
+  }
+
+// Density per event for shape S.
+#define FN_DALITZ_EVAL(NAME, S)                                                                               \
+  extern "C" __global__ __launch_bounds__(fn::kBlock) void NAME(                                               \
+      fn::DalitzConst dc, const fn::DalitzTable* __restrict__ tab, const double* __restrict__ ev, int64_t ld,  \
+      int64_t n, const double* __restrict__ norm, double* __restrict__ p) {                                    \
+    fn::dalitz_eval_body<S>(dc, tab, ev, ld, n, norm, p);                                                      \
   }
 
 // Matrix pass for shape S.

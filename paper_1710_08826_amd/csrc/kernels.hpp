@@ -47,6 +47,7 @@ struct DalitzJit {
   hipFunction_t gr[3] = {nullptr, nullptr, nullptr};
   hipFunction_t gram = nullptr;                 // normalization matrix of fixed lineshapes
   hipFunction_t gmax = nullptr, gen = nullptr;  // toy generation: grid maximum, accept-reject
+  hipFunction_t eval = nullptr;                 // density per event
 };
 // ept: events per thread and loop iteration of the events passes (1, or 2
 // for a module with the events passes alone).
@@ -136,8 +137,8 @@ void dalitz_launch_gridmax(const DalitzJit& j, const DalitzConst& dc, const Dali
 void dalitz_launch_gen(const DalitzJit& j, const DalitzConst& dc, const DalitzTable* tab, uint32_t k0, uint32_t k1,
                        int64_t n, const double* W, const double box[4], int max_attempts, double* ev, int64_t ld,
                        unsigned long long* bad, hipStream_t s);
-void dalitz_launch_eval(const DalitzConst& dc, const DalitzTable* tab, const double* ev, int64_t ld, int64_t n,
-                        const double* norm, double* p, hipStream_t s);
+void dalitz_launch_eval(const DalitzJit& j, const DalitzConst& dc, const DalitzTable* tab, const double* ev,
+                        int64_t ld, int64_t n, const double* norm, double* p, hipStream_t s);
 void dalitz_launch_check(const DalitzConst& dc, const double* ev, int64_t ld, int64_t n, unsigned long long* bad,
                          hipStream_t s);
 

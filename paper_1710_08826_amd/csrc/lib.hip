@@ -1063,8 +1063,8 @@ fn_status fn_eval(fn_model* m, const double* theta_host, const double* ev, int64
     const ParamBlock pb = make_block(m, theta_host);
     run_nll(m, &pb, nullptr, nullptr, 0, 0, false, nullptr, s);
     if (m->kind == kKindMix1d) mix1d_launch_eval(m->mix, m->table_mix(), ev, n, p_dev, s);
-    else if (m->kind == kKindTd4) td4_launch_eval(m->td4, m->table_td4(), ev, ld, n, m->out() + 1 + m->P, p_dev, s);
-    else dalitz_launch_eval(m->dal, m->table_dal(), ev, ld, n, m->out() + 1 + m->P, p_dev, s);
+    else if (m->kind == kKindTd4) td4_launch_eval(*m->td4_jit, m->td4, m->table_td4(), ev, ld, n, m->out() + 1 + m->P, p_dev, s);
+    else dalitz_launch_eval(*m->dal_jit, m->dal, m->table_dal(), ev, ld, n, m->out() + 1 + m->P, p_dev, s);
     hip_check(hipGetLastError(), "kernel launch");
     hip_check(hipStreamSynchronize(s), "hipStreamSynchronize");
   });

@@ -1,7 +1,7 @@
 // Time-dependent four-body amplitude model (the paper's four-body
 // time-dependent amplitude analyses, Abstract and Sec. 5): host launchers and
 // the kernels that do not depend on the model's shape (prologue, level-2
-// finalize, per-event density, domain check).  The per-event and
+// finalize, domain check).  The per-event and
 // normalization-matrix passes live in td4_device.hpp and are compiled at model
 // creation with the model's shape as compile-time constants (td4_jit below).
 #include <algorithm>
@@ -17,70 +17,6 @@
 #include "td4_device.hpp"
 
 namespace fn {
-
-// Lineshapes of one pair from its invariant mass m: amp[r] for every resonance of the pair.
-template <int NR>
-__device__ __forceinline__ void pair_amps(double m, double sum2, double dif2, double r2, const int* L, const int* nr,
-                                          int n, const double (*rt)[3], cplx (&amp)[NR]) {
-  const double s = m * m;
-  const double im = rcp_fast(m);
-  const double lq = fmax((s - sum2) * (s - dif2), 0.0);
-  const double q2 = 0.25 * lq * im * im;
-  const double q = sqrt_fast(q2);
-  const double G0 = q * im;
-  const double z = q2 * r2;
-  const double F1 = rsqrt_fast(1.0 + z);
-  const double G1 = G0 * q2 * F1 * F1;
-#pragma unroll
-  for (int r = 0; r < NR; ++r) {
-    amp[r] = {1.0, 0.0};
-    if (r < n && !nr[r]) {
-      const bool l1 = L[r] == 1;
-      const double G = l1 ? G1 : G0;
-      const double F = l1 ? F1 : 1.0;
-      const double a = rt[r][0] - s;
-      const double b = rt[r][1] * G;
-      const double d = rcp_fast(__builtin_fma(a, a, b * b));
-      const double k = rt[r][2] * F * d;
-      amp[r] = {k * a, k * b};
-    }
-  }
-}
-
-// Basis amplitudes B_k of one kinematic point under one fit's lineshapes.
-template <int KMAX>
-__device__ __forceinline__ void td4_basis(const Td4Const& tc, const Td4Table& tb, double m12, double m34, double c12,
-                                          double c34, double phi, cplx (&B)[KMAX]) {
-  cplx a12[kTd4MaxRes], a34[kTd4MaxRes];
-  pair_amps<kTd4MaxRes>(m12, tc.sum12, tc.dif12, tc.r2, tc.L12, tc.nr12, tc.n12, tb.r12, a12);
-  pair_amps<kTd4MaxRes>(m34, tc.sum34, tc.dif34, tc.r2, tc.L34, tc.nr34, tc.n34, tb.r34, a34);
-  const double ss = 0.5 * sqrt_fast(fmax(1.0 - c12 * c12, 0.0)) * sqrt_fast(fmax(1.0 - c34 * c34, 0.0));
-  double sp, cp;
-  sincos(phi, &sp, &cp);
-#pragma unroll
-  for (int k = 0; k < KMAX; ++k) {
-    B[k] = {0.0, 0.0};
-    if (k < tc.K) {
-      cplx x = a12[0], y = a34[0];
-#pragma unroll
-      for (int r = 1; r < kTd4MaxRes; ++r) {
-        if (tc.amp1[k] == r) x = a12[r];
-        if (tc.amp2[k] == r) y = a34[r];
-      }
-      const cplx xy = cmul(x, y);
-      cplx om;
-      switch (tc.atype[k]) {
-        case 0: om = {1.0, 0.0}; break;
-        case 1: om = {c34, 0.0}; break;
-        case 2: om = {c12, 0.0}; break;
-        case 3: om = {c12 * c34, 0.0}; break;
-        case 4: om = {ss * cp, ss * sp}; break;
-        default: om = {ss * cp, -ss * sp}; break;
-      }
-      B[k] = cmul(xy, om);
-    }
-  }
-}
 
 // --------------------------------------------------------------- prologue
 // One 64-thread workgroup per fit, each table entry written by its own thread
@@ -284,29 +220,6 @@ __global__ void td4_check(Td4Const tc, const double* __restrict__ ev, int64_t ld
   if ((threadIdx.x & 63) == 0 && cnt) atomicAdd(bad, (unsigned long long)__popcll(cnt));
 }
 
-// R(x_i, t_i) / I per event (I read from the finalize output).
-__global__ void td4_eval(Td4Const tc, const Td4Table* __restrict__ tab, const double* __restrict__ ev, int64_t ld,
-                         int64_t n, const double* __restrict__ norm, double* __restrict__ p) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const Td4Table& tb = *tab;
-  cplx B[kTd4MaxAmp];
-  td4_basis<kTd4MaxAmp>(tc, tb, ev[i], ev[ld + i], ev[2 * ld + i], ev[3 * ld + i], ev[4 * ld + i], B);
-  cplx A = {0.0, 0.0}, Ab = {0.0, 0.0};
-  for (int k = 0; k < tc.K; ++k) {
-    const cplx x = cmul({tb.c[k][0], tb.c[k][1]}, B[k]);
-    const cplx y = cmul({tb.cb[k][0], tb.cb[k][1]}, B[k]);
-    A = {A.re + x.re, A.im + x.im};
-    Ab = {Ab.re + y.re, Ab.im + y.im};
-  }
-  TimeFns T;
-  time_fns<false>(tb.tk, tc.wa, tc.wL, tb.x, tb.y, ev[5 * ld + i], T);
-  const double a2 = A.re * A.re + A.im * A.im, b2 = Ab.re * Ab.re + Ab.im * Ab.im;
-  const double zr = A.re * Ab.re + A.im * Ab.im, zi = A.re * Ab.im - A.im * Ab.re;
-  const double R = 0.5 * ((a2 + b2) * T.Hc + (a2 - b2) * T.hr - 2.0 * zr * T.Hs - 2.0 * zi * T.hi);
-  p[i] = R / *norm;
-}
-
 // ---------------------------------------------------------------- launchers
 int td4_kmax(int K) { return K; }  // partial rows hold exactly the model's amplitudes
 int td4_nv(const Td4Const& tc, bool grad) { return grad ? 1 + tc.n_params : 1; }
@@ -379,18 +292,21 @@ std::string td4_jit_source(const Td4Const& tc) {
        "FN_TD4_EVENTS(fn_td4_ev0, fn_td4_shape, false)\n"
        "FN_TD4_EVENTS(fn_td4_ev1, fn_td4_shape, true)\n"
        "FN_TD4_GRAM(fn_td4_gram, fn_td4_shape)\n"
+       "FN_TD4_EVAL(fn_td4_eval, fn_td4_shape)\n"
        "FN_TD4_GEN(fn_td4_envmax, fn_td4_gen, fn_td4_shape)\n";
   return o.str();
 }
 
 std::shared_ptr<Td4Jit> td4_jit(const Td4Const& tc) {
   auto j = std::make_shared<Td4Jit>();
-  j->prog = jit_load(td4_jit_source(tc), {"fn_td4_ev0", "fn_td4_ev1", "fn_td4_gram", "fn_td4_envmax", "fn_td4_gen"});
+  j->prog = jit_load(td4_jit_source(tc), {"fn_td4_ev0", "fn_td4_ev1", "fn_td4_gram", "fn_td4_envmax", "fn_td4_gen",
+                                            "fn_td4_eval"});
   j->ev[0] = j->prog->fns[0];
   j->ev[1] = j->prog->fns[1];
   j->gram = j->prog->fns[2];
   j->envmax = j->prog->fns[3];
   j->gen = j->prog->fns[4];
+  j->eval = j->prog->fns[5];
   return j;
 }
 
@@ -442,10 +358,16 @@ void td4_launch_finalize(const Td4Const& tc, const Td4Table* tabs, const int* st
                      td4_nv(tc, grad), kmax, grad ? 1 : 0, Mc, n_events, out, out_stride, out_user);
 }
 
-void td4_launch_eval(const Td4Const& tc, const Td4Table* tab, const double* ev, int64_t ld, int64_t n,
-                     const double* norm, double* p, hipStream_t s) {
+void td4_launch_eval(const Td4Jit& j, const Td4Const& tc, const Td4Table* tab, const double* ev, int64_t ld,
+                     int64_t n, const double* norm, double* p, hipStream_t s) {
   if (n == 0) return;
-  hipLaunchKernelGGL(td4_eval, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, tc, tab, ev, ld, n, norm, p);
+  Td4Const c = tc;
+  const Td4Table* t = tab;
+  const double *e = ev, *no = norm;
+  int64_t l = ld, nn = n;
+  double* o = p;
+  void* args[] = {&c, &t, &e, &l, &nn, &no, &o};
+  jit_launch(j.eval, (unsigned)((n + kBlock - 1) / kBlock), kBlock, s, args);
 }
 
 // ------------------------------------------------------- phase-space sample

@@ -15,6 +15,7 @@ struct Td4Jit {
   hipFunction_t ev[2] = {nullptr, nullptr};  // without, with the gradient
   hipFunction_t gram = nullptr;  // normalization matrix
   hipFunction_t envmax = nullptr, gen = nullptr;  // toy generation
+  hipFunction_t eval = nullptr;  // density per event
 };
 std::string td4_jit_source(const Td4Const& tc);
 std::shared_ptr<Td4Jit> td4_jit(const Td4Const& tc);
@@ -65,7 +66,7 @@ void td4_launch_finalize(const Td4Const& tc, const Td4Table* tabs, const int* st
                          int out_stride, double* out_user, hipStream_t s);
 void td4_launch_check(const Td4Const& tc, const double* ev, int64_t ld, int64_t n, unsigned long long* bad,
                       hipStream_t s);
-void td4_launch_eval(const Td4Const& tc, const Td4Table* tab, const double* ev, int64_t ld, int64_t n,
-                     const double* norm, double* p, hipStream_t s);
+void td4_launch_eval(const Td4Jit& j, const Td4Const& tc, const Td4Table* tab, const double* ev, int64_t ld,
+                     int64_t n, const double* norm, double* p, hipStream_t s);
 
 }  // namespace fn

@@ -269,12 +269,21 @@ struct Td4Pair {
   }
 };
 
+// m^2 rounded by itself, as the reference evaluation in 64 bits has it: formed
+// inside an FMA, m0^2 - m^2 keeps the square's rounding, which next to a narrow
+// peak is a difference of 1e-14 in the density.
+__device__ __forceinline__ double sq_rn(double m) {
+#pragma clang fp contract(off)
+  const double s = m * m;
+  return s;
+}
+
 // Lineshapes of one pair from its invariant mass m (rt: the fit's m0^2, Kw, Ka).
 template <class S, bool P34>
 __device__ __forceinline__ void pair_amps_s(double m, double sum2, double dif2, double r2,
                                             const double (*__restrict__ rt)[3], cplx (&amp)[Td4Pair<S, P34>::N]) {
   using T = Td4Pair<S, P34>;
-  const double s = m * m;
+  const double s = sq_rn(m);
   const double im = rcp_fast(m);
   const double lq = fmax((s - sum2) * (s - dif2), 0.0);
   const double q2 = 0.25 * lq * im * im;
@@ -550,6 +559,29 @@ __device__ inline void td4_events_body(const Td4Const& tc, const Td4Table* __res
   block_sum_row<NV>(acc, lds, part + ((int64_t)f * nch + ch) * NV);
 }
 
+// R(x_i, t_i) / I per event (I: the level-2 step's output): the events pass's
+// own point, sums and time functions, one event per thread.  A generic kernel
+// with the structure at run time kept its amplitude arrays in scratch memory:
+// 1M events, ten amplitudes and their ten mirror images, 172 us a call
+// against 45 here, both with the 9 us of the normalization's level-2 step.
+template <class S>
+__device__ inline void td4_eval_body(const Td4Const& tc, const Td4Table* __restrict__ tab,
+                                     const double* __restrict__ ev, int64_t ld, int64_t n,
+                                     const double* __restrict__ norm, double* __restrict__ p) {
+  const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  const int64_t q = i < n ? i : n - 1;  // all lanes run: the time functions vote by wave
+  const Td4Table& tb = *tab;
+  TimeFns T;
+  time_fns<false>(tb.tk, tc.wa, tc.wL, tb.x, tb.y, ev[5 * ld + q], T);
+  Td4Point<S> pt;
+  td4_point_s<S>(tc, tb, ev[q], ev[ld + q], ev[2 * ld + q], ev[3 * ld + q], ev[4 * ld + q], pt);
+  const cplx A = td4_sum<S, 0>(pt, tb.c), Ab = td4_sum<S, 1>(pt, tb.cb);
+  const double a2 = A.re * A.re + A.im * A.im, b2 = Ab.re * Ab.re + Ab.im * Ab.im;
+  const double zr = A.re * Ab.re + A.im * Ab.im, zi = A.re * Ab.im - A.im * Ab.re;
+  const double R = 0.5 * ((a2 + b2) * T.Hc + (a2 - b2) * T.hr - 2.0 * zr * T.Hs - 2.0 * zi * T.hi);
+  if (i < n) p[i] = R / *norm;
+}
+
 // ------------------------------------------------------ four-body phase space
 // Two-body momentum q(m; ma, mb) and the phase-space weight of (m12, m34)
 // with the angles uniform: q(M; m12, m34) q(m12; m1, m2) q(m34; m3, m4).
@@ -765,6 +797,12 @@ __device__ inline void td4_gram_body(const Td4Const& tc, const Td4Table* __restr
       const double* __restrict__ ev, int64_t ld, int64_t n, int chunk, int64_t nch, int n_fits,                \
       double* __restrict__ part) {                                                                              \
     fn::td4_events_body<S, GRAD>(tc, tabs, status, ev, ld, n, chunk, nch, n_fits, part);                       \
+  }
+#define FN_TD4_EVAL(NAME, S)                                                                                   \
+  extern "C" __global__ __launch_bounds__(fn::kBlock) void NAME(                                                \
+      fn::Td4Const tc, const fn::Td4Table* __restrict__ tab, const double* __restrict__ ev, int64_t ld,        \
+      int64_t n, const double* __restrict__ norm, double* __restrict__ p) {                                     \
+    fn::td4_eval_body<S>(tc, tab, ev, ld, n, norm, p);                                                          \
   }
 #define FN_TD4_GRAM(NAME, S)                                                                                   \
   extern "C" __global__ __launch_bounds__(fn::kBlock) void NAME(                                                \
