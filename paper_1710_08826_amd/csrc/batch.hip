@@ -4,15 +4,21 @@
 // trial point, followed by one state-machine step of BFGS with a strong-Wolfe
 // line search (Nocedal & Wright, Alg. 3.5/3.6) per fit:
 //
-//   batch_prologue   per running fit: theta_trial -> mix1d table
-//   batch_scan       exclusive scan of the running fits' chunk counts ->
-//                    item bases, total item count, running-fit count
-//   batch_eval       persistent kernel over (fit, chunk) items; each item runs
-//                    the single-fit chunk routine, so rows are bitwise those of
-//                    fn_nll for the same fit
-//   batch_finalize   per running fit: fixed-order level-2 sum -> NLL, gradient
-//   batch_bfgs       per running fit: accept/reject the trial, update H, pick
-//                    the next trial point, or retire (converged / failed)
+//   batch_head    per running fit: theta_trial -> mix1d table; in one more
+//                 workgroup: exclusive scan of the running fits' chunk counts
+//                 -> item bases, total item count, running-fit count
+//   batch_eval    persistent kernel over (fit, chunk) items; each item runs
+//                 the single-fit chunk routine, so rows are bitwise those of
+//                 fn_nll for the same fit
+//   batch_tail    one workgroup per running fit: fixed-order level-2 sum ->
+//                 NLL, gradient; then accept/reject the trial, update H, pick
+//                 the next trial point, or retire (converged / failed)
+//
+// Launches of a few microseconds each (table 5.3, scan 4.1, level 2 3.9,
+// minimizer 9.2: threads of one wave took the phases of their fits one after
+// the other, from device memory) were a third of a step of 512 fits; in two
+// launches, each fit's minimizer in its own workgroup on a copy in LDS, they
+// take 5.6 and 7.0 (up to 12 with numerical Hessians under way, 18 before).
 //
 // No host synchronisation inside a step; the host polls the running-fit
 // count between groups of steps.  Fits never interact, so a fit's trajectory
@@ -108,9 +114,11 @@ __global__ __launch_bounds__(kBlock) void batch_admit(const AdmitRec* __restrict
 }
 
 // fn_batch_set: workgroup f resets slot f -- a fresh fit at theta0[f] (all
-// parameters free) for f < n_fits, idle beyond; event pointers and counts are
-// copied separately.
-__global__ __launch_bounds__(kBlock) void batch_set_kernel(const double* __restrict__ theta0, int n_fits, int P,
+// parameters free) for f < n_fits, idle beyond; its event pointer and count come
+// from the host's staging arrays (pinned, read in place: 16 bytes a slot).
+__global__ __launch_bounds__(kBlock) void batch_set_kernel(const double* __restrict__ theta0,
+                                                           const double* const* __restrict__ h_ev,
+                                                           const int64_t* __restrict__ h_nev, int n_fits, int P,
                                                            BatchDev b) {
   const int f = blockIdx.x;
   uint64_t* w = reinterpret_cast<uint64_t*>(b.st + f);
@@ -128,11 +136,15 @@ __global__ __launch_bounds__(kBlock) void batch_set_kernel(const double* __restr
       st.phase = kPhaseStart;
     }
     b.stat[f] = f < n_fits ? kFitRunning : kFitIdle;
+    b.ev[f] = h_ev[f];
+    b.nev[f] = h_nev[f];
   }
 }
 
-void batch_launch_set(const BatchDev& b, const double* theta0, int n_fits, int max_fits, int P, hipStream_t s) {
-  hipLaunchKernelGGL(batch_set_kernel, dim3((unsigned)max_fits), dim3(kBlock), 0, s, theta0, n_fits, P, b);
+void batch_launch_set(const BatchDev& b, const double* theta0, const double* const* h_ev, const int64_t* h_nev,
+                      int n_fits, int max_fits, int P, hipStream_t s) {
+  hipLaunchKernelGGL(batch_set_kernel, dim3((unsigned)max_fits), dim3(kBlock), 0, s, theta0, h_ev, h_nev, n_fits, P,
+                     b);
 }
 
 __global__ void batch_gather_rows(const double* __restrict__ rres, const int* __restrict__ slots, int n, int w,
@@ -144,26 +156,19 @@ __global__ void batch_gather_rows(const double* __restrict__ rres, const int* __
 }
 
 // ------------------------------------------------------------------ steps
-__global__ void batch_prologue(Mix1dConst mc, const BfgsState* __restrict__ st, const int* __restrict__ stat,
-                               int n_fits, Mix1dTable* __restrict__ tabs) {
-  const int f = blockIdx.x * blockDim.x + threadIdx.x;
-  if (f >= n_fits || stat[f] != kFitRunning) return;
-  mix1d_table(mc, st[f].xt, tabs[f]);
-}
-
 __device__ __forceinline__ int64_t chunks_of(const ChunkRule& rule, int64_t n) {
   const int c = rule(n);
   return (n + c - 1) / c;
 }
 
-// Single workgroup: item_base[f] = sum of chunk counts of running fits < f;
-// item_base[n_fits] = total; *n_running = number of running fits.  Thread t
+// One workgroup: item_base[f] = sum of chunk counts of running fits < f;
+// item_base[n_fits] = total; *n_running = number of running fits (in host
+// memory, where the host reads it once the stream is idle).  Thread t
 // takes a contiguous run of fits; the exclusive scan of the per-thread sums
 // (thread order) is a shuffle scan within each wave plus the totals of the
 // preceding waves: exact integer sums, the same as a serial loop.
-__global__ __launch_bounds__(kBlock) void batch_scan(const int* __restrict__ stat, const int64_t* __restrict__ nev,
-                                                     int n_fits, ChunkRule rule, int64_t* __restrict__ item_base,
-                                                     int* __restrict__ n_running) {
+__device__ inline void batch_scan(const int* __restrict__ stat, const int64_t* __restrict__ nev, int n_fits,
+                                  const ChunkRule& rule, int64_t* __restrict__ item_base, int* __restrict__ n_running) {
   constexpr int kWaves = kBlock / 64;
   __shared__ int64_t wsum[kWaves];
   __shared__ int wcnt[kWaves];
@@ -211,6 +216,54 @@ __global__ __launch_bounds__(kBlock) void batch_scan(const int* __restrict__ sta
   }
 }
 
+// Workgroup 0 scans; the others make the tables of 64 fits each, component k
+// in wave k % 4 (different shapes in one wave would run one after the other).
+__global__ __launch_bounds__(kBlock) void batch_head(Mix1dConst mc, const BfgsState* __restrict__ st,
+                                                     const int* __restrict__ stat, const int64_t* __restrict__ nev,
+                                                     int n_fits, ChunkRule rule, Mix1dTable* __restrict__ tabs,
+                                                     int64_t* __restrict__ item_base, int* __restrict__ n_running) {
+  if (blockIdx.x == 0) {
+    batch_scan(stat, nev, n_fits, rule, item_base, n_running);
+    return;
+  }
+  __shared__ int bad[64];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int f = ((int)blockIdx.x - 1) * 64 + lane;
+  const bool run = f < n_fits && stat[f] == kFitRunning;
+  if (w == 0) bad[lane] = 0;
+  __syncthreads();
+  if (run) {
+    for (int k = w; k < mc.K; k += kBlock / 64)
+      if (!mix1d_component(mc, st[f].xt, k, tabs[f])) bad[lane] = 1;
+  }
+  __syncthreads();
+  if (run && w == 0) mix1d_table_rest(mc, st[f].xt, bad[lane] == 0, tabs[f]);
+}
+
+// The fit f >= lo with item_base[f] <= it < item_base[f+1] (fits that don't run
+// have empty ranges, so the search lands on a running one).  The wave looks at
+// 64 entries per round: two dependent loads for 4096 fits.
+__device__ __forceinline__ int fit_of_item(const int64_t* __restrict__ item_base, int64_t it, int lo, int n_fits) {
+  const int lane = threadIdx.x & 63;
+  int hi = n_fits;  // invariant: item_base[lo] <= it < item_base[hi]
+  while (hi - lo > 1) {
+    const int step = (hi - lo + 63) >> 6;
+    const int i = lo + lane * step;
+    const int below = __popcll(__ballot(i < hi && item_base[i < hi ? i : lo] <= it));
+    lo += (below - 1) * step;
+    hi = min(lo + step, hi);
+  }
+  return lo;
+}
+
+// Each workgroup takes one contiguous run of items (sizes differ by one at
+// most), so it looks for its fit once and then walks on.  One item at a time,
+// each with its own binary search, left the workgroups waiting: a step of 512
+// fits of 1e3 to 2e5 events (19M in all), 74 -> 62 us.  Bound by a chunk's
+// fixed part (four events per thread, then the row's sum): handing runs out
+// from a counter (2.13 -> 2.60 ms for the whole set of fits: the counter's
+// atomics), requesting the next chunk's events ahead and shorter sums of the
+// row were no faster.
 template <bool GRAD, int KMAX, int SIG>
 __global__ __launch_bounds__(kBlock) void batch_eval(Mix1dConst mc, const Mix1dTable* __restrict__ tabs,
                                                      const double* const* __restrict__ ev,
@@ -221,36 +274,84 @@ __global__ __launch_bounds__(kBlock) void batch_eval(Mix1dConst mc, const Mix1dT
   constexpr int NV = GRAD ? mix_nv(KMAX) : 1;
   __shared__ double lds[block_sum_lds(NV)];
   const int64_t total = item_base[n_fits];
-  for (int64_t it = blockIdx.x; it < total; it += gridDim.x) {
-    // fit f with item_base[f] <= it < item_base[f+1] (non-running fits have
-    // empty ranges, so the search lands on a running fit)
-    int lo = 0, hi = n_fits;  // invariant: item_base[lo] <= it < item_base[hi]
-    while (hi - lo > 1) {
-      const int mid = (lo + hi) >> 1;
-      if (item_base[mid] <= it) lo = mid;
-      else hi = mid;
+  const int64_t each = total / gridDim.x;
+  const int more = (int)(total - each * gridDim.x);  // workgroups with one item more
+  const int b = blockIdx.x;
+  int64_t it = b * each + min(b, more);
+  const int64_t last = it + each + (b < more ? 1 : 0);
+  int f = 0;
+  while (it < last) {
+    f = fit_of_item(item_base, it, f, n_fits);
+    const int64_t base = item_base[f], stop = min(last, item_base[f + 1]);
+    const int64_t n = nev[f];
+    const int chunk = rule(n);
+    const double* x = ev[f];
+    double* rows = part + part_base[f] * NV;
+    for (; it < stop; ++it) {
+      mix1d_chunk<GRAD, KMAX, SIG>(mc, tabs + f, x, n, it - base, chunk, rows + (it - base) * NV, lds);
+      __syncthreads();
     }
-    const int f = lo;
-    const int64_t ch = it - item_base[f];
-    mix1d_chunk<GRAD, KMAX, SIG>(mc, tabs + f, ev[f], nev[f], ch, rule(nev[f]), part + (part_base[f] + ch) * NV, lds);
-    __syncthreads();
+    ++f;
   }
 }
 
-__global__ __launch_bounds__(kBlock) void batch_finalize(Mix1dConst mc, const Mix1dTable* __restrict__ tabs,
-                                                         const int* __restrict__ stat,
-                                                         const int64_t* __restrict__ nev,
-                                                         const int64_t* __restrict__ part_base, const double* part,
-                                                         ChunkRule rule, int nv, int kmax, double* __restrict__ out,
-                                                         int out_stride) {
-  __shared__ double scratch[kBlock];
-  __shared__ double res[kBlock];
-  const int f = blockIdx.x;
+// Level 2 and the minimizer step of fit blockIdx.x.  The state's words are
+// requested before the rows, so that both come back together; thread 0 works on
+// them in LDS and registers.
+template <int PC>
+__global__ __launch_bounds__(kBlock) void batch_tail(Mix1dConst mc, const Mix1dTable* __restrict__ tabs,
+                                                     const int64_t* __restrict__ nev,
+                                                     const int64_t* __restrict__ part_base,
+                                                     const double* __restrict__ part, ChunkRule rule, int nv, int kmax,
+                                                     double tol, int max_iter, BfgsState* __restrict__ st,
+                                                     int* __restrict__ stat, double* __restrict__ rres) {
+  __shared__ double scratch[kBlock], res[kBlock], out[2 + 2 * kBatchMaxP];
+  __shared__ BfgsState m;
+  const int f = blockIdx.x, t = threadIdx.x;
   if (stat[f] != kFitRunning) return;
-  const int64_t rows = chunks_of(rule, nev[f]);
-  mix1d_finalize_one(mc, tabs[f], part + part_base[f] * nv, rows, nv, kmax, 1, (double)nev[f],
-                     out + (int64_t)f * out_stride,
+  const int P = PC > 0 ? PC : mc.n_params;
+  const int W = bfgs_words<kBatchMaxP>(P);
+  double word = 0.0;
+  int num = 0;
+  if (t < W) word = *bfgs_word(st[f], P, t);
+  if (t < P + 8) num = *bfgs_int(st[f], P, t);
+  mix1d_finalize_one(mc, tabs[f], part + part_base[f] * nv, chunks_of(rule, nev[f]), nv, kmax, 1, (double)nev[f], out,
                      nullptr, scratch, res);
+  if (t < W) *bfgs_word(m, P, t) = word;
+  if (t < P + 8) *bfgs_int(m, P, t) = num;
+  for (int w = t + kBlock; w < W; w += kBlock) *bfgs_word(m, P, w) = *bfgs_word(st[f], P, w);
+  __syncthreads();
+  if (t == 0) {
+    bfgs_step_one<kBatchMaxP, PC>(m, out, P, tol, max_iter);
+    if (m.status != kFitRunning) {
+      write_result(m, P, rres + (int64_t)f * (3 + 2 * P));
+      stat[f] = m.status;
+    }
+  }
+  __syncthreads();
+  for (int w = t; w < W; w += kBlock) *bfgs_word(st[f], P, w) = *bfgs_word(m, P, w);
+  if (t < P + 8) *bfgs_int(st[f], P, t) = *bfgs_int(m, P, t);
+}
+
+// Every slot's [status, NLL, iterations, evaluations, theta(P), sqrt|H_ii|(P)].
+__global__ __launch_bounds__(kBlock) void batch_collect(const BfgsState* __restrict__ st, int n, int P,
+                                                        double* __restrict__ rows) {
+  const int w = 4 + 2 * P;
+  const int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  if (t >= (int64_t)n * w) return;
+  const int f = (int)(t / w), j = (int)(t - (int64_t)f * w);
+  const BfgsState& s = st[f];
+  double v;
+  if (j == 0) v = s.status;
+  else if (j == 1) v = s.f;
+  else if (j == 2) v = s.iter;
+  else if (j == 3) v = s.n_eval;
+  else if (j < 4 + P) v = s.x[j - 4];
+  else {
+    const int i = j - 4 - P;
+    v = s.mask[i] ? sqrt(fabs(s.Hm(i, i))) : 0.0;
+  }
+  rows[t] = v;
 }
 
 // ---------------------------------------------------------------- launchers
@@ -280,10 +381,8 @@ void batch_launch_step(const BatchDev& b, const Mix1dConst& mc, int n_fits, int 
                        double tol, int max_iter, hipStream_t s) {
   const int kmax = mix1d_kmax(mc.K);
   const int nv = mix1d_nv(kmax, true);
-  const dim3 fg((n_fits + 63) / 64), fb(64);
-  hipLaunchKernelGGL(batch_prologue, fg, fb, 0, s, mc, b.st, b.stat, n_fits, b.tabs);
-  hipLaunchKernelGGL(batch_scan, dim3(1), dim3(kBlock), 0, s, b.stat, b.nev, n_fits, rule, b.item_base,
-                     b.n_running);
+  hipLaunchKernelGGL(batch_head, dim3(1 + (n_fits + 63) / 64), dim3(kBlock), 0, s, mc, b.st, b.stat, b.nev, n_fits,
+                     rule, b.tabs, b.item_base, b.n_running);
 #define FN_EVAL(K, SIG)                                                                               \
   hipLaunchKernelGGL((batch_eval<true, K, SIG>), dim3(eval_grid), dim3(kBlock), 0, s, mc, b.tabs, b.ev, b.nev, \
                      b.item_base, b.part_base, n_fits, rule, b.part)
@@ -299,9 +398,29 @@ void batch_launch_step(const BatchDev& b, const Mix1dConst& mc, int n_fits, int 
   }
 #undef FN_EVAL_SIG
 #undef FN_EVAL
-  hipLaunchKernelGGL(batch_finalize, dim3(n_fits), dim3(kBlock), 0, s, mc, b.tabs, b.stat, b.nev, b.part_base, b.part,
-                     rule, nv, kmax, b.out, 2 + 2 * P);
-  bfgs_launch<kBatchMaxP>(b.st, b.out, 2 + 2 * P, n_fits, P, tol, max_iter, b.stat, b.rres, s);
+#define FN_TAIL_P(PC)                                                                                        \
+  case PC:                                                                                                  \
+    hipLaunchKernelGGL((batch_tail<PC>), dim3(n_fits), dim3(kBlock), 0, s, mc, b.tabs, b.nev, b.part_base,  \
+                       b.part, rule, nv, kmax, tol, max_iter, b.st, b.stat, b.rres);                        \
+    break;
+  switch (P <= 8 ? P : 0) {
+    FN_TAIL_P(1)
+    FN_TAIL_P(2)
+    FN_TAIL_P(3)
+    FN_TAIL_P(4)
+    FN_TAIL_P(5)
+    FN_TAIL_P(6)
+    FN_TAIL_P(7)
+    FN_TAIL_P(8)
+    FN_TAIL_P(0)
+  }
+#undef FN_TAIL_P
+}
+
+void batch_launch_collect(const BatchDev& b, int n, int P, double* rows, hipStream_t s) {
+  const int64_t total = (int64_t)n * (4 + 2 * P);
+  hipLaunchKernelGGL(batch_collect, dim3((unsigned)((total + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, b.st, n, P,
+                     rows);
 }
 
 int batch_eval_blocks_per_cu(const Mix1dConst& mc) {

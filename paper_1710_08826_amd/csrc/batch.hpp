@@ -20,8 +20,7 @@ struct BatchDev {
   int64_t* item_base;      // n_fits + 1
   int64_t* part_base;      // first partial row of each slot
   double* part;            // partial rows
-  double* out;             // per slot [NLL, grad(P), I, dI(P)]
-  int* n_running;
+  int* n_running;          // host memory
   int* stat;               // per slot status, mirrored every step
   double* rres;            // per slot result row, written when the fit retires (3 + 2P)
 };
@@ -48,10 +47,15 @@ struct AdmitRec {
 void batch_launch_admit(const BatchDev& b, const AdmitRec* recs, int n_recs, int64_t gen_blocks, int P, double lo,
                         double hi, unsigned int* n_unresolved, hipStream_t s);
 // Slots [0, n_fits) become fresh fits at theta0 (device, n_fits x P, all
-// parameters free), slots [n_fits, max_fits) idle; one workgroup per slot.
-void batch_launch_set(const BatchDev& b, const double* theta0, int n_fits, int max_fits, int P, hipStream_t s);
+// parameters free) on the events of the host arrays h_ev, h_nev (pinned,
+// max_fits entries), slots [n_fits, max_fits) idle; one workgroup per slot.
+void batch_launch_set(const BatchDev& b, const double* theta0, const double* const* h_ev, const int64_t* h_nev,
+                      int n_fits, int max_fits, int P, hipStream_t s);
 // rows_out[i] = rres row of slot slots[i] (3 + 2P doubles), for n slots.
 void batch_launch_gather_rows(const BatchDev& b, const int* slots, int n, int P, double* rows_out, hipStream_t s);
+// rows (host memory) of every slot: status, NLL, iterations, evaluations,
+// theta(P), errors(P).
+void batch_launch_collect(const BatchDev& b, int n, int P, double* rows, hipStream_t s);
 
 void batch_launch_step(const BatchDev& b, const Mix1dConst& mc, int n_fits, int P, ChunkRule rule, int eval_grid,
                        double tol, int max_iter, hipStream_t s);

@@ -13,6 +13,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cmath>
+#include <cstddef>
 #include <cstdint>
 
 namespace fn {
@@ -30,7 +31,7 @@ enum FitPhase : int {
   kPhaseHessMinus = 5   // gradient at x - h e_col
 };
 
-// One fit's BFGS + line-search state (device memory, one thread per fit).
+// One fit's BFGS + line-search state (one thread per fit takes a step).
 // xt comes first so that a state array doubles as a strided array of trial points.
 template <int PM>
 struct BfgsStateT {
@@ -472,6 +473,54 @@ __device__ __forceinline__ void write_result(const ST& s, int P, double* __restr
   }
 }
 
+// A fit's state copied between device memory and LDS by a workgroup: the words
+// in use with P parameters as one list (H, Hn, the vectors, the scalars), and
+// the integers.
+template <int PM>
+__device__ __forceinline__ int bfgs_words(int P) {
+  return 2 * P * P + 5 * P + 14;
+}
+template <int PM>
+__device__ __forceinline__ double* bfgs_word(BfgsStateT<PM>& s, int P, int w) {
+  static_assert(offsetof(BfgsStateT<PM>, f_hi) - offsetof(BfgsStateT<PM>, f) == 13 * sizeof(double), "14 scalars");
+  if (w < 2 * P * P) {
+    double* m = w < P * P ? s.H : s.Hn;
+    if (w >= P * P) w -= P * P;
+    return m + (w / P) * PM + w % P;
+  }
+  w -= 2 * P * P;
+  if (w < 5 * P) {
+    const int a = w / P, i = w - a * P;
+    return (a == 0 ? s.xt : a == 1 ? s.x : a == 2 ? s.g : a == 3 ? s.p : s.gp) + i;
+  }
+  return &s.f + (w - 5 * P);
+}
+template <int PM>
+__device__ __forceinline__ int* bfgs_int(BfgsStateT<PM>& s, int P, int i) {
+  static_assert(offsetof(BfgsStateT<PM>, fresh) - offsetof(BfgsStateT<PM>, status) == 7 * sizeof(int), "8 integers");
+  return i < P ? s.mask + i : &s.status + (i - P);
+}
+
+// One step of the fit whose state is in m (LDS or device memory), by one
+// thread: on a register copy for PC = P <= 8 parameters (PC = 0: any P, in
+// place).  The numerical-Hessian phases, a few evaluations per fit, index the
+// state at run time and stay in place.
+template <int PM, int PC>
+__device__ __forceinline__ void bfgs_step_one(BfgsStateT<PM>& m, const double* o, int P, double tol, int max_iter) {
+  if constexpr (PC > 0) {
+    if (m.phase == kPhaseHessPlus || m.phase == kPhaseHessMinus) {
+      bfgs_update(m, o, PC, tol, max_iter);
+    } else {
+      BfgsLocal<PC, PM> s;
+      s.load(m);
+      bfgs_update(s, o, PC, tol, max_iter);
+      s.store(m);
+    }
+  } else {
+    bfgs_update(m, o, P, tol, max_iter);
+  }
+}
+
 // One minimizer step per running fit; every slot's status is mirrored into
 // stat[], and a fit that retires in this step writes its result row into rres.
 template <int PM>
@@ -490,8 +539,7 @@ __global__ __launch_bounds__(64) void bfgs_step(BfgsStateT<PM>* __restrict__ st,
 
 // The same step for fits with exactly PC parameters, on a register copy of the
 // state (one round of loads and one of stores instead of a chain of dependent
-// device-memory accesses).  The numerical-Hessian phases, a few evaluations
-// per fit, index the state at run time and stay on the device-memory copy.
+// device-memory accesses).
 template <int PM, int PC>
 __global__ __launch_bounds__(64) void bfgs_step_small(BfgsStateT<PM>* __restrict__ st,
                                                       const double* __restrict__ out, int out_stride, int n_fits,
@@ -500,24 +548,11 @@ __global__ __launch_bounds__(64) void bfgs_step_small(BfgsStateT<PM>* __restrict
   const int f = blockIdx.x * blockDim.x + threadIdx.x;
   if (f >= n_fits) return;
   BfgsStateT<PM>& m = st[f];
-  int status = m.status;
-  if (status == kFitRunning) {
-    const double* o = out + (int64_t)f * out_stride;
-    double* r = rres + (int64_t)f * (3 + 2 * PC);
-    if (m.phase == kPhaseHessPlus || m.phase == kPhaseHessMinus) {
-      bfgs_update(m, o, PC, tol, max_iter);
-      status = m.status;
-      if (status != kFitRunning) write_result(m, PC, r);
-    } else {
-      BfgsLocal<PC, PM> s;
-      s.load(m);
-      bfgs_update(s, o, PC, tol, max_iter);
-      s.store(m);
-      status = s.status;
-      if (status != kFitRunning) write_result(s, PC, r);
-    }
+  if (m.status == kFitRunning) {
+    bfgs_step_one<PM, PC>(m, out + (int64_t)f * out_stride, PC, tol, max_iter);
+    if (m.status != kFitRunning) write_result(m, PC, rres + (int64_t)f * (3 + 2 * PC));
   }
-  stat[f] = status;
+  stat[f] = m.status;
 }
 
 // Launch of one minimizer step for n_fits fits of P parameters (a register copy
