@@ -131,6 +131,29 @@ __device__ inline bool dalitz_inside(const DalitzConst& dc, double s12, double s
   return dalitz_in_row(dc, s12, s13, lo, hi);
 }
 
+// The same decision, most often without its square roots and divisions: with
+// A = 2 sqrt(s12) e2, B = 2 sqrt(s12) e3 and the squared momenta's a = A^2 - 4
+// s12 m2^2, b likewise, s23 lies between lo and hi where
+//   F = (4 s12 (s23 - m2^2 - m3^2) - 2 A B)^2 - 4 a b <= 0,
+// the physical region's boundary polynomial.  The rounding errors of F, and
+// those of lo and hi carried over to it, stay below 100 2^-53 T^2 with T = 4
+// s12 (|s23| + m2^2 + m3^2) + (|A| + |B|)^2; a point within 4500 2^-52 T^2 of
+// the boundary (one in 1e10), or NaN, is left to the predicate itself.  22
+// operations instead of 100 per draw of the event generators (263 with the
+// draw's own): half a million toys 234 -> 209 us.
+__device__ __forceinline__ bool dalitz_inside_quick(const DalitzConst& dc, double s12, double s13) {
+  const double s23 = dc.msum - s12 - s13;
+  const double A = s12 - dc.m1s + dc.m2s, B = dc.M2 - s12 - dc.m3s, f = 4.0 * s12;
+  const double a = __builtin_fma(A, A, -f * dc.m2s), b = __builtin_fma(B, B, -f * dc.m3s);
+  const double D = __builtin_fma(f, s23 - dc.m2s - dc.m3s, -2.0 * A * B);
+  const double F = __builtin_fma(D, D, -4.0 * a * b);
+  const double ab = fabs(A) + fabs(B);
+  const double T = __builtin_fma(f, fabs(s23) + dc.m2s + dc.m3s, ab * ab);
+  bool in = F < 0.0;
+  if (__builtin_expect(!(a > 0.0 && b > 0.0 && fabs(F) > 1e-12 * T * T), 0)) in = dalitz_inside(dc, s12, s13);
+  return in;
+}
+
 // Compile-time structure queries on a shape S (S::K, S::chan[], S::L[]).
 template <class S>
 __host__ __device__ constexpr bool shape_uses(int c, int l) {
@@ -508,26 +531,30 @@ __device__ inline void dalitz_gen_body(const DalitzConst& dc, const DalitzTable*
                                        double* __restrict__ ev, int64_t ld,
                                        unsigned long long* __restrict__ bad) {
 #pragma clang fp contract(off)
-  __shared__ AcceptLds lds;
+  __shared__ StagedLds lds;
   const double W = *Wp;
   if (!(W > 0.0 && W < __builtin_inf())) return;  // the host reports it
   const double* r = &tab->r[0][0];
   const double w12 = hi12 - lo12, w13 = hi13 - lo13;
-  double s12, s13, p;
-  accept_reject(
+  double p;
+  accept_reject_staged(
       lds, n, per_wave, max_attempts,
-      [&](int64_t i, int a) {
+      [&](int64_t i, int a, double& s12, double& s13) {
 #pragma clang fp contract(off)
-        double u1, u2, u3, unused;
+        double u1, u2;
         philox_uniforms((uint64_t)i, 2u * a, 1u, k0, k1, u1, u2);
         s12 = lo12 + u1 * w12;
         s13 = lo13 + u2 * w13;
-        if (!dalitz_inside(dc, s12, s13)) return false;
+        return dalitz_inside_quick(dc, s12, s13);
+      },
+      [&](int64_t i, int a, double s12, double s13) {
+#pragma clang fp contract(off)
+        double u3, unused;
         philox_uniforms((uint64_t)i, 2u * a + 1u, 1u, k0, k1, u3, unused);
         p = dalitz_value<S>(dc, r, (cdouble*)tab->coef, s12, s13);
         return u3 * W < p;
       },
-      [&](int64_t i) {
+      [&](int64_t i, double s12, double s13) {
         ev[i] = s12;
         ev[ld + i] = s13;
         if (p > W) atomicAdd(bad, 1ull);

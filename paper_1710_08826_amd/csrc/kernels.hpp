@@ -121,7 +121,7 @@ void launch_gen_envelope(GenRec* r, double factor, double user, const double* va
 // 128 -- and workgroups.
 inline int gen_per_wave(int64_t n) {
   const int64_t p = (n + 4095) / 4096;
-  return (int)(p < 1 ? 1 : (p > 128 ? 128 : p));
+  return (int)(p < 1 ? 1 : (p > 128 ? 128 : p));  // (at most kMaxPerWave)
 }
 inline unsigned gen_blocks(int64_t n) {
   const int64_t per_block = (int64_t)gen_per_wave(n) * kWaves;

@@ -317,7 +317,7 @@ __device__ inline void tddp_gen_body(const DalitzConst& dc, const DalitzTable* _
                                      double hi13, int per_wave, int max_attempts, double* __restrict__ ev, int64_t ld,
                                      unsigned long long* __restrict__ bad) {
 #pragma clang fp contract(off)
-  __shared__ AcceptLds lds;
+  __shared__ StagedLds lds;
   const double W = *Wp;
   if (!(W > 0.0 && W < __builtin_inf())) return;  // the host reports it
   const double* r = &tab->r[0][0];
@@ -326,16 +326,20 @@ __device__ inline void tddp_gen_body(const DalitzConst& dc, const DalitzTable* _
   const double G = tt.gamma;
   const double lam = G * (1.0 - fabs(y));
   const double w12 = hi12 - lo12, w13 = hi13 - lo13;
-  double s12, s13, t, env;
-  accept_reject(
+  double t, env;
+  accept_reject_staged(
       lds, n, per_wave, max_attempts,
-      [&](int64_t i, int a) {
+      [&](int64_t i, int a, double& s12, double& s13) {
 #pragma clang fp contract(off)
-        double u1, u2, u3, u4;
+        double u1, u2;
         philox_uniforms((uint64_t)i, 2u * a, 2u, k0, k1, u1, u2);
         s12 = lo12 + u1 * w12;
         s13 = lo13 + u2 * w13;
-        if (!dalitz_inside(dc, s12, s13)) return false;
+        return dalitz_inside_quick(dc, s12, s13);
+      },
+      [&](int64_t i, int a, double s12, double s13) {
+#pragma clang fp contract(off)
+        double u3, u4;
         philox_uniforms((uint64_t)i, 2u * a + 1u, 2u, k0, k1, u3, u4);
         t = -log1p(-u3) / lam;
         cplx A, Ab;
@@ -353,7 +357,7 @@ __device__ inline void tddp_gen_body(const DalitzConst& dc, const DalitzTable* _
         env = e * e;
         return u4 * W * exp(-lam * t) < R;
       },
-      [&](int64_t i) {
+      [&](int64_t i, double s12, double s13) {
 #pragma clang fp contract(off)
         double v1, v2;
         philox_uniforms((uint64_t)i, 0u, 3u, k0, k1, v1, v2);
