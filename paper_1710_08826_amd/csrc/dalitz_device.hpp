@@ -242,9 +242,15 @@ __device__ __forceinline__ void dalitz_amps(const DalitzConst& dc, const double*
         const PairTerms& pt = S::chan[k] == 0 ? pt0 : (S::chan[k] == 1 ? pt1 : pt2);
         const double* rk = r + k * kDalFields;
         double ar, ai;
-        bw_amplitude(rk, pt.H[L], a[j], b[j], D[j], ar, ai);
+        if (KEEP_T) {
+          Tre[k] = a[j] * D[j]; Tim[k] = b[j] * D[j]; Gk[k] = pt.G[L];
+          const double u = rk[dKA] * pt.H[L];
+          ar = u * Tre[k];
+          ai = u * Tim[k];
+        } else {
+          bw_amplitude(rk, pt.H[L], a[j], b[j], D[j], ar, ai);
+        }
         if (KEEP_A) { Are[k] = ar; Aim[k] = ai; }
-        if (KEEP_T) { Tre[k] = a[j] * D[j]; Tim[k] = b[j] * D[j]; Gk[k] = pt.G[L]; }
         if (SUM) {
           // S += c_k A_k as four chained FMAs
           const double cr = coef[2 * k], ci = coef[2 * k + 1];
@@ -284,7 +290,7 @@ __device__ __forceinline__ void dalitz_point(const DalitzConst& dc, const double
     add(0, Pt);
     w = 1.0;
   }
-  if (GRAD >= 1) {
+  if (GRAD == 1) {
     const double w2 = 2.0 * w;
     const double ur = w2 * Sre, ui = w2 * Sim;
 #pragma unroll
@@ -295,27 +301,43 @@ __device__ __forceinline__ void dalitz_point(const DalitzConst& dc, const double
     }
   }
   if (GRAD == 2) {
-    // (ur, ui) = 2 w S from the coefficient terms above
-    const double ur = 2.0 * w * Sre, ui = 2.0 * w * Sim;
+    // with g = 2 w conj(S) A and E = c g: Re g and -Im g (the coefficients'
+    // slots), Re(E T) and G Im(E T) (dalitz_lineshape_slots makes the rest)
+    const double w2 = 2.0 * w;
+    const double ur = w2 * Sre, ui = w2 * Sim;
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-      const double* rk = r + k * kDalFields;
       const double cr = coef[2 * k], ci = coef[2 * k + 1];
-      // E = 2 w conj(S) c A
-      const double car = cr * Are[k] - ci * Aim[k], cai = cr * Aim[k] + ci * Are[k];
-      const double er = __builtin_fma(ur, car, ui * cai), ei = __builtin_fma(ur, cai, -(ui * car));
-      // dA/dm0 = A (dlnKa - X), X = T (2 m0 - i G dKw/dm0);  dP~ = 2 Re(E (dlnKa - X))
-      const double gd = Gk[k] * rk[dDKW_DM0], tm = rk[dTWOM0];
-      const double xr = __builtin_fma(tm, Tre[k], Tim[k] * gd);
-      const double xi = __builtin_fma(tm, Tim[k], -(Tre[k] * gd));
-      add2(1 + 2 * K + 2 * k, er, rk[dDLNKA] - xr, ei, xi);
-      // dA/dGamma0 = i A T gw with gw = G Kw/Gamma0, so dP~ (times 2w) = Re(E i T) gw
-      // = -gw (er Tim + ei Tre)
-      const double gw = Gk[k] * rk[dKW_W0];
+      const double gr = __builtin_fma(ui, Aim[k], ur * Are[k]), gi = __builtin_fma(ur, Aim[k], -(ui * Are[k]));
+      const double er = __builtin_fma(-ci, gi, cr * gr), ei = __builtin_fma(ci, gr, cr * gi);
+      add(1 + 2 * k, gr);
+      add(2 + 2 * k, -gi);
+      add2(1 + 2 * K + 2 * k, er, Tre[k], -ei, Tim[k]);
       const double q = __builtin_fma(er, Tim[k], ei * Tre[k]);
-      const double t = __builtin_fma(-gw, q, acc[2 + 2 * K + 2 * k]);
+      const double t = __builtin_fma(Gk[k], q, acc[2 + 2 * K + 2 * k]);
       acc[2 + 2 * K + 2 * k] = valid ? t : acc[2 + 2 * K + 2 * k];
     }
+  }
+}
+
+// Mass and width slots of a thread's sums.  dA/dm0 = A (dlnKa - T (2 m0 - i G
+// dKw/dm0)) and dA/dGamma0 = i A T G Kw/Gamma0, so with E = 2 w conj(S) c A
+//   sum dP~/dm0     = dlnKa sum Re E - 2 m0 sum Re(E T) - dKw/dm0 sum G Im(E T)
+//   sum dP~/dGamma0 = -Kw/Gamma0 sum G Im(E T),
+// and Re E follows from the coefficients' slots: fifteen operations per
+// resonance and event instead of twenty-three.
+template <class S, int NV>
+__device__ __forceinline__ void dalitz_lineshape_slots(const double* __restrict__ r, cdouble* __restrict__ coef,
+                                                       double (&acc)[NV]) {
+  constexpr int K = S::K;
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    const double* rk = r + k * kDalFields;
+    const double e = __builtin_fma(coef[2 * k], acc[1 + 2 * k], coef[2 * k + 1] * acc[2 + 2 * k]);
+    double& m = acc[1 + 2 * K + 2 * k];
+    double& v = acc[2 + 2 * K + 2 * k];
+    m = __builtin_fma(rk[dDLNKA], e, -__builtin_fma(rk[dTWOM0], m, rk[dDKW_DM0] * v));
+    v = -rk[dKW_W0] * v;
   }
 }
 
@@ -339,6 +361,25 @@ __device__ inline void dalitz_chunk(const DalitzConst& dc, const DalitzTable* __
   const int64_t end = base + chunk < n ? base + chunk : n;
   const double* const r0 = &tab->r[0][0];
   LogProd lp;
+  // The next iteration's points are loaded while one is worked on (their index
+  // held to the chunk, so that the last round reads nothing else): with two
+  // waves per SIMD the loads' latency was as long as the work on a point.
+  double n12[EPT], n13[EPT];
+  GridCell nc[EPT];
+  auto load = [&](int64_t i) {
+#pragma unroll
+    for (int e = 0; e < EPT; ++e) {
+      const int64_t j = i + e * kBlock, jj = j < end ? j : end - 1;
+      if (MODE == kEvents) {
+        n12[e] = ev[jj];
+        n13[e] = ev[ld + jj];
+      } else {
+        // grid passes walk the list of the cells inside the region (ev)
+        nc[e] = reinterpret_cast<const GridCell*>(ev)[jj];
+      }
+    }
+  };
+  if (base < end) load(base + threadIdx.x);
   for (int64_t i = base + threadIdx.x; i < end; i += EPT * kBlock) {
     // The per-resonance constants are read through the scalar cache on every
     // event: an empty asm makes a zero offset opaque to the loop so that the
@@ -349,25 +390,19 @@ __device__ inline void dalitz_chunk(const DalitzConst& dc, const DalitzTable* __
     asm volatile("" : "+s"(zero));
     const double* r = r0 + zero;
     cdouble* coef = coef0 + zero;
+    double s12[EPT], s13[EPT];
 #pragma unroll
     for (int e = 0; e < EPT; ++e) {
-      const int64_t j = i + e * kBlock;
-      const bool valid = e == 0 || j < end;
-      const int64_t jj = valid ? j : i;  // a valid index; its terms are masked out
-      double s12, s13;
-      if (MODE == kEvents) {
-        s12 = ev[jj];
-        s13 = ev[ld + jj];
-      } else {
-        // grid passes walk the list of the cells inside the region (ev)
-        const GridCell g = reinterpret_cast<const GridCell*>(ev)[jj];
-        s12 = grid_centre(dc.a12, g.ix, dc.d12);
-        s13 = grid_centre(dc.a13, g.iy, dc.d13);
-      }
-      dalitz_point<S, MODE, GRAD>(dc, r, coef, s12, s13, valid, acc, lp);
+      s12[e] = MODE == kEvents ? n12[e] : grid_centre(dc.a12, nc[e].ix, dc.d12);
+      s13[e] = MODE == kEvents ? n13[e] : grid_centre(dc.a13, nc[e].iy, dc.d13);
     }
+    load(i + EPT * kBlock);
+#pragma unroll
+    for (int e = 0; e < EPT; ++e)
+      dalitz_point<S, MODE, GRAD>(dc, r, coef, s12[e], s13[e], e == 0 || i + e * kBlock < end, acc, lp);
   }
   if (MODE == kEvents) acc[0] = -lp.log();
+  if constexpr (GRAD == 2) dalitz_lineshape_slots<S>(r0, coef0, acc);
   block_sum_row<NV>(acc, lds, out_row);
 }
 
