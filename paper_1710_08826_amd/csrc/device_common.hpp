@@ -30,6 +30,15 @@ __device__ __forceinline__ double quad_sum(double x) {
   return x;
 }
 
+// Sum over the 16 lanes of a row, the same value in all (quads as above, then
+// the mirrored half row, then the mirrored row).
+__device__ __forceinline__ double row16_sum(double x) {
+  x = quad_sum(x);
+  x += __builtin_amdgcn_update_dpp(0.0, x, 0x141, 0xF, 0xF, true);  // row_half_mirror
+  x += __builtin_amdgcn_update_dpp(0.0, x, 0x140, 0xF, 0xF, true);  // row_mirror
+  return x;
+}
+
 template <int NV>
 __device__ inline void block_sum_row(double (&v)[NV], double* lds /* block_sum_lds(NV) */,
                                      double* __restrict__ out_row) {

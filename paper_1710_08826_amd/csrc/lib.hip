@@ -819,9 +819,7 @@ fn_status fn_model_create(fn_ctx* ctx, const char* desc_json, fn_model** out) {
     // workgroup's reduction pays.  The amplitude passes are bound by instruction
     // issue at two workgroups per compute unit (the mixing ones hold no more
     // registers), and a small sample gets one event per thread on as many
-    // workgroups as it has; the rows of free lineshapes are summed by many
-    // workgroups anyway, and four balance the compute units better (4M events:
-    // 120.4 us at four, 123.4 at two); the mixture's loads need eight, and below
+    // workgroups as it has; the mixture's loads need eight, and below
     // 1024 events its reduction costs more than it saves (1e5 events: 512 +30 %).
     // NLL and gradient against the fixed chunks (2048; 4096 for the mixing
     // models; 1024 for mixtures): three-body 20011 events 35.9 -> 31.5 us,
@@ -831,8 +829,7 @@ fn_status fn_model_create(fn_ctx* ctx, const char* desc_json, fn_model** out) {
     hip_check(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, m->device), "hipDeviceGetAttribute");
     const bool mix = m->kind == kKindMix1d;
     m->chunk_lo = mix ? m->chunk : kBlock;
-    const bool free_ls = m->kind == kKindDalitz3 && m->dal.free_ls;
-    m->chunk_slots = (mix ? 8 : (free_ls ? 4 : 2)) * (cus > 0 ? cus : 1);
+    m->chunk_slots = (mix ? 8 : 2) * (cus > 0 ? cus : 1);
     m->d_out.reserve(sizeof(double) * (2 + 2 * m->P));
     m->d_count.reserve(sizeof(unsigned long long));
     if (hipHostMalloc((void**)&m->h_out, sizeof(double) * (2 + 2 * m->P) + 64, hipHostMallocDefault) !=

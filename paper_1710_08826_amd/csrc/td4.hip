@@ -81,7 +81,7 @@ __global__ __launch_bounds__(kTd4PrologueThreads) void td4_prologue(Td4Const tc,
 // I = 1/2 [(a+b) cy + (a-b) cx - 2 Re(z) y cy - 2 Im(z) x cx], a = c^H M c form for A,
 // b for Abar, z = <conj(A) Abar> = sum_kl conj(c_k) cb_l M_lk; cy = 1/(G(1-y^2)),
 // cx = 1/(G(1+x^2)).  X_k = sum_j M_kj conj(c_j), Y_k = sum_j M_kj conj(cb_j),
-// U_k = sum_l cb_l M_lk, V_l = sum_k conj(c_k) M_lk.
+// U_k = sum_l cb_l M_lk, and sum_l conj(c_l) M_kl is X_k again.
 __global__ __launch_bounds__(kFinalBlock) void td4_finalize(Td4Const tc, const Td4Table* __restrict__ tabs,
                                                        const int* __restrict__ status, const double* __restrict__ part,
                                                        int64_t rows, int nv, int kmax, int with_grad,
@@ -90,97 +90,97 @@ __global__ __launch_bounds__(kFinalBlock) void td4_finalize(Td4Const tc, const T
                                                        double* __restrict__ out_user) {
   __shared__ double scratch[kFinalBlock];
   __shared__ double res[kBlock];
-  __shared__ double M[2 * kTd4MaxAmp * kTd4MaxAmp];
-  __shared__ double XYUV[8][kTd4MaxAmp];       // Re, Im of X, Y, U, V per amplitude
+  __shared__ double XYU[6][kTd4MaxAmp];        // Re, Im of X, Y, U per amplitude
+  __shared__ double form[4][kTd4MaxAmp];       // amplitude k's term of a, b, Re z, Im z
   __shared__ double gI[4 * kTd4MaxAmp + 2];    // dI/dtheta in theta order
-  __shared__ double form[4];                   // a, b, Re z, Im z
   __shared__ double Ish;
-  __shared__ double cc[4 * kTd4MaxAmp];        // c then cb, (Re, Im) per amplitude
-  static_assert(2 * kTd4MaxAmp * kTd4MaxAmp <= kFinalBlock, "one entry of M per thread");
   const int f = blockIdx.x;
   if (status && status[f] != 1) return;
   const Td4Table& tb = tabs[f];
   const int K = tc.K, P = tc.n_params;
   const int t = threadIdx.x;
-  // M, the coefficients, x, y and the validity flag are loaded first, by every
-  // thread (clamped indices, values not needed discarded; lane-varying offsets
-  // so that the uniform ones are vector loads too): no wait for them comes
-  // before the rows are requested, and their latency overlaps the row sums
+  // Row k of the matrix-vector products goes to 16 lanes, columns j and j + 16
+  // each, whose sums take four steps: with a thread per row, its serial sum and
+  // then the serial sum over k took most of the step (ten amplitudes each way,
+  // no rows: 9.0 -> 6.9 us).  The elements, coefficients, x, y and the validity flag
+  // are loaded before the row sums (the uniform ones at lane-varying offsets,
+  // so that they are vector loads too), so that their latency overlaps them.
   int zero = 0;
   asm volatile("" : "+v"(zero));
-  constexpr int nm = 2 * kTd4MaxAmp * kTd4MaxAmp;
-  const double mv = Mc[(int64_t)f * nm + (t < nm ? t : 0)];
-  static_assert(offsetof(Td4Table, cb) == offsetof(Td4Table, c) + 2 * kTd4MaxAmp * sizeof(double),
-                "cb follows c");
-  const double cv = reinterpret_cast<const double*>(&tb)[offsetof(Td4Table, c) / sizeof(double) +
-                                                         (t < 4 * kTd4MaxAmp ? t : 0)];
+  constexpr int nm = 2 * kTd4MaxAmp * kTd4MaxAmp, A = kTd4MaxAmp;
+  static_assert(A <= 32 && 16 * A <= kFinalBlock, "two columns per lane, a row of 16 lanes per amplitude");
+  const int k = t >> 4;
+  const double* Mf = Mc + (int64_t)f * nm;
+  cplx mkj[2]{}, mjk[2]{}, cj[2]{}, bj[2]{}, ck{0.0, 0.0}, bk{0.0, 0.0};
+  if (k < K) {
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int j = (t & 15) + 16 * u;
+      if (j < K) {
+        mkj[u] = {Mf[2 * (k * A + j)], Mf[2 * (k * A + j) + 1]};
+        mjk[u] = {Mf[2 * (j * A + k)], Mf[2 * (j * A + k) + 1]};
+        cj[u] = {tb.c[j][0], tb.c[j][1]};
+        bj[u] = {tb.cb[j][0], tb.cb[j][1]};
+      }
+    }
+    ck = {tb.c[k][0], tb.c[k][1]};
+    bk = {tb.cb[k][0], tb.cb[k][1]};
+  }
   const double x = (&tb.x)[zero], y = (&tb.y)[zero], valid = (&tb.valid)[zero];
   sum_rows_t<kFinalBlock>(part + (int64_t)f * rows * nv, rows, nv, scratch, res);
-  if (t < nm) M[t] = mv;
-  if (t < 4 * kTd4MaxAmp) cc[t] = cv;
-  __syncthreads();
-  auto m = [&](int i, int j) { return cplx{M[2 * (i * kTd4MaxAmp + j)], M[2 * (i * kTd4MaxAmp + j) + 1]}; };
-  const double* c = cc;
-  const double* cb = cc + 2 * kTd4MaxAmp;
-  // thread k < K: the k-th entries of the four matrix-vector products
-  if (t < K) {
-    const int k = t;
-    double Xr = 0.0, Xi = 0.0, Yr = 0.0, Yi = 0.0, Ur = 0.0, Ui = 0.0, Vr = 0.0, Vi = 0.0;
-    for (int j = 0; j < K; ++j) {
-      const cplx mkj = m(k, j), mjk = m(j, k);
-      const double cjr = c[2 * j], cji = c[2 * j + 1], bjr = cb[2 * j], bji = cb[2 * j + 1];
-      // X_k += M_kj conj(c_j), Y_k += M_kj conj(cb_j)
-      Xr += mkj.re * cjr + mkj.im * cji;
-      Xi += mkj.im * cjr - mkj.re * cji;
-      Yr += mkj.re * bjr + mkj.im * bji;
-      Yi += mkj.im * bjr - mkj.re * bji;
-      // U_k += cb_j M_jk, V_k += conj(c_j) M_kj
-      Ur += bjr * mjk.re - bji * mjk.im;
-      Ui += bjr * mjk.im + bji * mjk.re;
-      Vr += cjr * mkj.re + cji * mkj.im;
-      Vi += cjr * mkj.im - cji * mkj.re;
+  if (k < A) {
+    double v[6] = {};
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      // X_k += M_kj conj(c_j), Y_k += M_kj conj(cb_j), U_k += cb_j M_jk (and V_k = sum conj(c_j) M_kj = X_k)
+      v[0] += mkj[u].re * cj[u].re + mkj[u].im * cj[u].im;
+      v[1] += mkj[u].im * cj[u].re - mkj[u].re * cj[u].im;
+      v[2] += mkj[u].re * bj[u].re + mkj[u].im * bj[u].im;
+      v[3] += mkj[u].im * bj[u].re - mkj[u].re * bj[u].im;
+      v[4] += bj[u].re * mjk[u].re - bj[u].im * mjk[u].im;
+      v[5] += bj[u].re * mjk[u].im + bj[u].im * mjk[u].re;
     }
-    XYUV[0][k] = Xr; XYUV[1][k] = Xi; XYUV[2][k] = Yr; XYUV[3][k] = Yi;
-    XYUV[4][k] = Ur; XYUV[5][k] = Ui; XYUV[6][k] = Vr; XYUV[7][k] = Vi;
-  }
-  __syncthreads();
-  const double G = tc.gamma;
-  const double cy = 1.0 / (G * (1.0 - y * y)), cx = 1.0 / (G * (1.0 + x * x));
-  if (t == 0) {
-    // the quadratic forms, summed over k in order
-    double a = 0.0, b = 0.0, zr = 0.0, zi = 0.0;
-    for (int k = 0; k < K; ++k) {
-      a += c[2 * k] * XYUV[0][k] - c[2 * k + 1] * XYUV[1][k];
-      b += cb[2 * k] * XYUV[2][k] - cb[2 * k + 1] * XYUV[3][k];
-      // z = sum_k conj(c_k) U_k
-      zr += c[2 * k] * XYUV[4][k] + c[2 * k + 1] * XYUV[5][k];
-      zi += c[2 * k] * XYUV[5][k] - c[2 * k + 1] * XYUV[4][k];
-    }
-    form[0] = a;
-    form[1] = b;
-    form[2] = zr;
-    form[3] = zi;
-    Ish = 0.5 * ((a + b) * cy + (a - b) * cx - 2.0 * zr * y * cy - 2.0 * zi * x * cx);
-  }
-  if (t < K) {
-    const int k = t, ia = tc.pa[k], ib = tc.pb[k];
-    const double Xr = XYUV[0][k], Xi = XYUV[1][k], Yr = XYUV[2][k], Yi = XYUV[3][k];
-    const double Ur = XYUV[4][k], Ui = XYUV[5][k], Vr = XYUV[6][k], Vi = XYUV[7][k];
-    if (ia >= 0) {
-      gI[ia] = 0.5 * ((cy + cx) * 2.0 * Xr - 2.0 * y * cy * Ur - 2.0 * x * cx * Ui);
-      gI[ia + 1] = 0.5 * (-2.0 * (cy + cx) * Xi - 2.0 * y * cy * Ui + 2.0 * x * cx * Ur);
-    }
-    if (ib >= 0) {
-      gI[ib] = 0.5 * ((cy - cx) * 2.0 * Yr - 2.0 * y * cy * Vr - 2.0 * x * cx * Vi);
-      gI[ib + 1] = 0.5 * (-2.0 * (cy - cx) * Yi + 2.0 * y * cy * Vi - 2.0 * x * cx * Vr);
+#pragma unroll
+    for (int i = 0; i < 6; ++i) v[i] = row16_sum(v[i]);
+    if ((t & 15) == 0) {
+#pragma unroll
+      for (int i = 0; i < 6; ++i) XYU[i][k] = v[i];
+      form[0][k] = ck.re * v[0] - ck.im * v[1];
+      form[1][k] = bk.re * v[2] - bk.im * v[3];
+      form[2][k] = ck.re * v[4] + ck.im * v[5];  // z = sum_k conj(c_k) U_k
+      form[3][k] = ck.re * v[5] - ck.im * v[4];
     }
   }
   __syncthreads();
-  if (t == 0) {
-    const double a = form[0], b = form[1], zr = form[2], zi = form[3];
-    const double dcx = -2.0 * x * G * cx * cx, dcy = 2.0 * y * G * cy * cy;
-    gI[P - 2] = 0.5 * ((a - b) * dcx - 2.0 * zi * (cx + x * dcx));
-    gI[P - 1] = 0.5 * ((a + b) * dcy - 2.0 * zr * (cy + y * dcy));
+  if (t < 64) {
+    double q[4];  // a, b, Re z, Im z
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int l = t & 15;
+      q[i] = row16_sum(form[i][l] + (16 + l < A ? form[i][16 + l < A ? 16 + l : 0] : 0.0));
+    }
+    const double a = q[0], b = q[1], zr = q[2], zi = q[3];
+    const double G = tc.gamma;
+    const double cy = 1.0 / (G * (1.0 - y * y)), cx = 1.0 / (G * (1.0 + x * x));
+    if (t < K) {
+      const int ia = tc.pa[t], ib = tc.pb[t];
+      const double Xr = XYU[0][t], Xi = XYU[1][t], Yr = XYU[2][t], Yi = XYU[3][t];
+      const double Ur = XYU[4][t], Ui = XYU[5][t];
+      if (ia >= 0) {
+        gI[ia] = 0.5 * ((cy + cx) * 2.0 * Xr - 2.0 * y * cy * Ur - 2.0 * x * cx * Ui);
+        gI[ia + 1] = 0.5 * (-2.0 * (cy + cx) * Xi - 2.0 * y * cy * Ui + 2.0 * x * cx * Ur);
+      }
+      if (ib >= 0) {
+        gI[ib] = 0.5 * ((cy - cx) * 2.0 * Yr - 2.0 * y * cy * Xr - 2.0 * x * cx * Xi);
+        gI[ib + 1] = 0.5 * (-2.0 * (cy - cx) * Yi + 2.0 * y * cy * Xi - 2.0 * x * cx * Xr);
+      }
+    }
+    if (t == 63) {
+      const double dcx = -2.0 * x * G * cx * cx, dcy = 2.0 * y * G * cy * cy;
+      gI[P - 2] = 0.5 * ((a - b) * dcx - 2.0 * zi * (cx + x * dcx));
+      gI[P - 1] = 0.5 * ((a + b) * dcy - 2.0 * zr * (cy + y * dcy));
+      Ish = 0.5 * ((a + b) * cy + (a - b) * cx - 2.0 * zr * y * cy - 2.0 * zi * x * cx);
+    }
   }
   __syncthreads();
   const double I = Ish;

@@ -62,11 +62,9 @@ __global__ void tddp_copy_theta(ParamBlock pb, int P, double* __restrict__ dst) 
 
 struct TddpFinalLds {
   double scratch[kFinalBlock];
-  double M[6 * kDalMaxRes * kDalMaxRes];
   double res[kBlock];
-  double cre[kDalMaxRes], cim[kDalMaxRes], bre[kDalMaxRes], bim[kDalMaxRes];
   double X[kDalMaxRes][2], Xb[kDalMaxRes][2], U[kDalMaxRes][2], V[kDalMaxRes][2];
-  double Ia, Ib, Zr, Zi;
+  double form[4][kDalMaxRes];  // resonance k's term of Ia, Ib, Re Z, Im Z
 };
 
 // Level 2 and the normalization
@@ -90,79 +88,59 @@ __global__ __launch_bounds__(kFinalBlock) void tddp_finalize(DalitzConst dc, con
   const int K = dc.K;
   const int P = 4 * K + 2;
   const int t = threadIdx.x;
-  // the three matrices and the coefficients are loaded first, by every thread
-  // (clamped indices, values past the end discarded: no branch makes a wave
-  // wait for them), so that their latency overlaps the row sums
-  const int nm = 6 * K * K;
-  double mv[(6 * kDalMaxRes * kDalMaxRes + kFinalBlock - 1) / kFinalBlock];
-#pragma unroll
-  for (int u = 0; u < (int)(sizeof(mv) / sizeof(mv[0])); ++u) {
-    const int i = t + u * kFinalBlock;
-    mv[u] = Mc[i < nm ? i : 0];
+  // Row k of the matrix-vector products goes to 16 lanes, one column j each,
+  // whose sums take four steps: with a thread per row, its serial sum and then
+  // the serial sum over k took half of the step (1M events, 16 resonances: the
+  // step 11.5 -> 8.4 us).  The elements and coefficients are loaded before the row
+  // sums, so that their latency overlaps them.
+  const int k = t >> 4, j = t & 15;
+  const bool on = k < K && j < K;
+  static_assert(kDalMaxRes == 16, "a row of 16 lanes per resonance");
+  cplx maa{0.0, 0.0}, mbb{0.0, 0.0}, mab{0.0, 0.0}, mba{0.0, 0.0}, cj{0.0, 0.0}, bj{0.0, 0.0}, ck{0.0, 0.0}, bk{0.0, 0.0};
+  if (on) {
+    const double* m = Mc + 2 * (k * K + j);
+    const int nm = 2 * K * K;
+    const double* mt = Mc + 2 * nm + 2 * (j * K + k);
+    maa = {m[0], m[1]};
+    mbb = {m[nm], m[nm + 1]};
+    mab = {m[2 * nm], m[2 * nm + 1]};
+    mba = {mt[0], mt[1]};
+    cj = {coef[2 * j], coef[2 * j + 1]};
+    bj = {coef[2 * K + 2 * j], coef[2 * K + 2 * j + 1]};
+    ck = {coef[2 * k], coef[2 * k + 1]};
+    bk = {coef[2 * K + 2 * k], coef[2 * K + 2 * k + 1]};
   }
-  const int tc = t < K ? t : 0;
-  const double c0 = coef[2 * tc], c1 = coef[2 * tc + 1], c2 = coef[2 * K + 2 * tc], c3 = coef[2 * K + 2 * tc + 1];
   // the same for the uniform values, as vector loads (a lane-varying zero
   // offset): scalar ones would be waited for before the rows are requested
   int zero = 0;
   asm volatile("" : "+v"(zero));
   const double x = coef[4 * K + zero], y = coef[4 * K + 1 + zero], valid = (&tab->valid)[zero];
   sum_rows_t<kFinalBlock>(part, nrows, nv, L.scratch, L.res);
-#pragma unroll
-  for (int u = 0; u < (int)(sizeof(mv) / sizeof(mv[0])); ++u) {
-    const int i = t + u * kFinalBlock;
-    if (i < nm) L.M[i] = mv[u];
-  }
-  if (t < K) {
-    L.cre[t] = c0;
-    L.cim[t] = c1;
-    L.bre[t] = c2;
-    L.bim[t] = c3;
-  }
-  __syncthreads();
-  const double* MAA = L.M;
-  const double* MBB = L.M + 2 * K * K;
-  const double* MAB = L.M + 4 * K * K;
-  if (t < K) {
-    double xr = 0.0, xi = 0.0, br = 0.0, bi = 0.0, ur = 0.0, ui = 0.0, vr = 0.0, vi = 0.0;
-    for (int j = 0; j < K; ++j) {
-      // X_t = sum_j MAA_tj conj(c_j)
-      const double mr = MAA[2 * (t * K + j)], mi = MAA[2 * (t * K + j) + 1];
-      xr += mr * L.cre[j] + mi * L.cim[j];
-      xi += mi * L.cre[j] - mr * L.cim[j];
-      const double nr = MBB[2 * (t * K + j)], ni = MBB[2 * (t * K + j) + 1];
-      br += nr * L.bre[j] + ni * L.bim[j];
-      bi += ni * L.bre[j] - nr * L.bim[j];
-      // U_t = sum_j MAB_tj cbar_j
-      const double ar = MAB[2 * (t * K + j)], ai = MAB[2 * (t * K + j) + 1];
-      ur += ar * L.bre[j] - ai * L.bim[j];
-      ui += ar * L.bim[j] + ai * L.bre[j];
-      // V_t = sum_i conj(c_i) MAB_it
-      const double qr = MAB[2 * (j * K + t)], qi = MAB[2 * (j * K + t) + 1];
-      vr += L.cre[j] * qr + L.cim[j] * qi;
-      vi += L.cre[j] * qi - L.cim[j] * qr;
+  if (t < 16 * kDalMaxRes) {
+    // X_k = sum_j MAA_kj conj(c_j), Xb_k alike, U_k = sum_j MAB_kj cbar_j, V_k = sum_i conj(c_i) MAB_ik
+    const double xr = row16_sum(maa.re * cj.re + maa.im * cj.im), xi = row16_sum(maa.im * cj.re - maa.re * cj.im);
+    const double br = row16_sum(mbb.re * bj.re + mbb.im * bj.im), bi = row16_sum(mbb.im * bj.re - mbb.re * bj.im);
+    const double ur = row16_sum(mab.re * bj.re - mab.im * bj.im), ui = row16_sum(mab.re * bj.im + mab.im * bj.re);
+    const double vr = row16_sum(cj.re * mba.re + cj.im * mba.im), vi = row16_sum(cj.re * mba.im - cj.im * mba.re);
+    if (j == 0) {
+      L.X[k][0] = xr; L.X[k][1] = xi;
+      L.Xb[k][0] = br; L.Xb[k][1] = bi;
+      L.U[k][0] = ur; L.U[k][1] = ui;
+      L.V[k][0] = vr; L.V[k][1] = vi;
+      L.form[0][k] = ck.re * xr - ck.im * xi;  // Re(c_k X_k)
+      L.form[1][k] = bk.re * br - bk.im * bi;
+      L.form[2][k] = ck.re * ur + ck.im * ui;  // conj(c_k) U_k
+      L.form[3][k] = ck.re * ui - ck.im * ur;
     }
-    L.X[t][0] = xr; L.X[t][1] = xi;
-    L.Xb[t][0] = br; L.Xb[t][1] = bi;
-    L.U[t][0] = ur; L.U[t][1] = ui;
-    L.V[t][0] = vr; L.V[t][1] = vi;
   }
   __syncthreads();
-  if (t == 0) {
-    double ia = 0.0, ib = 0.0, zr = 0.0, zi = 0.0;
-    for (int k = 0; k < K; ++k) {
-      ia += L.cre[k] * L.X[k][0] - L.cim[k] * L.X[k][1];   // Re(c_k X_k)
-      ib += L.bre[k] * L.Xb[k][0] - L.bim[k] * L.Xb[k][1];
-      zr += L.cre[k] * L.U[k][0] + L.cim[k] * L.U[k][1];   // conj(c_k) U_k
-      zi += L.cre[k] * L.U[k][1] - L.cim[k] * L.U[k][0];
-    }
-    L.Ia = ia; L.Ib = ib; L.Zr = zr; L.Zi = zi;
-  }
-  __syncthreads();
+  if (t >= ((P + 63) & ~63)) return;  // (whole waves: no barrier follows)
+  const double Ia = row16_sum(L.form[0][j]), Ib = row16_sum(L.form[1][j]);
+  const double Zr = row16_sum(L.form[2][j]), Zi = row16_sum(L.form[3][j]);
   const double tau = 1.0 / tt.gamma;
   const double dy = 1.0 - y * y, dx = 1.0 + x * x;
   const double cy = tau / dy, cx = tau / dx;
-  const double I = 0.5 * (cy * (L.Ia + L.Ib) + cx * (L.Ia - L.Ib) - 2.0 * y * cy * L.Zr - 2.0 * x * cx * L.Zi);
+  const double I = 0.5 * (cy * (Ia + Ib) + cx * (Ia - Ib) - 2.0 * y * cy * Zr - 2.0 * x * cx * Zi);
   const bool ok = valid != 0.0 && I > 0.0 && isfinite(I) && dy > 0.0;
   if (t == 0) {
     const double v = ok ? L.res[0] + n_events * log(I) : INFINITY;
@@ -182,10 +160,10 @@ __global__ __launch_bounds__(kFinalBlock) void tddp_finalize(DalitzConst dc, con
                         : 0.5 * (-2.0 * (cy - cx) * L.Xb[k][1] + 2.0 * y * cy * L.V[k][1] - 2.0 * x * cx * L.V[k][0]);
     } else if (t == 4 * K) {
       const double dcx = -2.0 * x * tau / (dx * dx), dxcx = tau * (1.0 - x * x) / (dx * dx);
-      dI = 0.5 * ((L.Ia - L.Ib) * dcx - 2.0 * L.Zi * dxcx);
+      dI = 0.5 * ((Ia - Ib) * dcx - 2.0 * Zi * dxcx);
     } else {
       const double dcy = 2.0 * y * tau / (dy * dy), dycy = tau * (1.0 + y * y) / (dy * dy);
-      dI = 0.5 * ((L.Ia + L.Ib) * dcy - 2.0 * L.Zr * dycy);
+      dI = 0.5 * ((Ia + Ib) * dcy - 2.0 * Zr * dycy);
     }
     out[2 + P + t] = dI;
     if (with_grad) {
