@@ -393,7 +393,7 @@ void batch_launch_step(const BatchDev& b, const Mix1dConst& mc, int n_fits, int 
   switch (mix1d_sig(mc)) {
     FN_MIX_SIGS(FN_EVAL_SIG)
     default:
-      if (kmax == 2) FN_EVAL(2, 0);
+      if (kmax == 4) FN_EVAL(4, 0);
       else FN_EVAL(8, 0);
   }
 #undef FN_EVAL_SIG
@@ -432,8 +432,8 @@ int batch_eval_blocks_per_cu(const Mix1dConst& mc) {
   switch (mix1d_sig(mc)) {
     FN_MIX_SIGS(FN_OCC_SIG)
     default:
-      if (mix1d_kmax(mc.K) == 2)
-        (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, batch_eval<true, 2, 0>, kBlock, 0);
+      if (mix1d_kmax(mc.K) == 4)
+        (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, batch_eval<true, 4, 0>, kBlock, 0);
       else
         (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, batch_eval<true, 8, 0>, kBlock, 0);
   }

@@ -11,6 +11,7 @@ struct DevBuf;
 
 // mix1d
 int mix1d_kmax(int K);
+int mix1d_kmax_binned(int K);
 // Type signature a mixture's per-event passes are compiled for (mix_sig_K):
 // 1..20 for one or two components, 0 (generic passes) for more.
 int mix1d_sig(const Mix1dConst& mc);

@@ -668,7 +668,7 @@ void nll_binned_host(fn_model* m, const double* theta_host, const BinnedData& bd
   const bool g = grad != nullptr;
   mix1d_launch_prologue(mc, pb, nullptr, 1, 0, m->table_mix(), s);
   const int64_t nch = nchunks_for(bd.nb, m->chunk);
-  m->d_part.reserve(sizeof(double) * (size_t)nch * mix1d_nv_binned(mix1d_kmax(mc.K), g));
+  m->d_part.reserve(sizeof(double) * (size_t)nch * mix1d_nv_binned(mix1d_kmax_binned(mc.K), g));
   m->d_gen.reserve(3 * sizeof(unsigned long long));
   mix1d_launch_binned(mc, m->table_mix(), bd.counts, bd.nb, m->chunk, nch, bd.stat, g, m->part(),
                       (double*)m->d_gen.ptr, m->h_out_dev, s);

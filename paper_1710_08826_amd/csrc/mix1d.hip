@@ -107,7 +107,9 @@ __global__ void mix1d_check(Mix1dConst mc, const double* __restrict__ x, int64_t
 }
 
 // ---------------------------------------------------------------- launchers
-int mix1d_kmax(int K) { return K <= 2 ? 2 : 8; }
+// components the passes hold: events (two are compiled for their types) and bins
+int mix1d_kmax(int K) { return K <= 2 ? 2 : (K <= 4 ? 4 : 8); }
+int mix1d_kmax_binned(int K) { return K <= 2 ? 2 : 8; }
 int mix1d_sig(const Mix1dConst& mc) {
   if (mc.K == 1) return 1 + mc.type[0];
   if (mc.K == 2) return 5 + 4 * mc.type[0] + mc.type[1];
@@ -137,8 +139,8 @@ void mix1d_launch_events(const Mix1dConst& mc, const Mix1dTable* tab, const doub
   switch (mix1d_sig(mc)) {
     FN_MIX_SIGS(FN_MIX_SIG)
     default:
-      if (kmax == 2) {
-        if (grad) FN_MIX(true, 2, 0); else FN_MIX(false, 2, 0);
+      if (kmax == 4) {
+        if (grad) FN_MIX(true, 4, 0); else FN_MIX(false, 4, 0);
       } else {
         if (grad) FN_MIX(true, 8, 0); else FN_MIX(false, 8, 0);
       }
@@ -162,7 +164,7 @@ int mix1d_nv_binned(int kmax, bool grad) {
 void mix1d_launch_binned(const Mix1dConst& mc, const Mix1dTable* tab, const double* counts, int64_t nb, int chunk,
                          int64_t nchunks, int stat, bool grad, double* part, double* nbuf, double* out,
                          hipStream_t s) {
-  const int kmax = mix1d_kmax(mc.K);
+  const int kmax = mix1d_kmax_binned(mc.K);
   const dim3 g((unsigned)nchunks), b(kBlock);
   const double* nptr = nullptr;
   if (stat == 1 && mc.yidx < 0) {
