@@ -40,7 +40,7 @@ COUNTED_FP64_FLOPS_PER_EVENT = {(2048, 1): 404.9}
 TRAFFIC_SOURCES = ["paper_1710_08826_amd/csrc/dalitz_device.hpp", "paper_1710_08826_amd/csrc/dalitz3.hip",
                    "paper_1710_08826_amd/csrc/fastmath.hpp", "paper_1710_08826_amd/csrc/device_common.hpp",
                    "paper_1710_08826_amd/csrc/model.hpp"]
-TRAFFIC_HASH = "ea741244afb06c3e"
+TRAFFIC_HASH = "dd71866cab24fcd4"
 
 
 def counters_current() -> bool:
@@ -74,6 +74,16 @@ def log_sum_flops(chunk: int) -> float:
     return 1 + W_LOG * 256 / chunk
 
 
+def chunk_in_use(m, n: int, per_cu: int) -> int:
+    """Events per workgroup of a model without a fixed chunk: at most per_cu
+    workgroups per compute unit, at least the kind's default events (256 for
+    the amplitude models, m.chunk for mixtures)."""
+    import torch
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    lo = m.chunk if per_cu == 8 else 256
+    return max(lo, -(-n // (per_cu * cus)))
+
+
 def dalitz_amp_flops(desc: dict) -> int:
     """FP64 FLOPs per point of the Dalitz amplitudes and their coherent sum:
     per-pair kinematics shared by the pair's resonances, one complex
@@ -105,7 +115,32 @@ def dalitz_flops_per_event(desc: dict, grad: int, chunk: int) -> float:
     if grad >= 1:
         f += 4 + W_DIV + 6 * K                     # -1/P~, 2 Re(conj(S) A) per coefficient
     if grad >= 2:
-        f += 31 * K                                # mass and width derivatives
+        f += 16 * K                                # mass and width derivatives (constants of the fit factored out)
+    return f
+
+
+def td4_side_flops(desc: dict, side: str, grad: bool) -> int:
+    """One coherent sum of the four-body model, factored by pair entries
+    (sum_r1 a12 sum_r2 a34 sum_k c_k Omega_k), or its gradient terms."""
+    flat12 = [e["m0"] == 0.0 for e in desc["r12"]]
+    flat34 = [e["m0"] == 0.0 for e in desc["r34"]]
+    groups = {}
+    for a in desc["amps"]:
+        if len(a) < 4 or a[3] in ("both", side):
+            groups.setdefault(int(a[0]), {}).setdefault(int(a[1]), []).append(int(a[2]))
+    f = 0
+    for n1, (r1, inner) in enumerate(groups.items()):
+        if grad:
+            f += 0 if flat12[r1] else 6
+            for r2, types in inner.items():
+                f += 0 if flat34[r2] else 6
+                f += sum(2 if t == 0 else (4 if t <= 3 else 8) for t in types)
+            continue
+        for n2, (r2, types) in enumerate(inner.items()):
+            for m, t in enumerate(types):
+                f += (0 if t == 0 else (2 if t <= 3 else 6)) + (2 if m else 0)
+            f += (0 if flat34[r2] else 6) + (2 if n2 else 0)
+        f += (0 if flat12[r1] else 6) + (2 if n1 else 0)
     return f
 
 
@@ -113,10 +148,8 @@ def td4_flops_per_event(desc: dict, grad: bool, chunk: int) -> float:
     """Algorithmic FP64 FLOPs per (event, fit) of the time-dependent
     four-body NLL, counted from the formula as evaluated: per-pair kinematics
     shared by the pair's resonances, one complex reciprocal per resonance,
-    products with flat (non-resonant) entries free, the three time terms
-    through the rational Faddeeva approximation (40 coefficients, Horner),
-    the log sum (log_sum_flops)."""
-    N = 40
+    the sums factored by pair entries (td4_side_flops), the time terms
+    (time_terms_flops), the log sum (log_sum_flops)."""
     f = 0
     pairs = (desc["r12"], desc["r34"])
     for entries in pairs:
@@ -128,62 +161,61 @@ def td4_flops_per_event(desc: dict, grad: bool, chunk: int) -> float:
     types = [int(a[2]) for a in desc["amps"]]
     f += 2 * (2 + W_SQRT) + 2                      # sin12 sin34 / 2
     if any(t >= 4 for t in types):
-        f += W_SINCOS                              # e^{i phi}
+        f += W_SINCOS + 2                          # e^{i phi}
     if 3 in types:
         f += 1                                     # c12 c34
-    flat12 = [e["m0"] == 0.0 for e in desc["r12"]]
-    flat34 = [e["m0"] == 0.0 for e in desc["r34"]]
-    members = 0                                    # (basis function, sum) memberships
-    for a in desc["amps"]:
-        i12, i34, t = a[:3]
-        f += 0 if (flat12[i12] or flat34[i34]) else 6
-        f += 0 if t == 0 else (2 if t <= 3 else 6)
-        members += 2 if len(a) < 4 or a[3] == "both" else 1
-    f += 8 * members                               # A and Abar
-    f += 2 + W_EXP                                 # exp(-t^2 / 2 sigma^2)
-    horner_r = (N - 1) * 2
-    h_real = 3 + (1 + W_DIV) + 2 + horner_r + 4 + (4 + W_EXP) + 3
-    horner_c = (N - 1) * 7
-    w_c = 1 + (5 + W_DIV) + 7 + horner_c + 8 + 7
-    h_cplx = 5 + w_c + 9 + W_SINCOS + W_EXP + 7
-    f += 2 * h_real + h_cplx
-    f += 27 + log_sum_flops(chunk)                 # rate, -sum ln R
+    f += td4_side_flops(desc, "A", False) + td4_side_flops(desc, "Abar", False)
+    f += time_terms_flops(grad) + 27 + log_sum_flops(chunk)  # rate, -sum ln R
     if grad:
-        f += 2 * 3 + 8                             # dh/da of the three time terms
-        f += 1 + W_DIV + 2 + 24 + 8 * members + 20  # -1/R, the two complex weights, lc B_k and lb B_k, x and y
+        f += 1 + W_DIV + 2 + 24 + 20               # -1/R, the two complex weights, x and y
+        f += td4_side_flops(desc, "A", True) + td4_side_flops(desc, "Abar", True)
     return f
 
 
-def time_terms_flops() -> int:
-    """The three resolution-convolved time terms per event (rational Faddeeva
-    approximation, 40 coefficients) and exp(-t^2 / 2 sigma^2)."""
-    N = 40
-    h_real = 3 + (1 + W_DIV) + 2 + (N - 1) * 2 + 4 + (4 + W_EXP) + 3
-    w_c = 1 + (5 + W_DIV) + 7 + (N - 1) * 7 + 8 + 7
-    h_cplx = 5 + w_c + 9 + W_SINCOS + W_EXP + 7
-    return 2 + W_EXP + 2 * h_real + h_cplx
+def time_terms_flops(grad: bool) -> int:
+    """The time functions of an event: exp(-t^2 / 2 sigma^2), one real h(G; t)
+    through a 24-term polynomial and an exponential, and ten terms of its
+    Taylor series in x and y."""
+    f = 2 + W_EXP + 3 + 2 + 2 + W_EXP              # g, the series' radius, u, z, e^{G^2 s^2/2 - G t}
+    f += 2 + W_DIV + 1 + 23 * 2 + 1 + 3            # exp(z^2) erfc(z), h
+    f += 1 + 2 + 3 + 1 + 2                         # terms 1 and 2
+    f += 4 * (18 + (8 if grad else 0))             # terms 3 to 10
+    return f + 4 + (2 if grad else 0)
 
 
 def tddp3_flops_per_event(desc: dict, grad: bool, chunk: int) -> float:
     """Algorithmic FP64 FLOPs per event of the time-dependent Dalitz NLL: the
-    three-body amplitudes at (s12, s13) and at (s13, s12) (per-pair kinematics
-    shared by the pair's resonances, one complex reciprocal per resonance),
-    both coherent sums, the time terms, the rate and the log sum."""
-    K = len(desc["resonances"])
-    amp = dalitz_amp_flops(dict(desc, kind="dalitz3"))  # one amplitude set + sum
-    f = 2 * amp + time_terms_flops() + 27 + log_sum_flops(chunk)
+    three pairs' kinematics, one complex reciprocal per distinct lineshape and
+    pair mass (pairs 12 and 13 share theirs), both coherent sums with the pair
+    and spin factors applied once, the time terms, the rate and the log sum."""
+    res = desc["resonances"]
+    f = 2                                          # s23
+    Ls = {"23": {int(r["L"]) for r in res if r["pair"] == "23"}}
+    Ls["12"] = Ls["13"] = {int(r["L"]) for r in res if r["pair"] != "23"}
+    for spins in Ls.values():
+        if spins:
+            f += 11 + W_RSQRT + W_SQRT
+            f += 7 if spins & {1, 2} else 0
+            f += 6 + W_DIV + W_RSQRT if 1 in spins else 0
+            f += 17 + W_DIV + W_RSQRT if 2 in spins else 0
+    shapes = {(r["pair"] == "23", int(r["L"]), r["m0"], r["w0"]) for r in res}
+    f += sum((1 if one else 2) * (7 + (1 if L else 0) + W_DIV) for one, L, _, _ in shapes)
+    groups = {(r["pair"], int(r["L"])) for r in res}
+    f += 2 * (8 * len(res) + sum(4 if L else 2 for _, L in groups))
+    f += time_terms_flops(grad) + 27 + log_sum_flops(chunk)
     if grad:
-        f += 2 * 3 + 8                              # dh/da of the three time terms
-        f += 1 + W_DIV + 2 + 24 + 16 * K + 20       # -1/R, the two complex weights, c and cbar slots, x and y
+        f += 1 + W_DIV + 2 + 24 + 20                # -1/R, the two complex weights, x and y
+        f += 2 * (8 * len(res) + sum(2 if L else 0 for _, L in groups))
     return f
 
 
 def mix1d_flops_per_event(grad: bool, chunk: int) -> float:
-    """Config-0 mixture (Gaussian + exponential): 2 exp, the log sum, ~14
-    others; the gradient adds one division and ~22 FLOPs."""
-    f = 2 * W_EXP + log_sum_flops(chunk) + 14
+    """Config-0 mixture (Gaussian + exponential): one exponential of the
+    difference of their arguments, the log sum, ten others; the gradient adds
+    one division and the five sums it is formed from."""
+    f = W_EXP + log_sum_flops(chunk) + 10
     if grad:
-        f += W_DIV + 22
+        f += W_DIV + 10
     return f
 
 
@@ -646,8 +678,9 @@ def config0_above_mall(n: int = 1 << 26, steps: int = 20):
     tb = torch.from_numpy(truth * 1.001).cuda()
     o = torch.empty(1 + m.n_params, dtype=torch.float64, device="cuda")
     w, k, info = time_async(m, t, x, o, steps, 3, True, alt=tb)
-    fl = mix1d_flops_per_event(True, m.chunk)
-    r = {"config0_mall_events": n, "config0_mall_chunk": m.chunk, "config0_mall_events_per_s": n * steps / w,
+    chunk = chunk_in_use(m, n, 8)
+    fl = mix1d_flops_per_event(True, chunk)
+    r = {"config0_mall_events": n, "config0_mall_chunk": chunk, "config0_mall_events_per_s": n * steps / w,
          "config0_mall_ms_per_step": 1e3 * w / steps, "config0_mall_event_kernel_us": 1e3 * k,
          "config0_mall_hbm_gbs": 8.0 * n / (k * 1e-3) / 1e9,
          "config0_mall_tflops": fl * n / (k * 1e-3) / 1e12, "config0_mall_flops_per_event": fl,
@@ -674,7 +707,7 @@ def config3_leg(steps: int = 20):
     w3, k3, info = time_async(m3, t3, ev3, o3, steps, 3, True, alt=t3b)
     r = {"config3_events_per_s": 4_000_000 / w3 * steps, "config3_ms_per_step": 1e3 * w3 / steps,
          "config3_event_kernel_us": k3 * 1e3,
-         "config3_event_kernel_tflops": dalitz_flops_per_event(desc3, 2, m3.chunk) * 4e6 / (k3 * 1e-3) / 1e12,
+         "config3_event_kernel_tflops": dalitz_flops_per_event(desc3, 2, chunk_in_use(m3, 4_000_000, 2)) * 4e6 / (k3 * 1e-3) / 1e12,
          "config3_timing": info}
     r.update(config3_fits(m3, th3))
     return r

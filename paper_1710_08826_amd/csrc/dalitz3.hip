@@ -1,9 +1,9 @@
 // Three-body Dalitz-plot amplitude model (the paper's amplitude analyses of
 // three-body decays, Sec. 1 and 5): host launchers, and the kernels that do
-// not depend on the model's structure (prologue, level-2 finalize, per-event
-// density, domain check).  The per-event, grid and normalization-matrix
-// passes live in dalitz_device.hpp and are compiled at model creation with
-// the model's structure as compile-time constants (dalitz_jit below).
+// not depend on the model's structure (prologue, level-2 finalize, domain
+// check).  The per-event, density, grid and normalization-matrix passes and the
+// event generator live in dalitz_device.hpp and are compiled at model creation
+// with the model's structure as compile-time constants (dalitz_jit below).
 #include <algorithm>
 #include <cmath>
 #include <sstream>

@@ -180,14 +180,6 @@ __device__ __forceinline__ void bw_amplitude(const double* __restrict__ rk, doub
   ai = u * b;
 }
 
-__device__ __forceinline__ void dalitz_bw(const double* __restrict__ rk, double s, double G, double H, double& ar,
-                                          double& ai, double& a, double& b, double& d) {
-  double D;
-  bw_denominator(rk, s, G, a, b, D);
-  d = rcp_fast(D);
-  bw_amplitude(rk, H, a, b, d, ar, ai);
-}
-
 template <class S, int C>
 __host__ __device__ constexpr bool pair_used() {
   return shape_uses<S>(C, 0) || shape_uses<S>(C, 1) || shape_uses<S>(C, 2);

@@ -253,7 +253,6 @@ static void compile_dalitz3(const json::Value& d, fn_model* m, bool device = tru
     if (L < 0 || L > 2) throw Error(FN_E_INVALID, "dalitz3: L must be 0, 1 or 2");
     dc.chan[k] = c;
     dc.L[k] = (int)L;
-    dc.ch[c].useL[L] = 1;
     m->fixed_ls[2 * k] = res[k].at("m0").number();
     m->fixed_ls[2 * k + 1] = res[k].at("w0").number();
   }

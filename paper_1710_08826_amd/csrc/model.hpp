@@ -84,7 +84,6 @@ struct DalitzChan {               // a pair AB with bachelor C
   double sum2, dif2;              // (mA+mB)^2, (mA-mB)^2
   double Psum2, Pdif2;            // (M+mC)^2, (M-mC)^2
   double zc;                      // (M^2 - mC^2)(mB^2 - mA^2)
-  int useL[3];                    // which L occur in this pair
 };
 
 struct DalitzConst {
