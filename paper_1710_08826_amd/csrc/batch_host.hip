@@ -59,11 +59,7 @@ struct fn_batch {
     if (step_done) (void)hipEventDestroy(step_done);
     if (stream) (void)hipStreamDestroy(stream);
     if (h_st) (void)hipHostFree(h_st);
-    if (h_ev) (void)hipHostFree(h_ev);
-    if (h_nev) (void)hipHostFree(h_nev);
-    if (h_nrun) (void)hipHostFree(h_nrun);
-    if (h_rows) (void)hipHostFree(h_rows);
-    if (h_fin) (void)hipHostFree(h_fin);
+    if (h_rows) (void)hipHostFree(h_rows);  // and what shares its allocation
   }
 };
 
@@ -151,11 +147,13 @@ fn_status fn_batch_create(fn_model* m, int32_t max_fits, int64_t max_events_per_
     b->rres.reserve(sizeof(double) * (size_t)max_fits * (3 + 2 * b->P));
     hip_check(hipMemsetAsync(b->stat.ptr, 0, sizeof(int) * max_fits, b->stream), "hipMemsetAsync");
     b->h_st = (BfgsState*)pinned(sizeof(BfgsState) * max_fits);
-    b->h_ev = (const double**)pinned(sizeof(double*) * max_fits);
-    b->h_nev = (int64_t*)pinned(sizeof(int64_t) * max_fits);
-    b->h_nrun = (int*)pinned(sizeof(int));
-    b->h_rows = (double*)pinned(sizeof(double) * (size_t)max_fits * (4 + 2 * b->P));
-    b->h_fin = (int*)pinned(sizeof(int) * max_fits);
+    // one pinned allocation for the rest (each costs about as much as a step)
+    const size_t F = max_fits, row = 4 + 2 * b->P;
+    b->h_rows = (double*)pinned(sizeof(double) * F * (row + 2) + sizeof(int) * (F + 1));
+    b->h_ev = (const double**)(b->h_rows + F * row);
+    b->h_nev = (int64_t*)(b->h_ev + F);
+    b->h_fin = (int*)(b->h_nev + F);
+    b->h_nrun = b->h_fin + F;
     std::vector<int64_t> pb(max_fits);
     for (int f = 0; f < max_fits; ++f) pb[f] = (int64_t)f * b->rows_per_slot;
     // all slots idle, no events
