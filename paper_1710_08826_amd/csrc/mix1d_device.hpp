@@ -71,12 +71,18 @@ __device__ inline bool mix1d_component(const Mix1dConst& mc, const double* __res
     }
     case kExp: {
       const double tau = p0, D = hi - lo;
-      if (fabs(tau) < 1e-12) N = D * (1.0 + 0.5 * tau * (hi + lo));
-      else N = exp(tau * lo) * expm1(tau * D) / tau;
       const double td = tau * D;
+      const double up = expm1(td), dn = -expm1(-td);
+      if (fabs(tau) < 1e-12) N = D * (1.0 + 0.5 * tau * (hi + lo));
+      else N = exp(tau * lo) * up / tau;
       if (fabs(td) < 1e-3) d0 = 0.5 * (hi + lo) + tau * D * D / 12.0 - td * td * td * D / 720.0;
-      else d0 = lo + D / (-expm1(-td)) - 1.0 / tau;
+      else d0 = lo + D / dn - 1.0 / tau;
       t.a[k] = tau;
+      // the events passes' form (mix_term): relative to the end of the range
+      // where the shape is largest, and 1 over its integral in these units
+      t.b[k] = tau > 0.0 ? hi : lo;
+      const bool flat = fabs(tau) < 1e-12;
+      t.c[k] = (flat ? 1.0 : tau) / (flat ? D * (1.0 - 0.5 * fabs(td)) : (tau > 0.0 ? dn : up));
       break;
     }
     case kArgus: {
@@ -192,7 +198,11 @@ __host__ __device__ constexpr int mix_sig_pivot(int sig) {
 
 // A component's shape at x as pre e^arg, and its derivatives' factors:
 // d ln s / d(its parameters) are alpha0 m0 and alpha1 m1, alpha constants of
-// the fit (mix_alpha).
+// the fit (mix_alpha).  An exponential is taken relative to its value at the
+// end of the range where it is largest (e^(tau (x - x0)), with its integral and
+// d ln N in the same units: mix_invn, mix_dlnn): its shape then spans (0, 1] as
+// the others do, whatever the slope.  Relative to x = 0 it reaches e^709 on
+// legal ranges, where sums weighted by it overflow and its weight is subnormal.
 struct MixTerm {
   double pre, arg, m0, m1;
 };
@@ -203,13 +213,14 @@ __device__ __forceinline__ MixTerm mix_term(const Mix1dTable& t, int k, double x
     const double z = (x - t.a[k]) * t.b[k];
     r = {1.0, -0.5 * z * z, z, z * z};
   } else if (TYPE == kExp) {
-    r = {1.0, t.a[k] * x, x, 0.0};
+    const double d = x - t.b[k];
+    r = {1.0, t.a[k] * d, d, 0.0};
   } else if (TYPE == kArgus) {
     const double xx = x * x, w = 1.0 - xx * t.a[k];
     const bool in = w > 0.0;
     const double wi = in ? w : 1.0;
     r.pre = in ? x * sqrt(wi) : 0.0;
-    r.arg = t.b[k] * wi;
+    r.arg = in ? t.b[k] * wi : -__builtin_inf();  // e^-inf: the pivot's own argument is the larger one
     r.m0 = in ? (0.5 * rcp_acc(wi) + t.b[k]) * xx : 0.0;
     r.m1 = in ? w : 0.0;
   } else {
@@ -225,6 +236,14 @@ __device__ __forceinline__ double mix_alpha(const Mix1dTable& t, int k, int j) {
   if (TYPE == kArgus) return j == 0 ? 2.0 * t.a[k] * t.c[k] : 1.0;
   if (TYPE == kBW) return j == 0 ? 2.0 : -0.5 * t.c[k];
   return 1.0;
+}
+
+// 1 / N_k and d ln N_k / d(parameter j) in mix_term's units.
+__device__ __forceinline__ double mix_invn(int type, const Mix1dTable& t, int k) {
+  return type == kExp ? t.c[k] : t.invN[k];
+}
+__device__ __forceinline__ double mix_dlnn(int type, const Mix1dTable& t, int k, int j) {
+  return type == kExp && j == 0 ? t.dlnN[k][0] - t.b[k] : t.dlnN[k][j];
 }
 
 // slot[s] += w * dP/d(slot s) at one point: shape parameters of component k at
@@ -253,90 +272,122 @@ __device__ __forceinline__ void mix1d_add_dp(int K, const Mix1dTable& t, const d
 // are V_k = sum v, sum v m0 and sum v m1 with v = -s_k / P, and the slots
 // follow from them once per thread: shape slots f_k/N_k (alpha sum v m - V d ln
 // N), fraction slot V_0/N_0 - V_1/N_1.  With a pivot p (mix_sig_pivot) the
-// density is e^arg_p (g_p + g_o pre_o e^(arg_o - arg_p)): one exponential
-// serves both components, and sum arg_p is the pivot's parameter times sum x.
-// The Gaussian and exponential mixture takes 42 VALU instructions per event
-// instead of 112: NLL and gradient of 2^26 events 207 -> 149 us, and 131 us
-// with the loads below (their bytes alone take 88 at 6.1 TB/s); 512 toy fits to
+// density is e^arg_p (g_p + g_o pre_o e^d), d = arg_o - arg_p: one exponential
+// serves both components, and sum arg_p is the pivot's parameter times sum (x -
+// x0).  d is at most |tau| times the range's length, and where that exceeds
+// kPivotMax the larger of the two arguments is taken out instead, so that no
+// factor exceeds 1: e^d overflows from 709 on, and before that ln P is the small
+// difference of two parts (3e-14 of the sum at tau = -70 on [0, 10]).  Events
+// that overflow nevertheless lie outside the range, and the wave takes its
+// chunk again in that form.
+// The Gaussian and exponential mixture takes 43 VALU instructions per event (52
+// relative to the larger argument) instead of 112 with an exponential for each:
+// NLL and gradient of 2^26 events 207 -> 149 us, 134 with the loads below (their
+// bytes alone take 88 at 6.1 TB/s), 149 at slopes past the line; 512 toy fits to
 // convergence 3.87 -> 3.23 ms.
+constexpr double kPivotMax = 16.0;
 template <bool GRAD, int SIG>
-__device__ inline void mix1d_typed_chunk(const Mix1dTable* __restrict__ tabp, const double* __restrict__ x, int64_t n,
-                                         int64_t chunk_idx, int chunk, double* __restrict__ out_row, double* lds) {
+__device__ inline void mix1d_typed_chunk(const Mix1dConst& mc, const Mix1dTable* __restrict__ tabp,
+                                         const double* __restrict__ x, int64_t n, int64_t chunk_idx, int chunk,
+                                         double* __restrict__ out_row, double* lds) {
   constexpr int KMAX = 2;
   constexpr int NV = GRAD ? mix_nv(KMAX) : 1;
   constexpr int K = mix_sig_K(SIG), PV = mix_sig_pivot(SIG);
   constexpr int T0 = mix_sig_type(SIG, 0), T1 = K == 2 ? mix_sig_type(SIG, 1) : T0;
   const Mix1dTable& t = *tabp;
-  const double g0 = t.frac[0] * t.invN[0], g1 = K == 2 ? t.frac[1] * t.invN[1] : 0.0;
-  double V0 = 0.0, A0 = 0.0, B0 = 0.0, V1 = 0.0, A1 = 0.0, B1 = 0.0, X = 0.0;
+  const double i0 = mix_invn(T0, t, 0), i1 = K == 2 ? mix_invn(T1, t, 1) : 0.0;
+  const double g0 = t.frac[0] * i0, g1 = K == 2 ? t.frac[1] * i1 : 0.0;
+  double V0, A0, B0, V1, A1, B1, X, M;
   const int64_t base = chunk_idx * chunk;
   const int64_t end = base + chunk < n ? base + chunk : n;
   LogProd lp;  // -sum ln P enters acc[0] once per thread, at the end
-  auto event = [&](double xv) {
-    const MixTerm a = mix_term<T0>(t, 0, xv), b = mix_term<T1>(t, 1, xv);
-    double s0, s1 = 0.0;
-    if (PV == 1) {
-      s0 = a.pre * exp_fast(a.arg - b.arg);
-      s1 = 1.0;
-      X += xv;
-    } else if (PV == 0) {
-      s0 = 1.0;
-      s1 = b.pre * exp_fast(b.arg - a.arg);
-      X += xv;
-    } else {
-      s0 = T0 == kBW ? a.pre : a.pre * exp_fast(a.arg);
-      if (K == 2) s1 = T1 == kBW ? b.pre : b.pre * exp_fast(b.arg);
-    }
-    const double P = K == 2 ? __builtin_fma(g1, s1, g0 * s0) : g0 * s0;
-    lp.mul(P);
-    if (GRAD) {
-      const double w = -rcp_fast(P);
-      const double v0 = w * s0, v1 = w * s1;
-      V0 += v0;
-      A0 = __builtin_fma(v0, a.m0, A0);
-      if (T0 != kExp) B0 = __builtin_fma(v0, a.m1, B0);
-      if (K == 2) {
-        V1 += v1;
-        A1 = __builtin_fma(v1, b.m0, A1);
-        if (T1 != kExp) B1 = __builtin_fma(v1, b.m1, B1);
+  // the chunk's events; larger: relative to the larger argument (std::true_type) or to the pivot's
+  auto pass = [&](auto larger) {
+    V0 = A0 = B0 = V1 = A1 = B1 = X = M = 0.0;
+    lp = LogProd{};
+    auto event = [&](double xv) {
+      const MixTerm a = mix_term<T0>(t, 0, xv), b = mix_term<T1>(t, 1, xv);
+      double s0, s1 = 0.0;
+      if constexpr (PV >= 0) {
+        const MixTerm &p = PV == 1 ? b : a, &o = PV == 1 ? a : b;
+        const double d = o.arg - p.arg;
+        double so, sp = 1.0;
+        X += p.m0;
+        if constexpr (decltype(larger)::value) {
+          const double e = exp_fast(-fabs(d));
+          const bool up = d > 0.0;
+          so = (PV == 1 ? T0 : T1) == kArgus ? (up ? o.pre : o.pre * e) : (up ? 1.0 : e);
+          sp = up ? e : 1.0;
+          M += up ? d : 0.0;
+        } else {
+          so = o.pre * exp_fast(d);
+        }
+        s0 = PV == 1 ? so : sp;
+        s1 = PV == 1 ? sp : so;
+      } else {
+        s0 = T0 == kBW ? a.pre : a.pre * exp_fast(a.arg);
+        if (K == 2) s1 = T1 == kBW ? b.pre : b.pre * exp_fast(b.arg);
       }
-    }
-  };
-  // groups of four events per thread, the next group's loads in flight while
-  // one is worked on (one load at a time left the pass waiting for memory),
-  // then the rest one by one
-  constexpr int U = 4;
-  const int64_t full = (end - base) / (U * kBlock);
-  const double* xp = x + base + threadIdx.x;
-  double nx[U];
-  if (full > 0) {
-#pragma unroll
-    for (int u = 0; u < U; ++u) nx[u] = xp[u * kBlock];
-  }
-  for (int64_t g = 0; g < full; ++g) {
-    double cur[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) cur[u] = nx[u];
-    xp += U * kBlock;
-    if (g + 1 < full) {
+      const double P = K == 2 ? __builtin_fma(g1, s1, g0 * s0) : g0 * s0;
+      lp.mul(P);
+      if (GRAD) {
+        const double w = -rcp_fast(P);
+        const double v0 = w * s0, v1 = w * s1;
+        V0 += v0;
+        A0 = __builtin_fma(v0, a.m0, A0);
+        if (T0 != kExp) B0 = __builtin_fma(v0, a.m1, B0);
+        if (K == 2) {
+          V1 += v1;
+          A1 = __builtin_fma(v1, b.m0, A1);
+          if (T1 != kExp) B1 = __builtin_fma(v1, b.m1, B1);
+        }
+      }
+    };
+    // groups of four events per thread, the next group's loads in flight while
+    // one is worked on (one load at a time left the pass waiting for memory),
+    // then the rest one by one
+    constexpr int U = 4;
+    const int64_t full = (end - base) / (U * kBlock);
+    const double* xp = x + base + threadIdx.x;
+    double nx[U];
+    if (full > 0) {
 #pragma unroll
       for (int u = 0; u < U; ++u) nx[u] = xp[u * kBlock];
     }
+    for (int64_t g = 0; g < full; ++g) {
+      double cur[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) event(cur[u]);
+      for (int u = 0; u < U; ++u) cur[u] = nx[u];
+      xp += U * kBlock;
+      if (g + 1 < full) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) nx[u] = xp[u * kBlock];
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) event(cur[u]);
+    }
+    for (int64_t i = base + full * (U * kBlock) + threadIdx.x; i < end; i += kBlock) event(x[i]);
+  };
+  bool steep = false;
+  if constexpr (PV >= 0) steep = fabs(t.a[PV]) * (mc.hi - mc.lo) > kPivotMax;
+  if (__builtin_expect(!steep, 1)) {
+    pass(std::false_type{});
+    if constexpr (PV >= 0) steep = __any(!(lp.m < __builtin_inf()));
   }
-  for (int64_t i = base + full * (U * kBlock) + threadIdx.x; i < end; i += kBlock) event(x[i]);
+  if constexpr (PV >= 0) {
+    if (__builtin_expect(steep, 0)) pass(std::true_type{});
+  }
   double acc[NV];
   acc[0] = -lp.log();
-  if (PV >= 0) acc[0] = __builtin_fma(-t.a[PV >= 0 ? PV : 0], X, acc[0]);
+  if (PV >= 0) acc[0] -= __builtin_fma(t.a[PV >= 0 ? PV : 0], X, M);
   if (GRAD) {
-    acc[1] = g0 * __builtin_fma(-V0, t.dlnN[0][0], mix_alpha<T0>(t, 0, 0) * A0);
+    acc[1] = g0 * __builtin_fma(-V0, mix_dlnn(T0, t, 0, 0), mix_alpha<T0>(t, 0, 0) * A0);
     acc[2] = T0 == kExp ? 0.0 : g0 * __builtin_fma(-V0, t.dlnN[0][1], mix_alpha<T0>(t, 0, 1) * B0);
     acc[3] = acc[4] = acc[5] = acc[6] = 0.0;
     if (K == 2) {
-      acc[3] = g1 * __builtin_fma(-V1, t.dlnN[1][0], mix_alpha<T1>(t, 1, 0) * A1);
+      acc[3] = g1 * __builtin_fma(-V1, mix_dlnn(T1, t, 1, 0), mix_alpha<T1>(t, 1, 0) * A1);
       acc[4] = T1 == kExp ? 0.0 : g1 * __builtin_fma(-V1, t.dlnN[1][1], mix_alpha<T1>(t, 1, 1) * B1);
-      acc[5] = V0 * t.invN[0] - V1 * t.invN[1];
+      acc[5] = V0 * i0 - V1 * i1;
     }
   }
   block_sum_row<NV>(acc, lds, out_row);
@@ -369,7 +420,7 @@ __device__ inline void mix1d_generic_chunk(const Mix1dConst& mc, const Mix1dTabl
   double g[KMAX], V[KMAX], A[KMAX], B[KMAX];
 #pragma unroll
   for (int k = 0; k < KMAX; ++k) {
-    g[k] = k < K ? t.frac[k] * t.invN[k] : 0.0;
+    g[k] = k < K ? t.frac[k] * mix_invn(mc.type[k], t, k) : 0.0;
     V[k] = A[k] = B[k] = 0.0;
   }
   const int64_t base = chunk_idx * chunk;
@@ -419,7 +470,7 @@ __device__ inline void mix1d_generic_chunk(const Mix1dConst& mc, const Mix1dTabl
       // nothing is kept per component: one copy of the shapes' code (unrolled,
       // its first pass through the instruction cache cost small samples 1.5 us)
 #pragma unroll 1
-      for (int k = 0; k < K; ++k) component(k, 0, t.frac[k] * t.invN[k]);
+      for (int k = 0; k < K; ++k) component(k, 0, t.frac[k] * mix_invn(mc.type[k], t, k));
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -445,14 +496,14 @@ __device__ inline void mix1d_generic_chunk(const Mix1dConst& mc, const Mix1dTabl
     double last = 0.0;
 #pragma unroll
     for (int k = 0; k < KMAX; ++k)
-      if (k == K - 1) last = V[k] * t.invN[k];
+      if (k == K - 1) last = V[k] * mix_invn(mc.type[k], t, k);
 #pragma unroll
     for (int k = 0; k < KMAX; ++k) {
       const bool on = k < K;
       const int type = on ? mc.type[k] : kExp;
-      acc[1 + 2 * k] = on ? g[k] * __builtin_fma(-V[k], t.dlnN[k][0], mix_alpha_of(type, t, k, 0) * A[k]) : 0.0;
+      acc[1 + 2 * k] = on ? g[k] * __builtin_fma(-V[k], mix_dlnn(type, t, k, 0), mix_alpha_of(type, t, k, 0) * A[k]) : 0.0;
       acc[2 + 2 * k] = type != kExp ? g[k] * __builtin_fma(-V[k], t.dlnN[k][1], mix_alpha_of(type, t, k, 1) * B[k]) : 0.0;
-      acc[1 + 2 * KMAX + k] = k < K - 1 ? V[k] * t.invN[k] - last : 0.0;
+      acc[1 + 2 * KMAX + k] = k < K - 1 ? V[k] * mix_invn(type, t, k) - last : 0.0;
     }
   }
   block_sum_row<NV>(acc, lds, out_row);
@@ -466,7 +517,7 @@ __device__ inline void mix1d_chunk(const Mix1dConst& mc, const Mix1dTable* __res
                                    const double* __restrict__ x, int64_t n, int64_t chunk_idx,
                                    int chunk, double* __restrict__ out_row, double* lds) {
   static_assert(SIG == 0 || KMAX == 2, "typed passes hold two components");
-  if constexpr (SIG != 0) mix1d_typed_chunk<GRAD, SIG>(tabp, x, n, chunk_idx, chunk, out_row, lds);
+  if constexpr (SIG != 0) mix1d_typed_chunk<GRAD, SIG>(mc, tabp, x, n, chunk_idx, chunk, out_row, lds);
   else mix1d_generic_chunk<GRAD, KMAX>(mc, tabp, x, n, chunk_idx, chunk, out_row, lds);
 }
 
