@@ -130,9 +130,7 @@ fn_status fn_batch_create(fn_model* m, int32_t max_fits, int64_t max_events_per_
     b->max_ev = max_events_per_fit;
     b->P = m->P;
     b->rule = m->rule();
-    // most rows of any fit up to that size (a rule with slots never gives more)
-    b->rows_per_slot = (max_events_per_fit + b->rule.lo - 1) / b->rule.lo;
-    if (b->rule.slots > 0) b->rows_per_slot = std::min<int64_t>(b->rows_per_slot, b->rule.slots);
+    b->rows_per_slot = b->rule.rows_upto(max_events_per_fit);
     const int kmax = mix1d_kmax(m->mix.K);
     const int nv = mix1d_nv(kmax, true);
     hip_check(hipStreamCreateWithFlags(&b->stream, hipStreamNonBlocking), "hipStreamCreate");

@@ -23,7 +23,7 @@ constexpr int kMaxChunk = 1 << 22;    // most events per workgroup
 // Events per workgroup of a call on n events: lo, or (slots > 0) the smallest
 // multiple of kBlock from lo on that gives at most `slots` workgroups -- one
 // round of the workgroups that keep the device busy, each as long as the
-// sample allows.  A chunk fixed by the model's description or by the autotuner
+// sample allows -- up to kMaxChunk, beyond which there are more.  A chunk fixed by the model's description or by the autotuner
 // has slots = 0.
 struct ChunkRule {
   int lo, slots;
@@ -32,6 +32,14 @@ struct ChunkRule {
     const int64_t per = (n + slots - 1) / slots;
     const int64_t c = (per + kBlock - 1) / kBlock * kBlock;
     return c < lo ? lo : (c > kMaxChunk ? kMaxChunk : (int)c);
+  }
+  // Most workgroups of any sample of up to n events: `slots` from lo x slots
+  // events on, more only where the largest chunk leaves more.
+  __host__ __device__ int64_t rows_upto(int64_t n) const {
+    const int64_t least = (n + lo - 1) / lo;
+    if (slots <= 0 || least <= slots) return least;
+    const int64_t c = (*this)(n), rows = (n + c - 1) / c;
+    return rows > slots ? rows : slots;
   }
 };
 
