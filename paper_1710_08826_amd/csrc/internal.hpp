@@ -133,6 +133,8 @@ struct Workspace {
   size_t front = 0, back = 0;
   double* take_front(size_t count);
   double* take_back(size_t count);
+  // count doubles that overlap the rest: for launches whose results are read before the rest is written
+  double* before_rest(size_t count);
 };
 void run_nll(fn_model* m, const ParamBlock* pb, const double* theta_dev, const double* ev, int64_t n, int64_t ld,
              bool grad, double* out_user, hipStream_t s, Workspace* ws = nullptr);

@@ -448,6 +448,12 @@ double* Workspace::take_back(size_t count) {
   back += count;
   return base + (cap - back);
 }
+double* Workspace::before_rest(size_t count) {
+  if (count > cap)
+    throw Error(FN_E_INVALID, "the call needs " + std::to_string(count) + " doubles of scratch, more than the " +
+                                  std::to_string(cap) + " available");
+  return base;
+}
 
 void run_nll(fn_model* m, const ParamBlock* pb, const double* theta_dev, const double* ev, int64_t n, int64_t ld,
              bool grad, double* out_user, hipStream_t s, Workspace* ws) {
@@ -477,6 +483,11 @@ void run_nll(fn_model* m, const ParamBlock* pb, const double* theta_dev, const d
       npart = m->npart();
     }
   };
+  // a cached matrix's rows: dead once its level-2 step has run, before the events pass writes its own rows
+  auto matrix_rows = [&](size_t doubles) {
+    if (ws) npart = ws->before_rest(doubles);
+    else norm_rows(doubles);
+  };
   // workspace calls are never timed: timing takes HIP events from a pool
   const bool launches = nch > 0 && !ws;
   if (m->kind == kKindMix1d) {
@@ -504,7 +515,7 @@ void run_nll(fn_model* m, const ParamBlock* pb, const double* theta_dev, const d
     TddpArg ca{};
     if (pb) std::memcpy(ca.v, pb->v, sizeof(double) * m->P);
     if (!m->M_valid) {
-      norm_rows(tddp_gram_doubles(dc));
+      matrix_rows(tddp_gram_doubles(dc));
       tddp_launch_mmatrices(*m->tddp_jit, dc, m->table_dal(), npart, m->Mc(), s);
       m->M_valid = true;
     }
@@ -526,7 +537,7 @@ void run_nll(fn_model* m, const ParamBlock* pb, const double* theta_dev, const d
     const Td4FitConst* fc = (const Td4FitConst*)m->d_fixed.ptr;
     td4_launch_prologue(tc, pb, theta_dev, m->P, fc, nullptr, 1, m->table_td4(), s);
     if (!m->M_valid) {
-      norm_rows(td4_gram_doubles(tc, m->n_mc));
+      matrix_rows(td4_gram_doubles(tc, m->n_mc));
       td4_launch_mmatrix(*m->td4_jit, tc, m->table_td4(), 1, (const double*)m->d_mc.ptr, m->n_mc, m->n_mc, npart,
                          m->Mc(), s);
       m->M_valid = true;
@@ -585,7 +596,7 @@ void run_nll(fn_model* m, const ParamBlock* pb, const double* theta_dev, const d
       const int64_t ncell = (int64_t)dc.nx * dc.ny;
       const int gchunk = gram_chunk(ncell);
       const int64_t mrows = nchunks_for(ncell, gchunk);
-      norm_rows((size_t)mrows * dc.K * (dc.K + 1));
+      matrix_rows((size_t)mrows * dc.K * (dc.K + 1));
       dalitz_launch_gram(*m->dal_jit, dc, m->table_dal(), gchunk, mrows, npart, m->Mc(), s);
       m->M_valid = true;
     }
