@@ -137,7 +137,7 @@ __host__ __device__ inline TimeConst time_const(double G, double s) {
   k.ni2s2 = -0.5 / s2;
   k.kg = G * s * kInvSqrt2Pi;
   k.g2s2 = G * G * s2;
-  k.s3 = 3.0 * s;
+  k.s3 = s * fmax(3.0, G * s);
   return k;
 }
 
@@ -179,14 +179,17 @@ __device__ __forceinline__ void time_terms(TimeSeries& a, double v, double w, do
 // (u = G s^2 - t, g = exp(-t^2 / 2 s^2); for u < 0 the terms of each step have
 // one sign).  So one real h and a Taylor series give what otherwise takes two
 // real and one complex h.  |h_n d^n / n!| <= h_0 r^n / n! with r = max(|x|,
-// |y|) G (|t| + 3 s) for n <= 20, which puts the rest after ten terms below
-// 3e-18 h_0 (3e-16 in the derivatives' sums) for r <= 1/8 and after twenty
-// below 2e-18 (4e-17) for r <= 5/4.  A wave takes ten terms, twenty when one of
-// its events needs them, and the three functions evaluated one by one beyond
-// that (the line lies where twenty terms, 160 multiply-adds, stop sufficing;
-// the three evaluations take about 460 instructions).  The events are few
-// there: mixing parameters of the size fits meet (below 0.01) keep r <= 1/8 up
-// to twelve lifetimes.
+// |y|) G (|t| + s max(3, G s)) for n <= 20, which puts the rest after ten terms
+// below 3e-18 h_0 (3e-16 in the derivatives' sums) for r <= 1/8 and after twenty
+// below 2e-18 (4e-17) for r <= 5/4.  For u > 0 the recurrence cancels and each
+// step multiplies its rounding error by u, which r bounds as well: G s in place
+// of 3 for resolutions above three lifetimes, where u reaches G s^2 (with 3 s
+// there, the error grew to 7e-11 of h_0 at thirty lifetimes).  A wave takes ten
+// terms, twenty when one of its events needs them, and the three functions
+// evaluated one by one beyond that (the line lies where twenty terms, 160
+// multiply-adds, stop sufficing; the three evaluations take about 460
+// instructions).  The events are few there: mixing parameters of the size fits
+// meet (below 0.01) keep r <= 1/8 up to twelve lifetimes.
 // One NLL and gradient: four-body, 10M events, twenty amplitudes 456 -> 349 us;
 // three-body, 1M events, sixteen resonances 105.8 -> 94.5 us.  The rare forms are
 // kept out of the registers of the common one: their branches are marked

@@ -33,7 +33,7 @@ struct TimeConst {
   double g, s, s2;
   double gs2, hg2s2, g2s2;  // G s^2, G^2 s^2 / 2, G^2 s^2
   double iz, ni2s2;         // 1/(s sqrt 2), -1/(2 s^2)
-  double kg, s3;            // G s / sqrt(2 pi), 3 s
+  double kg, s3;            // G s / sqrt(2 pi), s max(3, G s)
 };
 
 struct Td4Const {
