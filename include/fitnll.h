@@ -246,6 +246,7 @@ fn_status fn_norm(fn_model* m, const double* theta_host, double* norm_host,
 
 /* Normalized density P~(x_i)/I per event into p_dev (n doubles, device,
  * caller-owned), the per-event function value of Sec. 1, for plots and tests.
+ * An event's density does not depend on the other events of the call.
  * theta_host: P doubles.  Synchronous.  FN_E_INVALID for tddp3 models and
  * for a NULL output with n > 0. */
 fn_status fn_eval(fn_model* m, const double* theta_host, const double* ev, int64_t n,

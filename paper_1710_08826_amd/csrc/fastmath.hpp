@@ -129,9 +129,12 @@ __device__ __attribute__((noinline)) inline void sincos_any(double x, double* sn
 // parts), the two functions of r by polynomials in r^2 at the Chebyshev nodes
 // of [0, pi^2/16] (errors 2.0e-17 relative and 9e-19), exchanged and signed by
 // k's quadrant.  Absolute error below 2e-16 for |x| < 1e5; a wave with a
-// larger (or not finite) argument takes the library's function.
+// larger (or not finite) argument takes the library's function (ALONE: only the
+// lanes that have one).
+template <bool ALONE = false>
 __device__ __forceinline__ void sincos_fast(double x, double& sn, double& cs) {
-  if (__builtin_expect(__any(!(fabs(x) < 1e5)), 0)) {
+  const bool far = !(fabs(x) < 1e5);
+  if (__builtin_expect(ALONE ? far : __any(far), 0)) {
     double a, b;
     sincos_any(x, &a, &b);
     sn = a;

@@ -96,7 +96,8 @@ __device__ inline void h_real(const double* __restrict__ we, double a, double t,
   dh = u * h - s * kInvSqrt2Pi * g;
 }
 
-// h(a; t) and dh/da for complex a.
+// h(a; t) and dh/da for complex a (ALONE: time_fns).
+template <bool ALONE>
 __device__ inline void h_cplx(const double* __restrict__ wa, double L, cplx a, double t, double s, double s2, double g,
                               cplx& h, cplx& dh) {
   const cplx u = {a.re * s2 - t, a.im * s2};
@@ -110,7 +111,7 @@ __device__ inline void h_cplx(const double* __restrict__ wa, double L, cplx a, d
     const double er = 0.5 * (a.re * a.re - a.im * a.im) * s2 - a.re * t;
     const double ei = a.re * a.im * s2 - a.im * t;
     double sn, cs;
-    sincos_fast(ei, sn, cs);
+    sincos_fast<ALONE>(ei, sn, cs);
     const double e = exp_fast(er);
     h = {e * cs - 0.5 * g * w.re, e * sn - 0.5 * g * w.im};
   }
@@ -197,18 +198,26 @@ __device__ __forceinline__ void time_terms(TimeSeries& a, double v, double w, do
 // library's inlined, its coefficients filled some sixty vector registers over
 // the whole event loop: four-body pass 227 -> 185 registers, 290 -> 281 us;
 // three-body 296 -> 256 and two waves per SIMD instead of one, 83.4 -> 77.4 us).
-template <bool GRAD>
+//
+// ALONE: each event takes the form its own r asks for, and its sine and cosine
+// likewise, so that its value does not depend on the others of its wave (the
+// density, which is handed out per event).  A wave with events of two forms then
+// takes both: 1M events, nine amplitudes, 43 us a call either way for mixing
+// parameters below 0.01, 57 instead of 53 at x = 0.8, whose events fall on both
+// sides of the line.
+template <bool GRAD, bool ALONE = false>
 __device__ __forceinline__ void time_fns(const TimeConst& k, const double* __restrict__ wt, double wL, double x,
                                          double y, double t, TimeFns& o) {
   const double g = exp_fast(t * t * k.ni2s2);
   const double r = fmax(fabs(x), fabs(y)) * k.g * (fabs(t) + k.s3);
-  if (__builtin_expect(__any(!(r <= kTimeSeriesMax)), 0)) {
+  const bool beyond = !(r <= kTimeSeriesMax), more = r > kTimeSeriesTen;
+  if (__builtin_expect(ALONE ? beyond : __any(beyond), 0)) {
     double hp, dhp, hm, dhm;
     cplx hc, dhc;
     const double* we = wt + kWeidN;
     h_real(we, k.g * (1.0 - y), t, k.s, k.s2, g, hp, dhp);
     h_real(we, k.g * (1.0 + y), t, k.s, k.s2, g, hm, dhm);
-    h_cplx(wt, wL, {k.g, -k.g * x}, t, k.s, k.s2, g, hc, dhc);
+    h_cplx<ALONE>(wt, wL, {k.g, -k.g * x}, t, k.s, k.s2, g, hc, dhc);
     o.Hc = 0.5 * (hp + hm);
     o.Hs = 0.5 * (hp - hm);
     o.hr = hc.re;
@@ -241,7 +250,7 @@ __device__ __forceinline__ void time_fns(const TimeConst& k, const double* __res
   a.ey = a.ce * y2;
   a.ex = a.ce * nx2;
   time_terms<GRAD>(a, v, w, y2, nx2, 1, 5);
-  if (__builtin_expect(__any(r > kTimeSeriesTen), 0)) time_terms<GRAD>(a, v, w, y2, nx2, 5, 10);
+  if (__builtin_expect(ALONE ? more : __any(more), 0)) time_terms<GRAD>(a, v, w, y2, nx2, 5, 10);
   o.Hc = c0 + a.ey;
   o.Hs = -y * a.oy;
   o.hr = c0 + a.ex;
@@ -320,7 +329,7 @@ struct Td4Point {
   double ssc, sss;  // 1/2 sin theta12 sin theta34 (cos phi, sin phi)
 };
 
-template <class S>
+template <class S, bool ALONE = false>
 __device__ __forceinline__ void td4_point_s(const Td4Const& tc, const Td4Table& tb, double m12, double m34, double c12,
                                             double c34, double phi, Td4Point<S>& p) {
   pair_amps_s<S, false>(m12, tc.sum12, tc.dif12, tc.r2, tb.r12, p.a12);
@@ -337,7 +346,7 @@ __device__ __forceinline__ void td4_point_s(const Td4Const& tc, const Td4Table& 
   if (has_sc) {
     const double ss = 0.5 * sqrt_fast(fmax(1.0 - c12 * c12, 0.0)) * sqrt_fast(fmax(1.0 - c34 * c34, 0.0));
     double sp, cp;
-    sincos_fast(phi, sp, cp);
+    sincos_fast<ALONE>(phi, sp, cp);
     p.ssc = ss * cp;
     p.sss = ss * sp;
   }
@@ -572,17 +581,17 @@ __device__ inline void td4_eval_body(const Td4Const& tc, const Td4Table* __restr
                                      const double* __restrict__ ev, int64_t ld, int64_t n,
                                      const double* __restrict__ norm, double* __restrict__ p) {
   const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  const int64_t q = i < n ? i : n - 1;  // all lanes run: the time functions vote by wave
+  if (i >= n) return;
   const Td4Table& tb = *tab;
   TimeFns T;
-  time_fns<false>(tb.tk, tc.wa, tc.wL, tb.x, tb.y, ev[5 * ld + q], T);
+  time_fns<false, true>(tb.tk, tc.wa, tc.wL, tb.x, tb.y, ev[5 * ld + i], T);
   Td4Point<S> pt;
-  td4_point_s<S>(tc, tb, ev[q], ev[ld + q], ev[2 * ld + q], ev[3 * ld + q], ev[4 * ld + q], pt);
+  td4_point_s<S, true>(tc, tb, ev[i], ev[ld + i], ev[2 * ld + i], ev[3 * ld + i], ev[4 * ld + i], pt);
   const cplx A = td4_sum<S, 0>(pt, tb.c), Ab = td4_sum<S, 1>(pt, tb.cb);
   const double a2 = A.re * A.re + A.im * A.im, b2 = Ab.re * Ab.re + Ab.im * Ab.im;
   const double zr = A.re * Ab.re + A.im * Ab.im, zi = A.re * Ab.im - A.im * Ab.re;
   const double R = 0.5 * ((a2 + b2) * T.Hc + (a2 - b2) * T.hr - 2.0 * zr * T.Hs - 2.0 * zi * T.hi);
-  if (i < n) p[i] = R / *norm;
+  p[i] = R / *norm;
 }
 
 // ------------------------------------------------------ four-body phase space
