@@ -84,8 +84,11 @@ __device__ __forceinline__ void accept_reject(AcceptLds& lds, int64_t n, int per
 // ran out of attempts is decided by the points it still has.  draw(i, a, x, y)
 // -> bool makes the point, test(i, a, x, y) -> bool decides it.
 // Half a million three-body toys (half of the draws outside): 282 -> 234 us a
-// call, 209 with the shorter region test; a million mixing ones 4.3 -> 3.1 ms,
-// 1000 of the former 52 (405 with one event per lane).
+// call, 209 with the shorter region test, 185 with whole sets of points to a
+// run's end too (its last events take draws they may not need: tests of 32 and
+// then of single points there were slower); a million mixing ones 4.3 -> 3.1 ms,
+// half a million 1.78 -> 1.47 ms with the latter, 1000 of the former 46 us (405
+// with one event per lane).
 struct StagedLds {
   int ev[kWaves][64], at[kWaves][64];       // open events and their next attempts
   int qe[kWaves][128], qa[kWaves][128];     // waiting points: event, attempt, place (a ring)
@@ -133,9 +136,7 @@ __device__ __forceinline__ void accept_reject_staged(StagedLds& lds, int64_t n, 
     order();
   };
   while (open > 0 || waiting > 0) {
-    // 2^sh lanes per open event: the most that 64 lanes give; once the run's
-    // last event is open a full set of points would take draws that its few
-    // events may not need
+    // 2^sh lanes per open event: the most that 64 lanes give
     order();
     while (open > 0) {
       const int sh = open > 1 ? __builtin_clz(open - 1) - 26 : 6;
@@ -158,7 +159,7 @@ __device__ __forceinline__ void accept_reject_staged(StagedLds& lds, int64_t n, 
       if (stays) pa[slot] = a + (1 << sh);
       if (__ballot(speaks != stays)) refill(stays, e, a + (1 << sh));
       order();
-      if (waiting >= (next < count ? 64 : (open > 16 ? 32 : 1))) break;
+      if (waiting >= 64) break;
     }
     const int m = waiting < 64 ? waiting : 64;
     const int q = (head + lane) & 127;
