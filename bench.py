@@ -76,12 +76,12 @@ def log_sum_flops(chunk: int) -> float:
 
 def chunk_in_use(m, n: int, per_cu: int) -> int:
     """Events per workgroup of a model without a fixed chunk: at most per_cu
-    workgroups per compute unit, at least the kind's default events (256 for
-    the amplitude models, m.chunk for mixtures)."""
+    workgroups per compute unit, a multiple of 256, at least the kind's least
+    (256 for the amplitude models, m.chunk for mixtures)."""
     import torch
     cus = torch.cuda.get_device_properties(0).multi_processor_count
     lo = m.chunk if per_cu == 8 else 256
-    return max(lo, -(-n // (per_cu * cus)))
+    return max(lo, -(-(-(-n // (per_cu * cus))) // 256) * 256)
 
 
 def dalitz_amp_flops(desc: dict) -> int:

@@ -33,9 +33,14 @@
  *    *_async ones only enqueue work.
  *  - A model may be used from one host thread and one stream at a time.
  *  - Results are deterministic: the event sum is a fixed two-level tree
- *    (a fixed chunk of events per workgroup, then a fixed-order sum of the
- *    chunk partials), so repeated calls, and the same fit alone or inside a
- *    batch, give bitwise identical values.
+ *    (a chunk of events per workgroup, then a fixed-order sum of the chunk
+ *    partials), so repeated calls, and the same fit alone or inside a batch,
+ *    give bitwise identical values.  The chunk follows from the number of
+ *    events and the device's compute units unless the model fixes it
+ *    (fn_model_create), so the last bits of a sum can differ between devices;
+ *    and the mixing models choose the form of their time functions per 64
+ *    events, so a term's last bits depend on the events beside it (fn_eval's
+ *    densities do not).
  *  - Non-finite or non-positive P~ at any event (or I <= 0) makes the NLL
  *    +inf, the gradient NaN, and the call returns FN_E_NONFINITE; a minimizer
  *    treats that as a rejected step.
@@ -125,8 +130,9 @@ typedef struct fn_model fn_model;
  *     entry, then sigma_t.
  *  Optional keys for every kind: "chunk" (events per workgroup, a multiple of
  *  256 in [256, 2^22]) -- it defines the summation tree; when given (or chosen
- *  by fn_model_autotune) it is the same for every sample, otherwise it
- *  follows from the number of events alone, by a rule of the kind.  dalitz3 only: "events_per_thread" (1, the
+ *  by fn_model_autotune) it is the same for every sample and device,
+ *  otherwise it follows from the number of events and the device's compute
+ *  units, by a rule of the kind.  dalitz3 only: "events_per_thread" (1, the
  *  default, or 2: events each thread of the events passes evaluates per loop
  *  iteration; a thread adds its events in index order either way, so the
  *  results are bitwise the same).
@@ -139,8 +145,9 @@ fn_status fn_model_create(fn_ctx* ctx, const char* desc_json, fn_model** out);
  * Returns FN_E_INVALID with the compiler log for a description that does not
  * compile.  Needs no GPU. */
 fn_status fn_model_check_compile(const char* desc_json, const char* arch);
-/* Number of parameters, observables, and the summation chunk of a model (the
- * kind's default where the chunk follows from the sample's size). */
+/* Number of parameters, observables, and the summation chunk of a model where
+ * it is fixed (otherwise a nominal one of its kind, which need not be that of
+ * any call). */
 fn_status fn_model_info(const fn_model* m, int32_t* n_params, int32_t* n_obs, int32_t* chunk);
 /* Frees the model's device memory.  Streams using it must be synchronised. */
 fn_status fn_model_destroy(fn_model* m);

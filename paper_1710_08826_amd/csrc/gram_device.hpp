@@ -12,7 +12,7 @@
 // x C accumulators per lane allowed no more) and took both triangles.
 //
 // A wave hands its 64 points' vectors over through its own LDS region,
-// kGramPoints at a time: lane p writes column p (rows of kGramPoints + 1
+// POINTS at a time: lane p writes column p (rows of POINTS + 1
 // doubles: consecutive banks), and the operand of tile t is read as row 16 t +
 // l % 16, point 4 s + l / 16 by lane l -- the layout of both MFMA operands,
 // since the right one is the transpose (the 16 lanes of one point lie in 16

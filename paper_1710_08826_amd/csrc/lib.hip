@@ -258,9 +258,8 @@ static void compile_dalitz3(const json::Value& d, fn_model* m, bool device = tru
   }
   m->P = dc.free_ls ? 4 * dc.K : 2 * dc.K;
   m->n_obs = 2;
-  // measured on MI355X with the structure-specialized kernels: 2048 events per
-  // workgroup is fastest for the coefficient gradient (17 sums per row) at 1M
-  // events, 4096 amortises the 33-sum rows of free lineshapes
+  // reported by fn_model_info and no more: without a fixed chunk the rule below
+  // (fn_model_create) sizes each call's
   m->chunk = dc.free_ls ? 4096 : 2048;
   m->grid_chunk = 1024;
   if (!device) return;
@@ -292,9 +291,7 @@ static void compile_tddp3(const json::Value& d, fn_model* m, bool device = true)
   td4_erfc_coefficients(m->tdt.we);
   m->P = 4 * dc.K + 2;
   m->n_obs = 3;
-  // two workgroups per compute unit in one round at 1M events on MI355X (NLL
-  // and gradient, sixteen resonances: 1024 86.7 us, 2048 77.4, 4096 80.4)
-  m->chunk = 2048;
+  m->chunk = 2048;  // reported, as above
   if (!device) return;
   m->tddp_jit = tddp_jit(dc, m->fixed_ls.data());
   m->d_table.reserve(sizeof(DalitzTable));
@@ -418,10 +415,7 @@ static void compile_td4(const json::Value& d, fn_model* m, bool device = true) {
   m->fixed_ls = fixed;
   m->P = tc.n_params;
   m->n_obs = 6;
-  // events per workgroup: median NLL + gradient on 10M events measured 588 /
-  // 550 / 532 / 538 us at 1024 / 2048 / 4096 / 8192 (fewer level-2 rows of
-  // 43 sums); fn_model_autotune refines it for a given sample
-  m->chunk = 4096;
+  m->chunk = 4096;  // reported, as above
   if (!device) return;
   m->td4_jit = td4_jit(tc);
   m->d_table.reserve(sizeof(Td4Table));
@@ -828,7 +822,8 @@ fn_status fn_model_create(fn_ctx* ctx, const char* desc_json, fn_model** out) {
     // compute unit it is cut into at most, and the least events for which a
     // workgroup's reduction pays.  The amplitude passes are bound by instruction
     // issue at two workgroups per compute unit (the mixing ones hold no more
-    // registers), and a small sample gets one event per thread on as many
+    // registers; 1M events, sixteen resonances: 1024 events 86.7 us, 2048 77.4,
+    // 4096 80.4), and a small sample gets one event per thread on as many
     // workgroups as it has; the mixture's loads need eight, and below
     // 1024 events its reduction costs more than it saves (1e5 events: 512 +30 %).
     // NLL and gradient against the fixed chunks (2048; 4096 for the mixing

@@ -126,7 +126,8 @@ __device__ inline bool mix1d_component(const Mix1dConst& mc, const double* __res
 }
 
 // The table entries past the components, the yield (extended likelihood) and
-// the validity flag; ok: every component's check.
+// the validity flag, by one thread once the components are in (the single-fit
+// prologue and batch_head give each component its own); ok: every component's check.
 __device__ inline void mix1d_table_rest(const Mix1dConst& mc, const double* __restrict__ th, bool ok, Mix1dTable& t) {
   for (int k = mc.K; k < kMixMaxComp; ++k) {
     t.frac[k] = 0.0; t.invN[k] = 0.0; t.a[k] = 0.0; t.b[k] = 0.0; t.c[k] = 0.0;
@@ -135,14 +136,6 @@ __device__ inline void mix1d_table_rest(const Mix1dConst& mc, const double* __re
   t.yield = mc.yidx >= 0 ? th[mc.yidx] : 0.0;
   if (mc.yidx >= 0 && !(t.yield > 0.0 && isfinite(t.yield))) ok = false;
   t.valid = ok ? 1.0 : 0.0;
-}
-
-// theta -> per-fit table, the components one after the other (one thread per
-// fit; the single-fit prologue gives each component its own thread).
-__device__ inline void mix1d_table(const Mix1dConst& mc, const double* __restrict__ th, Mix1dTable& out) {
-  bool ok = true;
-  for (int k = 0; k < mc.K; ++k) ok = mix1d_component(mc, th, k, out) && ok;
-  mix1d_table_rest(mc, th, ok, out);
 }
 
 // Component shape s(x) and d ln s / d(its parameters).

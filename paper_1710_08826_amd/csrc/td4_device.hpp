@@ -202,7 +202,7 @@ __device__ __forceinline__ void time_terms(TimeSeries& a, double v, double w, do
 // ALONE: each event takes the form its own r asks for, and its sine and cosine
 // likewise, so that its value does not depend on the others of its wave (the
 // density, which is handed out per event).  A wave with events of two forms then
-// takes both: 1M events, nine amplitudes, 43 us a call either way for mixing
+// takes both: 1M events, ten amplitudes, 43 us a call either way for mixing
 // parameters below 0.01, 57 instead of 53 at x = 0.8, whose events fall on both
 // sides of the line.
 template <bool GRAD, bool ALONE = false>
