@@ -78,11 +78,12 @@ __device__ inline bool mix1d_component(const Mix1dConst& mc, const double* __res
       if (fabs(td) < 1e-3) d0 = 0.5 * (hi + lo) + tau * D * D / 12.0 - td * td * td * D / 720.0;
       else d0 = lo + D / dn - 1.0 / tau;
       t.a[k] = tau;
-      // the events passes' form (mix_term): relative to the end of the range
-      // where the shape is largest, and 1 over its integral in these units
-      t.b[k] = tau > 0.0 ? hi : lo;
+      // the events passes' form, relative to the value at the mean d0 (mix_term):
+      // 1 over the integral relative to the end of the range where the shape is
+      // largest, taken to the mean by a factor between 1/e and 1
       const bool flat = fabs(tau) < 1e-12;
-      t.c[k] = (flat ? 1.0 : tau) / (flat ? D * (1.0 - 0.5 * fabs(td)) : (tau > 0.0 ? dn : up));
+      t.b[k] = (flat ? 1.0 : tau) / (flat ? D * (1.0 - 0.5 * fabs(td)) : (tau > 0.0 ? dn : up)) *
+               exp_fast(tau * (d0 - (tau > 0.0 ? hi : lo)));
       break;
     }
     case kArgus: {
@@ -191,11 +192,13 @@ __host__ __device__ constexpr int mix_sig_pivot(int sig) {
 
 // A component's shape at x as pre e^arg, and its derivatives' factors:
 // d ln s / d(its parameters) are alpha0 m0 and alpha1 m1, alpha constants of
-// the fit (mix_alpha).  An exponential is taken relative to its value at the
-// end of the range where it is largest (e^(tau (x - x0)), with its integral and
-// d ln N in the same units: mix_invn, mix_dlnn): its shape then spans (0, 1] as
-// the others do, whatever the slope.  Relative to x = 0 it reaches e^709 on
-// legal ranges, where sums weighted by it overflow and its weight is subnormal.
+// the fit (mix_alpha).  An exponential is taken relative to its value at its
+// mean d ln N / d tau, e^(tau (x - mean)), which is at most e times that on the
+// range whatever the slope (mix_invn: its weight in these units), and its
+// derivative's sum needs no second term (mix_dlnn).  Relative to x = 0 it reaches
+// e^709 on legal ranges, where sums weighted by it overflow and its weight is
+// subnormal, and both parts of the derivative grow with the range's distance
+// from zero.
 struct MixTerm {
   double pre, arg, m0, m1;
 };
@@ -206,7 +209,7 @@ __device__ __forceinline__ MixTerm mix_term(const Mix1dTable& t, int k, double x
     const double z = (x - t.a[k]) * t.b[k];
     r = {1.0, -0.5 * z * z, z, z * z};
   } else if (TYPE == kExp) {
-    const double d = x - t.b[k];
+    const double d = x - t.dlnN[k][0];
     r = {1.0, t.a[k] * d, d, 0.0};
   } else if (TYPE == kArgus) {
     const double xx = x * x, w = 1.0 - xx * t.a[k];
@@ -233,10 +236,10 @@ __device__ __forceinline__ double mix_alpha(const Mix1dTable& t, int k, int j) {
 
 // 1 / N_k and d ln N_k / d(parameter j) in mix_term's units.
 __device__ __forceinline__ double mix_invn(int type, const Mix1dTable& t, int k) {
-  return type == kExp ? t.c[k] : t.invN[k];
+  return type == kExp ? t.b[k] : t.invN[k];
 }
 __device__ __forceinline__ double mix_dlnn(int type, const Mix1dTable& t, int k, int j) {
-  return type == kExp && j == 0 ? t.dlnN[k][0] - t.b[k] : t.dlnN[k][j];
+  return type == kExp ? 0.0 : t.dlnN[k][j];
 }
 
 // slot[s] += w * dP/d(slot s) at one point: shape parameters of component k at
@@ -267,9 +270,9 @@ __device__ __forceinline__ void mix1d_add_dp(int K, const Mix1dTable& t, const d
 // N), fraction slot V_0/N_0 - V_1/N_1.  With a pivot p (mix_sig_pivot) the
 // density is e^arg_p (g_p + g_o pre_o e^d), d = arg_o - arg_p: one exponential
 // serves both components, and sum arg_p is the pivot's parameter times sum (x -
-// x0).  d is at most |tau| times the range's length, and where that exceeds
+// mean).  d is at most |tau| times the range's length, and where that exceeds
 // kPivotMax the larger of the two arguments is taken out instead, so that no
-// factor exceeds 1: e^d overflows from 709 on, and before that ln P is the small
+// factor of the two exceeds 1: e^d overflows from 709 on, and before that ln P is the small
 // difference of two parts (3e-14 of the sum at tau = -70 on [0, 10]).  Events
 // that overflow nevertheless lie outside the range, and the wave takes its
 // chunk again in that form.
