@@ -138,3 +138,31 @@ def test_four_body_structures(amps):
     for n in sizes(1024):
         say("fixed chunk td4 shape", spin1, n)
         compare(m, th, synth.td4_events(n, seed=n), lambda t, e: OT.nll_grad(t, e, mc, d), 1e-10, (spin1, n))
+
+
+@pytest.mark.parametrize("kind", ["dalitz3 free", "tddp3", "td4"])
+def test_presummed_rows(kind):
+    """Row sets long enough to be pre-summed by their own workgroups (above 256 KB, which the rule's rows reach only
+    for the widest rows), the last of them short: against few rows, which are not."""
+    from paper_1710_08826_amd import Model
+    n = 300 * 1024 + 300
+    say("presummed rows", kind)
+    if kind == "dalitz3 free":
+        d, th = synth.dalitz_desc(grid=(256, 256), free_lineshapes=True), synth.dalitz_truth(free_lineshapes=True)
+        ev = synth.dalitz_events(n, seed=5)
+    elif kind == "tddp3":
+        d, th, ev = synth.tddp3_desc16(grid=(64, 64)), synth.tddp3_truth16(), synth.tddp3_events(n, seed=5)
+    else:
+        d, th, ev = synth.td4_split_desc(), synth.td4_split_truth(), synth.td4_events(n, seed=5)
+    many, few = Model(dict(d, chunk=256)), Model(dict(d, chunk=16384))
+    if kind == "td4":
+        mc = to_dev(synth.td4_phase_space(2000, seed=41))
+        many.set_norm_sample(mc)
+        few.set_norm_sample(mc)
+    th = th * (1.0 + 0.01 * np.cos(np.arange(th.size)))
+    ev = to_dev(ev)
+    (v, g), (vo, go) = many.nll(th, ev, grad=True), few.nll(th, ev, grad=True)
+    # as in the tests of the rule: a few units over up to 1e5 terms
+    assert rel_close(v, vo, 1e-13), (v, vo)
+    ok, r = grad_close(g, go, 1e-12)
+    assert ok, r
