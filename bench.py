@@ -40,7 +40,7 @@ COUNTED_FP64_FLOPS_PER_EVENT = {(2048, 1): 404.9}
 TRAFFIC_SOURCES = ["paper_1710_08826_amd/csrc/dalitz_device.hpp", "paper_1710_08826_amd/csrc/dalitz3.hip",
                    "paper_1710_08826_amd/csrc/fastmath.hpp", "paper_1710_08826_amd/csrc/device_common.hpp",
                    "paper_1710_08826_amd/csrc/model.hpp"]
-TRAFFIC_HASH = "dd71866cab24fcd4"
+TRAFFIC_HASH = "5fb26d7351614b59"
 
 
 def counters_current() -> bool:

@@ -278,9 +278,9 @@ __device__ __forceinline__ void mix1d_add_dp(int K, const Mix1dTable& t, const d
 // chunk again in that form.
 // The Gaussian and exponential mixture takes 43 VALU instructions per event (52
 // relative to the larger argument) instead of 112 with an exponential for each:
-// NLL and gradient of 2^26 events 207 -> 149 us, 134 with the loads below (their
-// bytes alone take 88 at 6.1 TB/s), 149 at slopes past the line; 512 toy fits to
-// convergence 3.87 -> 3.23 ms.
+// NLL and gradient of 2^26 events 207 -> 149 us, 130 with the loads below (their
+// bytes alone take 88 at 6.1 TB/s) and a tenth more at slopes past the line; 512
+// toy fits to convergence 3.87 -> 3.23 ms.
 constexpr double kPivotMax = 16.0;
 template <bool GRAD, int SIG>
 __device__ inline void mix1d_typed_chunk(const Mix1dConst& mc, const Mix1dTable* __restrict__ tabp,
