@@ -272,10 +272,9 @@ __device__ __forceinline__ void mix1d_add_dp(int K, const Mix1dTable& t, const d
 // serves both components, and sum arg_p is the pivot's parameter times sum (x -
 // mean).  d is at most |tau| times the range's length, and where that exceeds
 // kPivotMax the larger of the two arguments is taken out instead, so that no
-// factor of the two exceeds 1: e^d overflows from 709 on, and before that ln P is the small
-// difference of two parts (3e-14 of the sum at tau = -70 on [0, 10]).  Events
-// that overflow nevertheless lie outside the range, and the wave takes its
-// chunk again in that form.
+// factor of the two exceeds 1: e^d overflows from 709 on, and d's rounding error
+// grows with it before that.  Events that overflow nevertheless lie outside the
+// range, and the wave takes its chunk again in that form.
 // The Gaussian and exponential mixture takes 43 VALU instructions per event (52
 // relative to the larger argument) instead of 112 with an exponential for each:
 // NLL and gradient of 2^26 events 207 -> 149 us, 130 with the loads below (their
